@@ -154,13 +154,14 @@ def work(case):
 
 def tolerance(case):
     # About four times what the same formulas in 64 bits showed.  Attention: bf16 probabilities and
-    # a bf16 result (2.1e-3, largest single difference 7.9e-3); the rest holds 32-bit sums (2.4e-6,
-    # largest 3.5e-6; longer rows were not tried) and whole numbers that only a tie could move.
+    # a bf16 result (2.1e-3, largest single difference 7.9e-3); the rest holds 32-bit sums and whole
+    # numbers that only a tie could move; probabilities pass on the absolute error of logits near
+    # 10, summed in another order they moved by 6.1e-6.
     if case["kind"] == "commit":
         return "exact"
     if case["kind"] in ("attn", "step"):
         return {"rel": 8e-3, "max": 3.2e-2, "differ": 2e-3}
-    return {"rel": 1e-5, "max": 5e-5, "differ": 2e-3}
+    return {"rel": 2.5e-5, "max": 1e-4, "differ": 2e-3}
 
 
 def _normal(gen, shape, std):
