@@ -38,8 +38,8 @@ KERNELS_OF = {
     "verify_attn": "lvspec_verify_attn = attn_split_kernel + attn_combine_kernel",
     "visual_relevance": ("lvspec_visual_relevance = gemm_stream_kernel<REL> + rel_cand_kernel + "
                          "rel_merge_kernel"),
-    "lm_head_accept": ("lvspec_loose_accept = gemm_stream_kernel<LMH> + accept_finalize_kernel + "
-                       "accept_decide_kernel"),
+    "lm_head_accept": ("lvspec_loose_accept = gemm_stream_kernel<LMH> + "
+                       "accept_finalize_kernel"),
 }
 # the configurations timed besides the headline (name, draft rows override, steps)
 EXTRA_WORKLOADS = [("c1", 0), ("c2", 0), ("c3", 0), ("c4", 3), ("c4", 8), ("c4t", 0), ("c5", 0)]

@@ -313,7 +313,8 @@ typedef struct {
   int32_t rel_stage_bytes;       /* bytes of a video row per pipeline stage: 256 or 512 */
   int32_t rel_slices;            /* slices of the two-kernel Top-N; 0 = single-kernel selection */
   int32_t rel_slice_rows;        /* video rows per slice */
-  int32_t acc_rows_per_task;     /* vocabulary rows per lm_head task: 64 or 128 */
+  int32_t acc_rows_per_task;     /* vocabulary rows per lm_head task: 64 or 128 (one or two
+                                    blocks of 64, or one of 128) */
   int32_t acc_chains_per_pass;   /* chains served by one pass over lm_head */
   int32_t acc_passes;            /* passes over lm_head */
 } lvspec_plan_info;

@@ -7,13 +7,12 @@
 //                  Top-N largest cosines per draft row (paper Eq. 8).  The N-th largest value
 //                  is found exactly (duplicates count by value) and the sum is taken in fixed
 //                  point, so the result does not depend on thread scheduling.
-// accept_finalize: merges the per-vocabulary-block (max, sum exp, top-k candidates) into the
+// accept_finalize: merges the per-workgroup (max, sum exp, top-k candidates) of lm_head into the
 //                  greedy target token and the k most probable tokens per draft row
-//                  (optionally the row's softmax entropy).
-// accept_decide:   one wave per chain, one lane per draft position: the paper's Eq. 9
-//                  (loosened set), Eq. 10/11 (verdicts incl. position-shift tolerance) and
-//                  Eq. 2 (accepted length = longest accepted prefix); the chains of a draft
-//                  tree share a workgroup, which then keeps the longest one.
+//                  (optionally the row's softmax entropy), then the paper's Eq. 9 (loosened
+//                  set), Eq. 10/11 (verdicts incl. position-shift tolerance) and Eq. 2 (accepted
+//                  length = longest accepted prefix); the chains of a draft tree share a
+//                  workgroup, which then keeps the longest one.
 #include "lvspec_dev.h"
 #include "lvspec_kernels.h"
 
@@ -350,387 +349,232 @@ __global__ __launch_bounds__(kFinThreads) void rel_finalize_kernel(const RelFina
 }
 
 // ------------------------------------------------------------------------------------------
-constexpr int kAccThreads = 1024;
-constexpr int kAccWaves = kAccThreads / 64;
-constexpr int kCandRegs = 20;     // candidates a thread can keep in registers (V = 152064, k = 16)
+constexpr int kAccWaves = 16;          // waves of the merge at most
+constexpr int kRecRegs = 8;            // records per lane: kAcceptMaxRecords / 64
+constexpr int kPickedMax = 32;         // records the short way of the selection can take
 
-// (value desc, id asc) order, written without short-circuit branches
-LVS_DEV bool better(float v, int id, float bv, int bid) {
-  return (v > bv) | ((v == bv) & (id < bid));
+// Largest T with at least k of the wave's keys >= T (0 = no key; fewer than k keys: T = 1), found
+// bit by bit from the first bit in which the keys differ; exact unless it can stop early because
+// exactly k keys are left.
+template <int NV>
+LVS_DEV uint32_t kth_bound(const uint32_t (&key)[NV], int k) {
+  uint32_t hi = key[0], nlo = 0u;      // largest key; largest complement = smallest key
+  int have = 0;
+#pragma unroll
+  for (int u = 0; u < NV; ++u) {
+    hi = max(hi, key[u]);
+    nlo = max(nlo, key[u] != 0u ? ~key[u] : 0u);
+    have += __popcll(__ballot(key[u] != 0u));
+  }
+  if (have <= k) return 1u;
+  hi = wave_max_u32(hi);
+  const uint32_t lo = ~wave_max_u32(nlo);
+  if (hi == lo) return hi;
+  const int top = 31 - __clz((int)(hi ^ lo));
+  uint32_t T = hi & ~((2u << top) - 1u);     // (top = 31: 2u << 31 = 0, T = 0)
+  for (int bit = top; bit >= 0; --bit) {
+    const uint32_t c = T | (1u << bit);
+    int n = 0;
+#pragma unroll
+    for (int u = 0; u < NV; ++u) n += __popcll(__ballot(key[u] >= c));
+    if (n >= k) T = c;
+    if (n == k) break;
+  }
+  return T;
 }
 
-// Merge of the per-vocabulary-block statistics and top-k candidates of one logits column when
-// all candidates fit in registers (kCandRegs per thread: any k at V = 152064).  Every wave
-// first selects the k best of its own candidates with k wave-wide maxima over the DPP network
-// (no LDS, no barrier), then wave 0 selects the k best of the 16 x k survivors the same way:
-// two barriers in the whole kernel.  SLOTS = candidates per thread, a compile-time bound so that
-// the loops over them carry no branches (a taken branch costs about as much as five vector
-// instructions, and there would be two per slot and round).
-template <int SLOTS>
-__global__ __launch_bounds__(kAccThreads) void accept_finalize_kernel(const AcceptFinalizeArgs p) {
-  __shared__ float red_max[kAccWaves], red_sum[kAccWaves], red_sz[kAccWaves];
-  __shared__ uint64_t sm_keys[kAccWaves * 16];
-  const int i = blockIdx.x;
-  const int b = blockIdx.y;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int col = b * p.rows + i;
-  const int n_cand = p.n_tasks * p.topk;
-  LVS_TRACE_BEGIN;
-  LVS_TRACE(0);
-
-  // candidates of this thread (requested first: they are not needed before the rounds below)
-  float cv[SLOTS];
-  int ci[SLOTS];
-#pragma unroll
-  for (int u = 0; u < SLOTS; ++u) {
-    const int c = tid + u * kAccThreads;
-    const int cc = c < n_cand ? c : n_cand - 1;
-    const int t = (int)fast_div((uint32_t)cc, p.div_topk);
-    const int e = cc - t * p.topk;
-    const int64_t off = ((int64_t)t * p.n_cols + col) * p.topk + e;
-    ci[u] = p.cand_idx[off];     // (no use of the loaded values here: a select on them
-    cv[u] = p.cand_val[off];     // would make every slot wait for its own load)
-  }
-  LVS_TRACE(1);
-  // global max and denominator over the vocabulary blocks
-  constexpr int kStatRegs = 2;
-  float smax[kStatRegs], ssum[kStatRegs];
-  float mx = -INFINITY;
-#pragma unroll
-  for (int u = 0; u < kStatRegs; ++u) {
-    const int t = tid + u * kAccThreads;
-    smax[u] = -INFINITY;
-    ssum[u] = 0.f;
-    if (t < p.n_tasks) {
-      const float* st = p.stats + ((int64_t)t * p.n_cols + col) * 2;
-      smax[u] = st[0];
-      ssum[u] = st[1];
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < kStatRegs; ++u) mx = fmaxf(mx, smax[u]);
-  for (int t = tid + kStatRegs * kAccThreads; t < p.n_tasks; t += kAccThreads)
-    mx = fmaxf(mx, p.stats[((int64_t)t * p.n_cols + col) * 2]);
-  mx = wave_max(mx);
-  if (lane == 0) red_max[wave] = mx;
-  LVS_TRACE(5);
-
-  // ---- the k best candidates of this wave ---------------------------------------------------
-  uint64_t key[SLOTS];
-#pragma unroll
-  for (int u = 0; u < SLOTS; ++u)   // slots past the end hold a clamped copy
-    key[u] = tid + u * kAccThreads < n_cand ? cand_key(cv[u], ci[u]) : 0ull;
-  uint64_t mine = 0;     // lane r keeps the wave's r-th best
-  for (int r = 0; r < p.topk; ++r) {
-    uint64_t best = 0;
-#pragma unroll
-    for (int u = 0; u < SLOTS; ++u) best = key[u] > best ? key[u] : best;
-    const uint64_t w = wave_max_u64(best);
-#pragma unroll
-    for (int u = 0; u < SLOTS; ++u) key[u] = key[u] == w ? 0ull : key[u];
-    mine = lane == r ? w : mine;
-  }
-  if (lane < p.topk) sm_keys[wave * 16 + lane] = mine;
-  LVS_TRACE(6);
-  __syncthreads();
-  LVS_TRACE(2);
-  mx = wave_max(lane < kAccWaves ? red_max[lane] : -INFINITY);
-  float se = 0.f;
-#pragma unroll
-  for (int u = 0; u < kStatRegs; ++u) se += ssum[u] * __expf(smax[u] - mx);
-  for (int t = tid + kStatRegs * kAccThreads; t < p.n_tasks; t += kAccThreads) {
-    const float* st = p.stats + ((int64_t)t * p.n_cols + col) * 2;
-    se += st[1] * __expf(st[0] - mx);
-  }
-  se = wave_sum(se);
-  if (lane == 0) red_sum[wave] = se;
-  if (p.entropy != nullptr) {   // same rescaling for the blocks' sum exp(z - max) * z
-    float sz = 0.f;
-    for (int t = tid; t < p.n_tasks; t += kAccThreads) {
-      const int64_t rec = (int64_t)t * p.n_cols + col;
-      sz += p.stats_z[rec] * __expf(p.stats[rec * 2] - mx);
-    }
-    sz = wave_sum(sz);
-    if (lane == 0) red_sz[wave] = sz;
-  }
-  __syncthreads();
-  LVS_TRACE(3);
-  if (wave != 0) return;
-
-  // ---- wave 0: the k best of the 16 x k survivors, denominators, results --------------------
-  se = wave_sum(lane < kAccWaves ? red_sum[lane] : 0.f);
-  if (p.entropy != nullptr) {
-    // H = -sum p ln p with p = exp(z - max) / se:  ln se + max - (sum exp(z - max) z) / se
-    const float sz = wave_sum(lane < kAccWaves ? red_sz[lane] : 0.f);
-    if (lane == 0) p.entropy[col] = __logf(se) + mx - sz / se;
-  }
-  uint64_t k4[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int idx = lane + 64 * j;          // wave idx / 16, rank idx % 16
-    k4[j] = (idx & 15) < p.topk ? sm_keys[idx] : 0ull;
-  }
-  mine = 0;
-  for (int r = 0; r < p.topk; ++r) {
-    uint64_t best = k4[0] > k4[1] ? k4[0] : k4[1];
-    const uint64_t b2 = k4[2] > k4[3] ? k4[2] : k4[3];
-    best = best > b2 ? best : b2;
-    const uint64_t w = wave_max_u64(best);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) k4[j] = k4[j] == w ? 0ull : k4[j];
-    mine = lane == r ? w : mine;
-  }
-  if (lane < p.topk) {
-    const bool none = mine == 0ull;
-    const float win_v = key_value((uint32_t)(mine >> 32));
-    const int out_id = none ? -1 : 0x7fffffff - (int)(uint32_t)mine;
-    const float prob = none ? 0.f : __expf(win_v - mx) / se;
-    if (lane == 0) p.target_ids[col] = out_id;
-    p.ws_topk_ids[col * 16 + lane] = out_id;
-    if (p.topk_ids) p.topk_ids[(int64_t)col * p.topk + lane] = out_id;
-    if (p.topk_probs) p.topk_probs[(int64_t)col * p.topk + lane] = prob;
-  }
-  LVS_TRACE(4);
-  LVS_TRACE_END;
-}
-
-// The same merge for candidate counts beyond the register budget: every round re-reads the
-// candidates from memory.
-__global__ __launch_bounds__(kAccThreads) void accept_finalize_general_kernel(
-    const AcceptFinalizeArgs p) {
-  __shared__ float redf[2][kAccWaves];
-  __shared__ int redi[2][kAccWaves];
-  const int i = blockIdx.x;
-  const int b = blockIdx.y;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int col = b * p.rows + i;
-  const int n_cand = p.n_tasks * p.topk;
-  const bool in_regs = n_cand <= kCandRegs * kAccThreads;
-  LVS_TRACE_BEGIN;
-  LVS_TRACE(0);
-
-  // candidates of this thread (requested first: they are not needed before the rounds below)
-  float cv[kCandRegs];
-  int ci[kCandRegs];
-  if (in_regs) {
-#pragma unroll
-    for (int u = 0; u < kCandRegs; ++u) {
-      const int c = tid + u * kAccThreads;
-      cv[u] = -INFINITY;
-      ci[u] = -1;
-      if (c < n_cand) {
-        const int t = c / p.topk;
-        const int e = c - t * p.topk;
-        const int64_t off = ((int64_t)t * p.n_cols + col) * p.topk + e;
-        ci[u] = p.cand_idx[off];
-        cv[u] = p.cand_val[off];
-      }
-    }
-  }
-
-  LVS_TRACE(1);
-  // global max and denominator over the vocabulary blocks (each block's pair loaded once)
-  constexpr int kStatRegs = 2;
-  float smax[kStatRegs], ssum[kStatRegs];
-  float mx = -INFINITY;
-#pragma unroll
-  for (int u = 0; u < kStatRegs; ++u) {
-    const int t = tid + u * kAccThreads;
-    smax[u] = -INFINITY;
-    ssum[u] = 0.f;
-    if (t < p.n_tasks) {
-      const float* st = p.stats + ((int64_t)t * p.n_cols + col) * 2;
-      smax[u] = st[0];
-      ssum[u] = st[1];
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < kStatRegs; ++u) mx = fmaxf(mx, smax[u]);
-  for (int t = tid + kStatRegs * kAccThreads; t < p.n_tasks; t += kAccThreads)
-    mx = fmaxf(mx, p.stats[((int64_t)t * p.n_cols + col) * 2]);
-#pragma unroll
-  for (int s = 1; s < 64; s <<= 1) mx = fmaxf(mx, __shfl_xor(mx, s, 64));
-  if (lane == 0) redf[0][wave] = mx;
-  __syncthreads();
-  mx = redf[0][0];
-  for (int w = 1; w < kAccWaves; ++w) mx = fmaxf(mx, redf[0][w]);
-  LVS_TRACE(2);
-  float se = 0.f;
-#pragma unroll
-  for (int u = 0; u < kStatRegs; ++u) se += ssum[u] * __expf(smax[u] - mx);
-  for (int t = tid + kStatRegs * kAccThreads; t < p.n_tasks; t += kAccThreads) {
-    const float* st = p.stats + ((int64_t)t * p.n_cols + col) * 2;
-    se += st[1] * __expf(st[0] - mx);
-  }
-#pragma unroll
-  for (int s = 1; s < 64; s <<= 1) se += __shfl_xor(se, s, 64);
-  if (lane == 0) redf[1][wave] = se;
-  __syncthreads();
-  se = 0.f;
-  for (int w = 0; w < kAccWaves; ++w) se += redf[1][w];
-  __syncthreads();
-  if (p.entropy != nullptr) {   // see accept_finalize_kernel
-    float sz = 0.f;
-    for (int t = tid; t < p.n_tasks; t += kAccThreads) {
-      const int64_t rec = (int64_t)t * p.n_cols + col;
-      sz += p.stats_z[rec] * __expf(p.stats[rec * 2] - mx);
-    }
-    sz = wave_sum(sz);
-    if (lane == 0) redf[1][wave] = sz;
-    __syncthreads();
-    sz = 0.f;
-    for (int w = 0; w < kAccWaves; ++w) sz += redf[1][w];
-    if (tid == 0) p.entropy[col] = __logf(se) + mx - sz / se;
-    __syncthreads();
-  }
-
-  LVS_TRACE(3);
-  // k rounds: best candidate strictly after the previous winner in (value desc, id asc) order
-  float pv = INFINITY, win_v = -INFINITY;
-  int pid = -1, win_i = -1;
-  for (int r = 0; r < p.topk; ++r) {
-    float bv = -INFINITY;
-    int bid = 0x7fffffff;
-    if (in_regs) {
-#pragma unroll
-      for (int u = 0; u < kCandRegs; ++u) {
-        const bool after_prev = (cv[u] < pv) | ((cv[u] == pv) & (ci[u] > pid));
-        const bool take = (ci[u] >= 0) & after_prev & better(cv[u], ci[u], bv, bid);
-        bv = take ? cv[u] : bv;
-        bid = take ? ci[u] : bid;
-      }
-    } else {
-      for (int c = tid; c < n_cand; c += kAccThreads) {
-        const int t = c / p.topk;
-        const int e = c - t * p.topk;
-        const int64_t off = ((int64_t)t * p.n_cols + col) * p.topk + e;
-        const int id = p.cand_idx[off];
-        const float v = p.cand_val[off];
-        const bool after_prev = v < pv || (v == pv && id > pid);
-        if (id >= 0 && after_prev && better(v, id, bv, bid)) {
-          bv = v;
-          bid = id;
-        }
-      }
-    }
-#pragma unroll
-    for (int s = 1; s < 64; s <<= 1) {
-      const float ov = __shfl_xor(bv, s, 64);
-      const int oi = __shfl_xor(bid, s, 64);
-      const bool take = better(ov, oi, bv, bid);
-      bv = take ? ov : bv;
-      bid = take ? oi : bid;
-    }
-    const int buf = r & 1;
-    if (lane == 0) {
-      redf[buf][wave] = bv;
-      redi[buf][wave] = bid;
-    }
-    __syncthreads();
-    pv = redf[buf][0];
-    pid = redi[buf][0];
-#pragma unroll
-    for (int w = 1; w < kAccWaves; ++w) {
-      const float ov = redf[buf][w];
-      const int oi = redi[buf][w];
-      const bool take = better(ov, oi, pv, pid);
-      pv = take ? ov : pv;
-      pid = take ? oi : pid;
-    }
-    if (tid == r) {   // thread r keeps the winner of round r; results are stored after the loop
-      win_v = pv;     // (a store inside the loop would be waited for at every barrier)
-      win_i = pid;
-    }
-  }
-  if (tid < p.topk) {
-    const int out_id = win_v == -INFINITY ? -1 : win_i;
-    const float prob = win_v == -INFINITY ? 0.f : __expf(win_v - mx) / se;
-    if (tid == 0) p.target_ids[col] = out_id;
-    p.ws_topk_ids[col * 16 + tid] = out_id;
-    if (p.topk_ids) p.topk_ids[(int64_t)col * p.topk + tid] = out_id;
-    if (p.topk_probs) p.topk_probs[(int64_t)col * p.topk + tid] = prob;
-  }
-  LVS_TRACE(4);
-  LVS_TRACE_END;
-}
-
-// One workgroup per sequence, one wave per chain of its draft tree (a plain chain draft is a
-// tree with one branch), one lane per draft position: loosened set (Eq. 9), verdicts (Eq. 10 /
-// 11), accepted length (Eq. 2) per chain, then the chain with the longest accepted length
-// (appendix on draft token trees).  Everything a position needs from the others comes through
-// v_readlane in a loop over the positions, so there is no serial single-lane code and no LDS
-// traffic.  Runs after accept_finalize_kernel in stream order, so the target tokens are visible
-// without any in-kernel fence.
-__global__ __launch_bounds__(64 * kMaxBranches) void accept_decide_kernel(
-    const AcceptFinalizeArgs p) {
+// One workgroup per sequence, for both halves of the acceptance.
+// First the merge, one wave per hidden row (rows beyond sixteen in turn): the records lm_head
+// left of the row (one per workgroup of that launch) become the greedy target token, the k most
+// probable tokens and (optionally) the softmax entropy.  The k best candidates can only come from
+// the k records with the largest maxima, and the maxima are needed for the softmax sum anyway: so
+// the wave looks for the k-th largest maximum (kth_bound) and fetches the candidates of those
+// records alone, k * k instead of all (5 rows, 475 records, k = 4: 16 of 1900).  What bounds this
+// kernel is the number of instructions and dependent loads on one CU.  Measured (rocprofv3, against
+// a merge over one record per 64 vocabulary rows followed by a launch of its own for the rule):
+// 5 rows, V = 152064: k = 4 9.5 + 4.8 -> 7.0 us, k = 16 28.4 + 4.6 -> 11.4; 48 rows, k = 4
+// 18.8 + 4.8 -> 8.4.
+// Then, behind one barrier, the rule: one wave per chain of the sequence's draft tree (a plain
+// chain draft is a tree with one branch), one lane per draft position: loosened set (Eq. 9),
+// verdicts (Eq. 10 / 11), accepted length (Eq. 2) per chain, then the chain with the longest
+// accepted length (appendix on draft token trees).  Everything a position needs from the others
+// comes through v_readlane in a loop over the positions.
+__global__ __launch_bounds__(64 * kAccWaves) void accept_finalize_kernel(const AcceptFinalizeArgs p) {
+  __shared__ int sm_pick[kAccWaves][kPickedMax];
+  __shared__ int sh_y[kAcceptMaxRows];
+  __shared__ int sh_top[kAcceptMaxRows][16];
+  __shared__ float sh_ent[kAcceptMaxRows];
   __shared__ int sh_tau[kMaxBranches];
   const int seq = blockIdx.x;
   const int lane = threadIdx.x & 63;
-  const int br = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // branch of this wave
-  const int b = seq * p.n_branches + br;                             // chain index
-  const int g = p.gamma;
-  const bool on = lane < g;
-  const int idx = b * g + (on ? lane : 0);                 // draft position of this lane
-  const int row = b * p.rows + (lane < p.rows ? lane : 0);  // hidden row of this lane
-  const int dk = p.draft_ids[idx];
-  const int yk = p.target_ids[row];
-  unsigned char vd = 0;
-  if (p.rule == 0) {
-    const float ak = p.relevance[idx];
-    int gate_ok = 1;
-    if (p.gate > 0) {
-      gate_ok = 0;
-      for (int e = 0; e < p.gate; ++e) gate_ok |= (p.ws_topk_ids[row * 16 + e] == dk);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n_waves = (int)(blockDim.x >> 6);
+  const int R = p.n_branches * p.rows;      // hidden rows of this sequence
+  const bool want_z = p.stats_z != nullptr;
+  const int n_rec = p.n_rec;
+
+  for (int row = wave; row < R; row += n_waves) {
+    const int64_t col = (int64_t)seq * R + row;
+    const float2* st = reinterpret_cast<const float2*>(p.stats) + col * n_rec;
+    const uint64_t* ck = p.cand + col * n_rec * p.topk;
+    // ---- softmax statistics over the records
+    float2 ms[kRecRegs];
+    float z[kRecRegs];
+#pragma unroll
+    for (int u = 0; u < kRecRegs; ++u) {
+      const int i = 64 * u + lane;
+      const int ic = i < n_rec ? i : n_rec - 1;
+      ms[u] = st[ic];
+      z[u] = want_z ? p.stats_z[col * n_rec + ic] : 0.f;
     }
-    // position of this lane in the stable ascending order of the relevance scores (Eq. 9: the
-    // n_loose first are loosened), and whether its target token occurs among the other drafts
-    // within the shift window (Eq. 11)
-    int rank = 0;
-    bool shifted = false;
-    for (int j = 0; j < g; ++j) {
-      const float aj = __builtin_bit_cast(
-          float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, ak), j));
-      const int dj = __builtin_amdgcn_readlane(dk, j);
-      rank += ((aj < ak) | ((aj == ak) & (j < lane))) ? 1 : 0;
-      const int dist = j > lane ? j - lane : lane - j;
-      shifted |= (j != lane) & (dist <= p.pst_window) & (dj == yk);
+    float mx = -INFINITY;
+    uint32_t mkey[kRecRegs];
+#pragma unroll
+    for (int u = 0; u < kRecRegs; ++u) {
+      const bool on = 64 * u + lane < n_rec;
+      ms[u].x = on ? ms[u].x : -INFINITY;
+      mkey[u] = ms[u].x != -INFINITY ? order_key(ms[u].x) : 0u;
+      mx = fmaxf(mx, ms[u].x);
     }
-    if (dk == yk) {
-      vd = 1;
-    } else if (rank < p.n_loose && gate_ok) {
-      vd = 2;
-    } else if (p.pst_window > 0 && shifted) {
-      vd = 3;
+    // ---- records that can hold one of the k best
+    const uint32_t bound = kth_bound<kRecRegs>(mkey, p.topk);
+    int picked = 0;
+#pragma unroll
+    for (int u = 0; u < kRecRegs; ++u) {
+      const bool q = mkey[u] >= bound;
+      const unsigned long long mask = __ballot(q);
+      const int slot = picked + __popcll(mask & ((1ull << lane) - 1ull));
+      if (q && slot < kPickedMax) sm_pick[wave][slot] = 64 * u + lane;
+      picked += __popcll(mask);
     }
-  } else {
-    // Entropy-gated rules of the text-only loose methods the paper compares against: a
-    // mismatch passes when its row's entropy exceeds the threshold and (rule 2) the w
-    // positions behind it are all draft positions that match exactly.  The row entropies were
-    // written by accept_finalize_kernel earlier in stream order.
-    const float hk = p.ent_rows[row];
-    const unsigned long long exact = __ballot(on && dk == yk);
-    const int w = p.rule == 2 ? p.defer_window : 0;
-    const unsigned long long need = ((1ull << w) - 1ull) << (on ? lane + 1 : 0);   // < 2^33
-    const bool confirmed = (lane + w <= g - 1) && ((exact & need) == need);
-    if (dk == yk) {
-      vd = 1;
-    } else if (hk > p.ent_threshold && confirmed) {
-      vd = 4;
+    uint64_t top = 0ull;
+    if (picked <= kPickedMax) {
+      const int nk = picked * p.topk;
+      for (int k0 = 0; k0 < nk; k0 += 256) {
+        uint64_t key[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int i = k0 + 64 * u + lane;
+          const int ic = i < nk ? i : nk - 1;
+          const int t = (int)fast_div((uint32_t)ic, p.div_topk);
+          const int e = ic - t * p.topk;
+          key[u] = ck[(int64_t)sm_pick[wave][t] * p.topk + e];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) key[u] = k0 + 64 * u + lane < nk ? key[u] : 0ull;
+        topk_insert<4>(top, key, p.topk, lane);
+      }
+    } else {
+      // (many records share the k-th largest maximum) all candidates
+      const int nk = n_rec * p.topk;
+      for (int k0 = 0; k0 < nk; k0 += 256) {
+        uint64_t key[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int i = k0 + 64 * u + lane;
+          key[u] = i < nk ? ck[i] : 0ull;
+        }
+        topk_insert<4>(top, key, p.topk, lane);
+      }
+    }
+    // ---- results of the row
+    mx = wave_max(mx);
+    float se = 0.f, sz = 0.f;
+#pragma unroll
+    for (int u = 0; u < kRecRegs; ++u) {
+      const float f = ms[u].x == -INFINITY ? 0.f : fast_exp2((ms[u].x - mx) * kLog2e);
+      se += ms[u].y * f;
+      sz += z[u] * f;
+    }
+    se = wave_sum(se);
+    if (want_z) {
+      // H = -sum p ln p with p = exp(z - max) / se:  ln se + max - (sum exp(z - max) z) / se
+      sz = wave_sum(sz);
+      const float ent = __logf(se) + mx - sz / se;
+      if (lane == 0) {
+        sh_ent[row] = ent;
+        if (p.entropy) p.entropy[col] = ent;
+      }
+    }
+    if (lane < p.topk) {
+      const bool none = top == 0ull;
+      const float win_v = key_value((uint32_t)(top >> 32));
+      const int id = none ? -1 : 0x7fffffff - (int)(uint32_t)top;
+      const float prob = none ? 0.f : __expf(win_v - mx) / se;
+      if (lane == 0) {
+        p.target_ids[col] = id;
+        sh_y[row] = id;
+      }
+      sh_top[row][lane] = id;
+      if (p.topk_ids) p.topk_ids[col * p.topk + lane] = id;
+      if (p.topk_probs) p.topk_probs[col * p.topk + lane] = prob;
     }
   }
-  if (on) p.verdict[idx] = vd;
-  const unsigned long long rejected = __ballot(on && vd == 0);
-  const int tau = rejected ? __ffsll((long long)rejected) - 1 : g;   // first rejected position
-  // the target's token at the first rejected position, or the one after the last draft when
-  // the chain brought that row
-  const int bonus = __builtin_amdgcn_readlane(yk, tau < p.rows ? tau : 0);
-  if (lane == 0) {
-    p.accept_len[b] = tau;
-    p.bonus_id[b] = tau < p.rows ? bonus : -1;
-    sh_tau[br] = tau;
+  __syncthreads();
+
+  const int br = wave;                                     // branch of this wave
+  if (br < p.n_branches) {
+    const int b = seq * p.n_branches + br;                 // chain index
+    const int g = p.gamma;
+    const bool on = lane < g;
+    const int idx = b * g + (on ? lane : 0);                      // draft position of this lane
+    const int row = br * p.rows + (lane < p.rows ? lane : 0);     // hidden row of this lane
+    const int dk = p.draft_ids[idx];
+    const int yk = sh_y[row];
+    unsigned char vd = 0;
+    if (p.rule == 0) {
+      const float ak = p.relevance[idx];
+      int gate_ok = 1;
+      if (p.gate > 0) {
+        gate_ok = 0;
+        for (int e = 0; e < p.gate; ++e) gate_ok |= (sh_top[row][e] == dk);
+      }
+      // position of this lane in the stable ascending order of the relevance scores (Eq. 9: the
+      // n_loose first are loosened), and whether its target token occurs among the other drafts
+      // within the shift window (Eq. 11)
+      int rank = 0;
+      bool shifted = false;
+      for (int j = 0; j < g; ++j) {
+        const float aj = __builtin_bit_cast(
+            float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, ak), j));
+        const int dj = __builtin_amdgcn_readlane(dk, j);
+        rank += ((aj < ak) | ((aj == ak) & (j < lane))) ? 1 : 0;
+        const int dist = j > lane ? j - lane : lane - j;
+        shifted |= (j != lane) & (dist <= p.pst_window) & (dj == yk);
+      }
+      if (dk == yk) {
+        vd = 1;
+      } else if (rank < p.n_loose && gate_ok) {
+        vd = 2;
+      } else if (p.pst_window > 0 && shifted) {
+        vd = 3;
+      }
+    } else {
+      // Entropy-gated rules of the text-only loose methods the paper compares against: a
+      // mismatch passes when its row's entropy exceeds the threshold and (rule 2) the w
+      // positions behind it are all draft positions that match exactly.
+      const float hk = sh_ent[row];
+      const unsigned long long exact = __ballot(on && dk == yk);
+      const int w = p.rule == 2 ? p.defer_window : 0;
+      const unsigned long long need = ((1ull << w) - 1ull) << (on ? lane + 1 : 0);   // < 2^33
+      const bool confirmed = (lane + w <= g - 1) && ((exact & need) == need);
+      if (dk == yk) {
+        vd = 1;
+      } else if (hk > p.ent_threshold && confirmed) {
+        vd = 4;
+      }
+    }
+    if (on) p.verdict[idx] = vd;
+    const unsigned long long rejected = __ballot(on && vd == 0);
+    const int tau = rejected ? __ffsll((long long)rejected) - 1 : g;   // first rejected position
+    // the target's token at the first rejected position, or the one after the last draft when
+    // the chain brought that row
+    const int bonus = __builtin_amdgcn_readlane(yk, tau < p.rows ? tau : 0);
+    if (lane == 0) {
+      p.accept_len[b] = tau;
+      p.bonus_id[b] = tau < p.rows ? bonus : -1;
+      sh_tau[br] = tau;
+    }
   }
   __syncthreads();
   if (threadIdx.x == 0 && p.best_branch != nullptr) {
@@ -942,22 +786,12 @@ hipError_t launch_rel_finalize(const RelFinalizeArgs& a, hipStream_t stream) {
 }
 
 hipError_t launch_accept_finalize(const AcceptFinalizeArgs& a, hipStream_t stream) {
-  static_assert(kCandRegs * kAccThreads == kAcceptRegCandidates, "planner and merge kernel agree");
-  const int64_t n_cand = (int64_t)a.n_tasks * a.topk;
-  const dim3 grid(a.rows, a.B);
-  if (n_cand <= 5 * kAccThreads)
-    hipLaunchKernelGGL(accept_finalize_kernel<5>, grid, dim3(kAccThreads), 0, stream, a);
-  else if (n_cand <= 10 * kAccThreads)
-    hipLaunchKernelGGL(accept_finalize_kernel<10>, grid, dim3(kAccThreads), 0, stream, a);
-  else if (n_cand <= (int64_t)kCandRegs * kAccThreads)
-    hipLaunchKernelGGL(accept_finalize_kernel<kCandRegs>, grid, dim3(kAccThreads), 0, stream, a);
-  else
-    hipLaunchKernelGGL(accept_finalize_general_kernel, grid, dim3(kAccThreads), 0,
-                       stream, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(accept_decide_kernel, dim3(a.B / a.n_branches), dim3(64 * a.n_branches), 0,
-                     stream, a);
+  static_assert(kRecRegs * 64 == kAcceptMaxRecords, "records per lane");
+  const int R = a.n_branches * a.rows;
+  if (R > kAcceptMaxRows || a.topk > 16 || a.n_rec > kAcceptMaxRecords || a.n_branches > kMaxBranches)
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(accept_finalize_kernel, dim3(a.B / a.n_branches),
+                     dim3(64 * (R < kAccWaves ? R : kAccWaves)), 0, stream, a);
   return hipGetLastError();
 }
 

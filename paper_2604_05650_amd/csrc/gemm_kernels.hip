@@ -4,9 +4,9 @@
 //       H_D [gamma, d]; the kernel emits raw dot products and squared row norms per split of d;
 //       a finalize kernel turns them into cosines and the mean of the Top-N.
 //   lm_head (paper Eq. 6):    A = lm_head [V, d], X = the B*gamma final hidden rows; the
-//       epilogue reduces each block of vocabulary rows to (max, sum exp, top-k candidates) per
-//       column, so the gamma x V logits never have to be re-read (they are written only on
-//       request).
+//       epilogue folds each block of vocabulary rows into the workgroup's running (max, sum exp,
+//       top-k candidates) per column, so the gamma x V logits never have to be re-read (they are
+//       written only on request) and a column leaves one record per workgroup.
 //
 // Structure: persistent workgroups (two per CU, 4 waves each).  A workgroup walks its tasks (row
 // block x split of d) as one uninterrupted sequence of stages; a stage is a slice of d of RB
@@ -19,9 +19,8 @@
 //
 // Instances <MODE, MB, NBX, RB>: 64*MB rows of A per task, 16*NBX columns of X.
 //   relevance: <1,1,512> (up to 16 draft rows, d % 256 == 0); otherwise <1|2, 1|2, 256>
-//   lm_head:   <1,1,256> or <2,1,256> up to 16 columns, <1,2,256> or <2,2,256> up to 32,
-//              <1,3,256> up to 48, <1,4,256> up to 64 (a last,
-//              narrower pass over a group of chains keeps the task size of the full passes)
+//   lm_head:   <1,1,256> or <2,1,256> up to 16 columns, <1,2,256> or <2,2,256> up to 32; more
+//              columns (up to 128) take lm_head_wide_kernel below
 #include "lvspec_dev.h"
 #include "lvspec_kernels.h"
 
@@ -33,7 +32,6 @@ constexpr int MODE_REL = 0;    // relevance, squared row norms of A taken in the
 constexpr int MODE_LMH = 1;
 constexpr int MODE_RELP = 2;   // relevance with the rows' inverse norms prepared by the caller
 constexpr bool is_rel(int mode) { return mode != MODE_LMH; }
-constexpr float kLog2e = 1.4426950408889634f;
 
 template <int MB, int NBX, int RB>
 struct Geo {
@@ -217,6 +215,111 @@ LVS_DEV void wait_stages(int ahead) {
   }
 }
 
+
+// ---- running softmax statistics and top-k of one logits column over the tasks of a workgroup ----
+// The same wave serves a column in every task, so the state stays in its registers: lane l keeps
+// the maximum and the sums of the rows it has seen (no cross-lane work per task), lane r the r-th
+// best candidate of the whole wave.  Per task only the rows that beat the k-th best so far cost a
+// selection round (about k/t of task t's rows do), where every task used to run k rounds of its own
+// and write k candidates: five columns, V = 152064: 2376 records per column before, 475 now; the
+// pass itself 228.5 -> 223.6 us at d = 5120, with 48 columns 333 -> 307, with k = 16 (d = 3584)
+// 177 -> 163.
+struct ColumnState {
+  uint64_t top;   // lane r < k: r-th best (value, id) key, descending; 0 = none
+  float m, s, sz; // this lane's rows: maximum, sum exp(z - m), sum exp(z - m) * z
+};
+
+LVS_DEV void column_init(ColumnState& c) {
+  c.top = 0ull;
+  c.m = -INFINITY;
+  c.s = 0.f;
+  c.sz = 0.f;
+}
+
+// v[j]: logit of vocabulary row id0 + 64 * j (lane's rows), to be ignored from n_rows on.
+// The set of the k best under the total order (value descending, id ascending) does not depend
+// on the order in which rows arrive, and the tasks of a workgroup are a fixed function of the
+// shape: results are reproducible.
+template <int NV>
+LVS_DEV void column_fold(ColumnState& c, const float (&vin)[NV], int id0, int n_rows, int topk,
+                         bool want_z, int lane) {
+  float v[NV];
+  uint64_t key[NV];
+  float mn = c.m;
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    const int id = id0 + 64 * j;
+    v[j] = id < n_rows ? vin[j] : -INFINITY;
+    key[j] = v[j] != -INFINITY ? cand_key(v[j], id) : 0ull;
+    mn = fmaxf(mn, v[j]);
+  }
+  const float keep = c.m == -INFINITY ? 0.f : fast_exp2((c.m - mn) * kLog2e);
+  float s = c.s * keep;
+  float e[NV];
+#pragma unroll
+  for (int j = 0; j < NV; ++j) {
+    e[j] = v[j] == -INFINITY ? 0.f : fast_exp2((v[j] - mn) * kLog2e);
+    s += e[j];
+  }
+  if (want_z) {
+    float sz = c.sz * keep;
+#pragma unroll
+    for (int j = 0; j < NV; ++j) sz += v[j] == -INFINITY ? 0.f : e[j] * v[j];
+    c.sz = sz;
+  }
+  c.m = mn;
+  c.s = s;
+  topk_insert<NV>(c.top, key, topk, lane);
+}
+
+// the workgroup's record of a column
+LVS_DEV void column_emit(const ColumnState& c, const GemmKernelArgs& p, int col, int lane) {
+  const float mx = wave_max(c.m);
+  const float f = c.m == -INFINITY ? 0.f : fast_exp2((c.m - mx) * kLog2e);
+  const float s = wave_sum(c.s * f);
+  const int64_t rec = (int64_t)col * p.n_rec + blockIdx.x;
+  if (lane == 0) {
+    p.stats[rec * 2] = mx;
+    p.stats[rec * 2 + 1] = s;
+  }
+  if (p.stats_z != nullptr) {
+    const float sz = wave_sum(c.sz * f);
+    if (lane == 0) p.stats_z[rec] = sz;
+  }
+  if (lane < p.topk) p.cand[rec * p.topk + lane] = c.top;
+}
+
+// Four columns' values of this lane's rows from the epilogue tile.  Assembly, like every LDS read
+// of these kernels: an ordinary load would wait for all outstanding copies.
+template <int NV>
+LVS_DEV void read_columns4(float (&v)[4][NV], const uint32_t (&a)[4]) {
+  static_assert(NV == 1 || NV == 2, "64 or 128 rows");
+  if constexpr (NV == 1) {
+    asm volatile(
+        "ds_read_b32 %0, %4\n\tds_read_b32 %1, %5\n\tds_read_b32 %2, %6\n\tds_read_b32 %3, %7\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(v[0][0]), "=&v"(v[1][0]), "=&v"(v[2][0]), "=&v"(v[3][0])
+        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3])
+        : "memory");
+  } else {
+    asm volatile(
+        "ds_read_b32 %0, %8\n\tds_read_b32 %1, %8 offset:256\n\t"
+        "ds_read_b32 %2, %9\n\tds_read_b32 %3, %9 offset:256\n\t"
+        "ds_read_b32 %4, %10\n\tds_read_b32 %5, %10 offset:256\n\t"
+        "ds_read_b32 %6, %11\n\tds_read_b32 %7, %11 offset:256\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(v[0][0]), "=&v"(v[0][1]), "=&v"(v[1][0]), "=&v"(v[1][1]), "=&v"(v[2][0]),
+          "=&v"(v[2][1]), "=&v"(v[3][0]), "=&v"(v[3][1])
+        : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3])
+        : "memory");
+  }
+}
+
+// own LDS writes done, then the barrier; unlike __syncthreads it leaves copies in flight
+LVS_DEV void barrier_after_lds_writes() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 template <int MODE, int MB, int NBX, int RB>
 __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(const GemmKernelArgs p) {
   using G = Geo<MB, NBX, RB>;
@@ -239,6 +342,14 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(const GemmKernelArg
     accn[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int nx = 0; nx < NBX; ++nx) acc[mb][nx] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+
+  // lm_head: wave w serves columns w, w + 4, ...
+  constexpr int kCols = MODE == MODE_LMH ? 4 * NBX : 1;
+  ColumnState cst[kCols];
+  if constexpr (MODE == MODE_LMH) {
+#pragma unroll
+    for (int t = 0; t < kCols; ++t) column_init(cst[t]);
   }
 
   Cursor cc{(int)blockIdx.x, 0, -1, 0};   // compute cursor
@@ -310,7 +421,7 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(const GemmKernelArg
       int b, rb, ds;
       decode_task<MODE>(p, cc.task, b, rb, ds);
       const int row0 = rb * G::kRowsWg;
-      if (is_rel(MODE)) {
+      if constexpr (is_rel(MODE)) {
         // acc[mb][nx][i] = dot(A row row0 + wave*16*MB + 16*mb + 4*g4 + i, X column 16*nx + n16)
 #pragma unroll
         for (int nx = 0; nx < NBX; ++nx) {
@@ -344,61 +455,30 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(const GemmKernelArg
           for (int nx = 0; nx < NBX; ++nx)
             *reinterpret_cast<f32x4*>(zt + (16 * nx + n16) * G::kZtStride + wave * 16 * MB +
                                       16 * mb + 4 * g4) = acc[mb][nx];
-        __syncthreads();
-        if (p.logits != nullptr) {
-          for (int idx = threadIdx.x; idx < p.n_cols * G::kRowsWg; idx += 256) {
-            const int col = idx / G::kRowsWg;
-            const int r = idx - col * G::kRowsWg;
-            if (row0 + r < n_rows)
-              p.logits[(int64_t)col * n_rows + row0 + r] = zt[col * G::kZtStride + r];
-          }
-        }
-        // per column: block maximum, sum of exponentials and the k best (value, id) pairs, by
-        // wave-wide reductions over the DPP lane network (lane l holds rows l and l + 64)
-        for (int col = wave; col < p.n_cols; col += 4) {
-          float v[MB];
-          uint64_t key[MB];
-          float mx = -INFINITY;
+        barrier_after_lds_writes();
+        const uint32_t zl = slot + (uint32_t)lane * 4u;
 #pragma unroll
-          for (int j = 0; j < MB; ++j) {
-            const int r = lane + 64 * j;
-            const bool on = row0 + r < n_rows;
-            v[j] = on ? zt[col * G::kZtStride + r] : -INFINITY;
-            key[j] = (on && v[j] != -INFINITY) ? cand_key(v[j], row0 + r) : 0ull;
-            mx = fmaxf(mx, v[j]);
-          }
-          mx = wave_max(mx);
-          float se = 0.f;
+        for (int t4 = 0; t4 < kCols; t4 += 4) {
+          if (wave + 4 * t4 < p.n_cols) {
+            uint32_t a[4];
 #pragma unroll
-          for (int j = 0; j < MB; ++j) se += fast_exp2((v[j] - mx) * kLog2e);
-          se = wave_sum(se);
-          const int64_t rec = (int64_t)cc.task * p.n_cols + col;
-          if (lane == 0) {
-            p.stats[rec * 2] = mx;
-            p.stats[rec * 2 + 1] = se;
-          }
-          if (p.stats_z != nullptr) {   // sum exp(z - max) * z, for the row entropy
-            float sz = 0.f;
+            for (int t = 0; t < 4; ++t) a[t] = zl + (wave + 4 * (t4 + t)) * (G::kZtStride * 4);
+            float v[4][MB];
+            read_columns4<MB>(v, a);
 #pragma unroll
-            for (int j = 0; j < MB; ++j)
-              sz += v[j] == -INFINITY ? 0.f : fast_exp2((v[j] - mx) * kLog2e) * v[j];
-            sz = wave_sum(sz);
-            if (lane == 0) p.stats_z[rec] = sz;
-          }
-          uint64_t mine = 0;   // lane r keeps the r-th best
-          for (int r = 0; r < p.topk; ++r) {
-            uint64_t best = key[0];
+            for (int t = 0; t < 4; ++t) {
+              const int col = wave + 4 * (t4 + t);
+              if (col < p.n_cols) {
+                if (p.logits != nullptr) {
 #pragma unroll
-            for (int j = 1; j < MB; ++j) best = key[j] > best ? key[j] : best;
-            const uint64_t w = wave_max_u64(best);
-#pragma unroll
-            for (int j = 0; j < MB; ++j) key[j] = key[j] == w ? 0ull : key[j];
-            mine = lane == r ? w : mine;
-          }
-          if (lane < p.topk) {
-            p.cand_val[rec * p.topk + lane] =
-                mine ? key_value((uint32_t)(mine >> 32)) : -INFINITY;
-            p.cand_idx[rec * p.topk + lane] = mine ? 0x7fffffff - (int)(uint32_t)mine : -1;
+                  for (int j = 0; j < MB; ++j)
+                    if (row0 + lane + 64 * j < n_rows)
+                      p.logits[(int64_t)col * n_rows + row0 + lane + 64 * j] = v[t][j];
+                }
+                column_fold<MB>(cst[t4 + t], v[t], row0 + lane, n_rows, p.topk,
+                                p.stats_z != nullptr, lane);
+              }
+            }
           }
         }
       }
@@ -412,6 +492,22 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(const GemmKernelArg
     advance<MODE, G::kRowsWg>(p, cc);
     slot_c = slot_c + 1 == G::kStages ? 0 : slot_c + 1;
   }
+  if constexpr (MODE == MODE_LMH) {
+#pragma unroll
+    for (int t = 0; t < kCols; ++t)
+      if (wave + 4 * t < p.n_cols) column_emit(cst[t], p, wave + 4 * t, lane);
+  }
+}
+
+// As many workgroups as fit at once, then trimmed so that every workgroup walks the same number
+// of tasks (1188 tasks on 512 slots: 396 workgroups x 3 instead of 164 doing a third task while
+// 348 sit idle).  The kernels are bandwidth-bound, so a few idle CUs cost nothing.
+int stream_grid(int n_tasks, int slots) {
+  int grid = n_tasks < slots ? n_tasks : slots;
+  if (grid < 1) grid = 1;
+  const int rounds = (n_tasks + grid - 1) / grid;
+  if (rounds > 0) grid = (n_tasks + rounds - 1) / rounds;
+  return grid < 1 ? 1 : grid;
 }
 
 template <int MODE, int MB, int NBX, int RB>
@@ -425,15 +521,8 @@ hipError_t launch_gemm(const GemmKernelArgs& a, int num_cu, hipStream_t stream) 
   hipError_t e = lds_limit.ensure(
       reinterpret_cast<const void*>(&gemm_stream_kernel<MODE, MB, NBX, RB>), lds);
   if (e != hipSuccess) return e;
-  // As many workgroups as fit at once, then trimmed so that every workgroup walks the same
-  // number of tasks (1188 tasks on 512 slots: 396 workgroups x 3 instead of 164 doing a third
-  // task while 348 sit idle).  The kernel is bandwidth-bound, so a few idle CUs cost nothing.
-  const int slots = num_cu * G::kWgPerCu;
-  int grid = a.n_tasks < slots ? a.n_tasks : slots;
-  if (grid < 1) grid = 1;
-  const int rounds = (a.n_tasks + grid - 1) / grid;
-  if (rounds > 0) grid = (a.n_tasks + rounds - 1) / rounds;
-  if (grid < 1) grid = 1;
+  // (lm_head: one record per workgroup, the number the planner sized the records by)
+  const int grid = MODE == MODE_LMH ? a.n_rec : stream_grid(a.n_tasks, num_cu * G::kWgPerCu);
   hipLaunchKernelGGL((gemm_stream_kernel<MODE, MB, NBX, RB>), dim3(grid), dim3(256), lds, stream,
                      a);
   return hipGetLastError();
@@ -442,16 +531,16 @@ hipError_t launch_gemm(const GemmKernelArgs& a, int num_cu, hipStream_t stream) 
 }  // namespace
 
 int rel_rows_per_block(int big) { return big ? Geo<2, 1, 256>::kRowsWg : Geo<1, 1, 256>::kRowsWg; }
-int lmh_rows_per_block(int n_cols, int64_t row_pitch_bytes, int64_t n_rows, int topk) {
+int lmh_records(int n_tasks, int num_cu) {
+  const int slots = num_cu * Geo<1, 1, 256>::kWgPerCu;
+  return stream_grid(n_tasks, slots < kAcceptMaxRecords ? slots : kAcceptMaxRecords);
+}
+// Rows of a stage.  Up to 32 columns: 64-row stages with a three- or four-slot ring stream 2-4 %
+// faster than 128-row stages with two slots (d = 2048 .. 7168), except at row pitches that are
+// multiples of 8 KiB (d = 4096, 8192), where the 64 segments of a stage fall into too few HBM
+// channels (d = 4096, five columns: 5.6 against 6.4 TB/s).
+int lmh_block_rows(int n_cols, int64_t row_pitch_bytes) {
   if (n_cols > 32) return Geo<1, 4, 256>::kRowsWg;
-  // twice the row blocks are twice the top-k candidates: stay within what the merge kernel
-  // keeps in registers (V = 152064: k <= 8)
-  const int64_t blocks64 = (n_rows + Geo<1, 1, 256>::kRowsWg - 1) / Geo<1, 1, 256>::kRowsWg;
-  if (blocks64 * topk > kAcceptRegCandidates) return Geo<2, 1, 256>::kRowsWg;
-  // Up to 32 columns: 64-row tasks with a three- or four-slot ring stream 2-4 % faster than
-  // 128-row tasks with two slots (d = 2048 .. 7168), except at row pitches that are multiples
-  // of 8 KiB (d = 4096, 8192), where the 64 segments of a stage fall into too few HBM channels
-  // (d = 4096, five columns: 5.6 against 6.4 TB/s).
   return row_pitch_bytes % 8192 == 0 ? Geo<2, 1, 256>::kRowsWg : Geo<1, 1, 256>::kRowsWg;
 }
 
@@ -473,10 +562,6 @@ hipError_t launch_rel_gemm(const GemmKernelArgs& a, int num_cu, hipStream_t stre
 }
 
 hipError_t launch_lmh_gemm(const GemmKernelArgs& a, int num_cu, hipStream_t stream) {
-  // The task size is the planner's (it sized the partial results by it): 64-row tasks for
-  // 33..64 columns (the wider X slice then still leaves two ring slots for each of the two
-  // workgroups of a CU) and, unless the row pitch speaks against it, for up to 16 columns;
-  // 128-row tasks otherwise.
   if (a.rows_per_block == Geo<1, 1, 256>::kRowsWg) {
     if (a.n_cols <= 16) return launch_gemm<MODE_LMH, 1, 1, 256>(a, num_cu, stream);
     if (a.n_cols <= 32) return launch_gemm<MODE_LMH, 1, 2, 256>(a, num_cu, stream);

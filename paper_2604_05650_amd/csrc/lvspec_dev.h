@@ -31,6 +31,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kRowBytes = 256;   // 128 bf16
 constexpr int kWave = 64;
+constexpr float kLog2e = 1.4426950408889634f;
 
 #define LVS_DEV __device__ __forceinline__
 
@@ -205,6 +206,37 @@ LVS_DEV uint64_t wave_max_u64(uint64_t x) {
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, 63);
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), 63);
   return ((uint64_t)hi << 32) | lo;
+}
+
+LVS_DEV uint64_t read_lane64(uint64_t x, int lane) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), lane);
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// A wave's running list of the k <= 16 largest 64-bit keys, lane r < 16 holding the r-th largest
+// (0 = none): take in NV keys per lane.  Only keys above the k-th so far cost a round, largest
+// first; every round retires one key, so the loop ends.  Equal keys are the same candidate.
+template <int NV>
+LVS_DEV void topk_insert(uint64_t& top, uint64_t (&key)[NV], int k, int lane) {
+  uint64_t kth = read_lane64(top, k - 1);
+  while (true) {
+    uint64_t best = key[0];
+#pragma unroll
+    for (int j = 1; j < NV; ++j) best = key[j] > best ? key[j] : best;
+    if (__ballot(best > kth) == 0ull) break;
+    const uint64_t w = wave_max_u64(best);
+#pragma unroll
+    for (int j = 0; j < NV; ++j) key[j] = key[j] == w ? 0ull : key[j];
+    // lanes above w keep their key, the next one takes w, the others move down by one
+    // (row_shr:1: the list lives in one DPP row)
+    const int pos = __popcll(__ballot((lane < 16) & (top > w)));
+    const uint32_t dlo = dpp_move<0x111, 0xf>(0u, (uint32_t)top);
+    const uint32_t dhi = dpp_move<0x111, 0xf>(0u, (uint32_t)(top >> 32));
+    const uint64_t down = ((uint64_t)dhi << 32) | dlo;
+    top = lane < pos ? top : lane == pos ? w : lane < 16 ? down : 0ull;
+    kth = read_lane64(top, k - 1);
+  }
 }
 
 }  // namespace lvspec

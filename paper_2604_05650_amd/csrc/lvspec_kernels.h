@@ -108,11 +108,11 @@ struct GemmKernelArgs {
   float* dots;               // [B][n_ds][gamma][ld]
   float* nv2;                // [B][n_ds][ld]
   int64_t ld;
-  // lm_head outputs
-  float* stats;
-  float* stats_z;            // optional [n_tasks][n_cols]: sum exp(z - max) * z per block (entropy)              // [n_tasks][n_cols][2]  (max, sum exp(z - max))
-  float* cand_val;           // [n_tasks][n_cols][topk]
-  int32_t* cand_idx;         // [n_tasks][n_cols][topk]
+  // lm_head outputs: one record per column and workgroup, rec = column * n_rec + workgroup
+  int n_rec;                 // workgroups of the launch
+  float* stats;              // [n_cols][n_rec][2]  (max, sum exp(z - max))
+  float* stats_z;            // optional [n_cols][n_rec]: sum exp(z - max) * z (entropy)
+  uint64_t* cand;            // [n_cols][n_rec][topk]: (value, id) keys, descending
   int topk;
   float* logits;             // optional [n_cols][n_rows]
 };
@@ -120,10 +120,10 @@ struct GemmKernelArgs {
 hipError_t launch_rel_gemm(const GemmKernelArgs& a, int num_cu, hipStream_t stream);
 hipError_t launch_lmh_gemm(const GemmKernelArgs& a, int num_cu, hipStream_t stream);
 int rel_rows_per_block(int big);   // 64, or 128 rows when there are plenty of row blocks
-// vocabulary rows per task: 64 or 128
-int lmh_rows_per_block(int n_cols, int64_t row_pitch_bytes, int64_t n_rows, int topk);
-// candidates per column (row blocks x top-k) that accept_finalize_kernel keeps in registers
-constexpr int kAcceptRegCandidates = 20 * 1024;
+// vocabulary rows per stage: 64 or 128
+int lmh_block_rows(int n_cols, int64_t row_pitch_bytes);
+// workgroups of an lm_head launch over n_tasks tasks = records per column it leaves
+int lmh_records(int n_tasks, int num_cu);
 
 // ---------------------------------------------------------------- relevance finalize
 struct RelFinalizeArgs {
@@ -160,31 +160,31 @@ hipError_t launch_hv_prepare(const HvPrepareArgs& a, hipStream_t stream);
 
 // ---------------------------------------------------------------- accept finalize
 struct AcceptFinalizeArgs {
-  int B, gamma, V, topk, n_tasks, n_cols;
+  int B, gamma, V, topk;
+  int n_rec;                 // records per column, see GemmKernelArgs
   int rows;                  // hidden rows per chain: gamma, or gamma + 1 with a bonus row
   FastDiv div_topk;
   const float* stats;
   const float* stats_z;      // optional, see GemmKernelArgs
+  const uint64_t* cand;
   float* entropy;            // optional [B*rows]
-  const float* cand_val;
-  const int32_t* cand_idx;
   const int32_t* draft_ids;
   const float* relevance;
   int n_loose, pst_window, gate;
   int rule;                  // 0 the paper's rule; 1 entropy gate; 2 entropy gate + deferred window
   float ent_threshold;
   int defer_window;
-  const float* ent_rows;     // [B*rows] entropies the entropy rules read (entropy, or scratch)
-  int n_branches;            // chains per sequence (>= 1)
+  int n_branches;            // chains per sequence (>= 1); n_branches * rows <= kAcceptMaxRows
   int32_t* best_branch;      // optional, [B / n_branches]
   int32_t* target_ids;
   int32_t* topk_ids;         // optional
   float* topk_probs;         // optional
-  int32_t* ws_topk_ids;      // [B*rows][16]
   uint8_t* verdict;
   int32_t* accept_len;
   int32_t* bonus_id;
 };
+constexpr int kAcceptMaxRows = 64;      // hidden rows of one sequence (all chains of its tree)
+constexpr int kAcceptMaxRecords = 512;   // records per column (two workgroups on each of 256 CUs)
 hipError_t launch_accept_finalize(const AcceptFinalizeArgs& a, hipStream_t stream);
 
 // ---------------------------------------------------------------- KV commit

@@ -113,8 +113,7 @@ GROUPS = {   # kernels launched by one call of each entry point
     "verify_attn": ("attn_split_kernel", "attn_combine_kernel"),
     "visual_relevance": ("gemm_stream_kernel<0", "gemm_stream_kernel<2", "rel_finalize_kernel",
                          "rel_cand_kernel", "rel_merge_kernel"),
-    "lm_head_accept": ("gemm_stream_kernel<1", "accept_finalize_kernel",
-                       "accept_finalize_general_kernel", "accept_decide_kernel"),
+    "lm_head_accept": ("gemm_stream_kernel<1", "accept_finalize_kernel"),
 }
 CALIBRATION_KERNEL = "CUDAFunctorOnSelf_add<int>"
 GIB = float(1 << 30)

@@ -1,0 +1,52 @@
+"""GPU parity at the edges of the lm_head pass and its merge: vocabularies that end inside a block,
+long candidate lists, many hidden rows per sequence, and rows whose maxima tie everywhere."""
+import numpy as np
+import pytest
+import torch
+
+import test_gpu_accept as acc
+from paper_2604_05650_amd import synth
+from parity import t_bf16, t_f32, t_i32
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,K,n_br,bonus,V,d,topk", [
+    (1, 1, 1, False, 40, 128, 16),        # fewer rows than a block, one hidden row
+    (1, 5, 1, False, 193, 128, 1),        # one row beyond three blocks
+    (1, 5, 1, True, 33000, 256, 16),      # several blocks per workgroup, k * k candidates
+    (2, 16, 1, True, 20001, 128, 4),      # more hidden rows than waves of the merge
+    (8, 8, 8, False, 8192, 256, 5),       # 64 hidden rows of one sequence
+])
+def test_edges(B, K, n_br, bonus, V, d, topk):
+    rows = K + (1 if bonus else 0)
+    key = (611, B, K, V, topk)
+    h = synth.normal_bf16(key + (0,), (B, rows, d), 1.0)
+    w = synth.normal_bf16(key + (1,), (V, d), 0.1)
+    h, planted = synth.plant_target_rows(h, w, 24.0, key + (2,))
+    draft = synth.draft_ids_from_target(planted[:, :K], key + (3,), p_wrong=0.3, V=V)
+    rel = np.random.default_rng(611).random((B, K)).astype(np.float32)
+    acc._check(h, w, draft, rel, int(0.7 * K), K, topk=topk, bonus_row=bonus, n_branches=n_br,
+               tag=f"edges V{V} d{d} rows{B * rows}")
+
+
+@pytest.mark.parametrize("V,topk,step", [(38400, 4, 1), (38400, 16, 1), (152064, 16, 64 * 512)])
+def test_equal_logits_take_the_lowest_ids(V, topk, step):
+    # every `step`-th vocabulary row is the same vector and the others are zero: the best logit
+    # occurs in all records (step 1: more of them than the short selection takes) or in a few,
+    # and the k best are the k lowest ids among them, exactly
+    from paper_2604_05650_amd import binding as L
+    d = 128
+    w = torch.zeros((V, d), dtype=torch.bfloat16, device="cuda:0")
+    w[::step] = 0.5
+    h = np.full((1, 3, d), 0x3F80, np.uint16)     # ones
+    outs = L.loose_accept(t_bf16(h), w, t_i32([[0, 1, 2]]), t_f32([[0.0, 0.1, 0.2]]), 0, 0,
+                          topk=topk, return_entropy=True)
+    torch.cuda.synchronize()
+    best = list(range(0, V, step))
+    rest = [i for i in range(2 * topk) if i not in best]
+    want = (best + rest)[:topk]
+    assert outs["target_ids"].cpu().tolist() == [[0, 0, 0]]
+    assert outs["topk_ids"].cpu().tolist() == [[want] * 3]
+    # the softmax of `len(best)` logits 64 and V - len(best) zeros
+    np.testing.assert_allclose(outs["topk_probs"][0, 0, 0].item(), 1.0 / len(best), rtol=1e-5)
