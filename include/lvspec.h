@@ -225,9 +225,9 @@ enum { LVSPEC_RULE_VISUAL = 0, LVSPEC_RULE_ENTROPY_GATE = 1, LVSPEC_RULE_ENTROPY
 
 typedef struct {
   int32_t B, gamma, d, V, topk;     /* B chains of gamma <= 16 tokens; d % 128 == 0;
-                                       1 <= topk <= 16.  One pass over lm_head serves up to 64
-                                       hidden rows; with more rows the chains are taken in
-                                       groups of whole sequences, one pass each */
+                                       1 <= topk <= 16.  Chains are taken in groups of whole
+                                       sequences with up to 64 hidden rows; one pass over
+                                       lm_head serves two groups */
   const void* h_d;                  /* DEVICE bf16 [B, gamma + bonus_row, d] final hidden rows */
   int64_t hd_sb, hd_sg;
   const void* lm_head;              /* DEVICE bf16 [V, d] row-major, no bias */
@@ -313,10 +313,10 @@ typedef struct {
   int32_t rel_stage_bytes;       /* bytes of a video row per pipeline stage: 256 or 512 */
   int32_t rel_slices;            /* slices of the two-kernel Top-N; 0 = single-kernel selection */
   int32_t rel_slice_rows;        /* video rows per slice */
-  int32_t acc_rows_per_task;     /* vocabulary rows per lm_head task: 64 or 128 (one or two
-                                    blocks of 64, or one of 128) */
-  int32_t acc_chains_per_pass;   /* chains served by one pass over lm_head */
-  int32_t acc_passes;            /* passes over lm_head */
+  int32_t acc_rows_per_task;     /* vocabulary rows per lm_head task: 64 or 128 (a stage of the
+                                    pass holds half of one, one, or two) */
+  int32_t acc_chains_per_pass;   /* chains of a group (up to 64 hidden rows) */
+  int32_t acc_passes;            /* groups; two of them share one pass over lm_head */
 } lvspec_plan_info;
 
 int lvspec_describe_plan(const lvspec_attn_args* attn, const lvspec_rel_args* rel,

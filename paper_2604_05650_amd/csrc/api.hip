@@ -192,9 +192,10 @@ int plan_rel(const lvspec_rel_args* a, RelPlan* pl) {
 // ------------------------------------------------------------------------------ accept
 struct AccPlan {
   int n_tasks, n_cols;     // n_cols: columns of one (full) pass
+  int per_pass;            // chains of one pass: one group, or two side by side
   int rows_per_block;      // vocabulary rows per task: one or two blocks
   int block_rows;          // vocabulary rows per pipeline stage
-  int group;               // chains per pass (a multiple of the branches per sequence)
+  int group;               // chains of a group (a multiple of the branches per sequence)
   int n_rec;               // records per column (workgroups of the lm_head launch)
   size_t off_cand, off_sz, ws_bytes;
 };
@@ -216,26 +217,29 @@ int plan_acc(const lvspec_accept_args* a, AccPlan* pl) {
       (!(a->entropy_threshold >= 0.f) || a->defer_window < 0 || a->defer_window > LVSPEC_MAX_GAMMA))
     return LVSPEC_EINVAL;
   if (a->d % 128 != 0) return LVSPEC_EUNSUPPORTED;
-  // one pass of the lm_head stream serves at most kMaxCols hidden rows; more chains take
-  // several passes (whole sequences per pass: the branches of a tree stay together)
+  // Chains are taken in groups of whole sequences (the branches of a tree stay together) with at
+  // most kMaxCols hidden rows, and two groups share one pass of the lm_head stream.
   constexpr int kMaxCols = 64;
   const int nbr = a->n_branches > 1 ? a->n_branches : 1;
   const int rpc = a->gamma + a->bonus_row;   // hidden rows per chain
   if (nbr * rpc > kMaxCols || a->B > 4096) return LVSPEC_EUNSUPPORTED;
-  // Fewest passes first; among equal pass counts the smallest group whose columns fit the
+  // Fewest groups first; among equal counts the smallest group whose columns fit the
   // narrower (faster) kernel variants.
   const int gmax = (kMaxCols / rpc) / nbr * nbr;
-  const int passes = (a->B + gmax - 1) / gmax;
-  pl->group = ((a->B + passes - 1) / passes + nbr - 1) / nbr * nbr;
+  const int groups = (a->B + gmax - 1) / gmax;
+  pl->group = ((a->B + groups - 1) / groups + nbr - 1) / nbr * nbr;
   if (pl->group > a->B) pl->group = a->B;
-  pl->n_cols = pl->group * rpc;
+  pl->per_pass = pl->group < a->B ? 2 * pl->group : pl->group;
+  pl->n_cols = (pl->per_pass < a->B ? pl->per_pass : a->B) * rpc;
   // Tasks are counted in blocks of 64 rows, except that long candidate lists (k > 8) and row
   // pitches that want 128-row stages pair them up.  A pair of 64-row blocks is still streamed
   // block by block: at k = 16 (d = 3584, V = 152064) 163 us against 171 us in 128-row stages.
-  pl->block_rows = lvspec::lmh_block_rows(pl->n_cols, (a->w_sv > 0 ? a->w_sv : a->d) * 2);
-  pl->rows_per_block = a->topk > 8 && pl->n_cols <= 32 ? 128 : pl->block_rows;
+  // More than 32 columns: the wide kernel's blocks hold one or two tasks.
+  pl->block_rows = lvspec::lmh_block_rows(pl->n_cols, (a->w_sv > 0 ? a->w_sv : a->d) * 2, a->V,
+                                          num_compute_units());
+  pl->rows_per_block = pl->n_cols > 32 ? 64 : a->topk > 8 ? 128 : pl->block_rows;
   pl->n_tasks = (a->V + pl->block_rows - 1) / pl->block_rows;
-  pl->n_rec = lvspec::lmh_records(pl->n_tasks, num_compute_units());
+  pl->n_rec = lvspec::lmh_records(pl->n_cols, pl->n_tasks, num_compute_units());
   const size_t rec = (size_t)pl->n_rec * pl->n_cols;
   pl->off_cand = round_up(rec * 2 * sizeof(float), 256);
   pl->off_sz = pl->off_cand + round_up(rec * a->topk * sizeof(uint64_t), 256);
@@ -477,9 +481,18 @@ int lvspec_loose_accept(const lvspec_accept_args* a, void* stream) {
   uint8_t* ws = static_cast<uint8_t*>(a->workspace);
   const int nbr = a->n_branches > 1 ? a->n_branches : 1;
   const int rpc = a->gamma + a->bonus_row;                         // hidden rows per chain
-  for (int b0 = 0; b0 < a->B; b0 += pl.group) {
-    const int nb = a->B - b0 < pl.group ? a->B - b0 : pl.group;   // chains of this pass
+  for (int b0 = 0; b0 < a->B; b0 += pl.per_pass) {
+    const int nb = a->B - b0 < pl.per_pass ? a->B - b0 : pl.per_pass;   // chains of this pass
     const int n_cols = nb * rpc;
+    // a last, narrower pass has its own stage size and grid, within the records of a full pass
+    int block_rows = pl.block_rows, n_tasks = pl.n_tasks, n_rec = pl.n_rec;
+    if (n_cols < pl.n_cols) {
+      block_rows = lvspec::lmh_block_rows(n_cols, w_sv * 2, a->V, num_compute_units());
+      n_tasks = (a->V + block_rows - 1) / block_rows;
+      n_rec = lvspec::lmh_records(n_cols, n_tasks, num_compute_units());
+      const int room = (int)((int64_t)pl.n_rec * pl.n_cols / n_cols);
+      n_rec = n_rec < room ? n_rec : room;
+    }
     const int64_t c0 = (int64_t)b0 * rpc;                          // first hidden row of this pass
     const int64_t t0 = (int64_t)b0 * a->gamma;                     // first draft token of this pass
     lvspec::GemmKernelArgs g{};
@@ -493,16 +506,17 @@ int lvspec_loose_accept(const lvspec_accept_args* a, void* stream) {
     g.x_sg = a->hd_sg * 2;
     g.gamma = rpc;
     g.n_cols = n_cols;
+    g.half_cols = nb > pl.group ? pl.group * rpc : n_cols < 32 ? n_cols : 32;
     g.B = 1;
-    g.rows_per_block = pl.block_rows;
-    g.n_rb = pl.n_tasks;
+    g.rows_per_block = block_rows;
+    g.n_rb = n_tasks;
     g.n_ds = 1;
     g.kc = a->d / 128;
     g.row_bytes = 256;
-    g.n_tasks = pl.n_tasks;
+    g.n_tasks = n_tasks;
     g.stats = reinterpret_cast<float*>(ws);
     g.cand = reinterpret_cast<uint64_t*>(ws + pl.off_cand);
-    g.n_rec = pl.n_rec;
+    g.n_rec = n_rec;
     // the entropy rules read the row entropies, asked for or not
     const bool ent = a->entropy != nullptr || a->rule != LVSPEC_RULE_VISUAL;
     g.stats_z = ent ? reinterpret_cast<float*>(ws + pl.off_sz) : nullptr;
@@ -512,7 +526,7 @@ int lvspec_loose_accept(const lvspec_accept_args* a, void* stream) {
     if (e != hipSuccess) return hip_fail(e);
     lvspec::AcceptFinalizeArgs f{};
     f.B = nb; f.gamma = a->gamma; f.rows = rpc; f.V = a->V; f.topk = a->topk;
-    f.n_rec = pl.n_rec;
+    f.n_rec = n_rec;
     f.div_topk = lvspec::make_fast_div((uint32_t)a->topk);
     f.stats = g.stats; f.stats_z = g.stats_z; f.cand = g.cand;
     f.entropy = a->entropy ? a->entropy + c0 : nullptr;

@@ -499,6 +499,223 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(const GemmKernelArg
   }
 }
 
+// ---- lm_head for 33 to 128 hidden rows ------------------------------------------------------------
+// A server's batch brings more hidden rows than the kernel above can hold next to its ring: with 33
+// to 64 columns it keeps one stage in flight (two slots), and more columns meant another pass over
+// lm_head.  Here one workgroup of eight waves has the CU to itself: 64 * MB vocabulary rows by two
+// column halves of 16 * NB2, waves 4 (row groups of 16 * MB) x 2 (halves), so that a wave feeds
+// MB * NB2 independent accumulators from MB + NB2 operands per step and every X byte in LDS is
+// read by four waves instead of eight.  What bounds it besides HBM is the LDS: per 32 KiB of
+// lm_head (3050 cycles at 6.6 TB/s) 128 columns write 64 and read 192 KiB (2000 cycles).
+//
+// Rings: three slots of A (two stages in flight) and two of X (it comes from L2).  Copies complete
+// in issue order, so X(i+1) is issued ahead of A(i+2) and the wait for X(i) leaves A(i+1) out.
+// Two groups of chains with up to 64 columns each share a pass, one in each half; a single group of
+// more than 32 columns is split over the halves.
+template <int MB, int NB2>
+struct Wide {
+  static constexpr int kRowsWg = 64 * MB;
+  static constexpr int kASlot = kRowsWg * kRowBytes;
+  static constexpr int kXSlot = 2 * NB2 * 16 * kRowBytes;
+  static constexpr int kXOff = 3 * kASlot;
+  static constexpr int kLds = kXOff + 2 * kXSlot;
+  static constexpr int kAInstr = 2 * MB;        // copy instructions per wave and stage
+  static constexpr int kXInstr = NB2;
+  static constexpr int kZtStride = kRowsWg + 4; // floats per column of the epilogue tile
+  static_assert(kLds <= 160 * 1024, "LDS of one CU");
+  static_assert(32 * kZtStride * 4 <= kASlot, "epilogue tile of 32 columns in one A slot");
+};
+
+template <int MB, int NB2>
+__global__ __launch_bounds__(512, 2) void lm_head_wide_kernel(const GemmKernelArgs p) {
+  using W = Wide<MB, NB2>;
+  extern __shared__ __align__(16) uint8_t smem[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wr = wave & 3;       // row group
+  const int wc = wave >> 2;      // column half
+  const int n16 = lane & 15;
+  const int g4 = lane >> 4;
+  const uint32_t ring = lds_addr(smem);
+  const int n_chunks = p.kc;     // 256-byte chunks of a row
+
+  uint32_t oaddr[4];             // operand chunk 4*ks + g4 of row n16
+#pragma unroll
+  for (int i = 0; i < 4; ++i) oaddr[i] = n16 * kRowBytes + (((4 * i + g4) ^ n16) << 4);
+
+  // X sources: LDS row cl of half h = cl / (16 * NB2) is column h * half_cols + cl % (16 * NB2);
+  // rows without a column hold a copy of the last one and are never looked at
+  const int rsub = lane >> 4;
+  const uint8_t* xcol[W::kXInstr];
+#pragma unroll
+  for (int k = 0; k < W::kXInstr; ++k) {
+    const int cl = 4 * (8 * k + wave) + rsub;
+    const int h = cl / (16 * NB2);
+    int col = h * p.half_cols + (cl - h * 16 * NB2);
+    col = col < p.n_cols ? col : p.n_cols - 1;
+    const int xb = col / p.gamma;
+    const int xi = col - xb * p.gamma;
+    xcol[k] = p.x + (int64_t)xb * p.x_sb + (int64_t)xi * p.x_sg + ((n16 ^ (cl & 15)) << 4);
+  }
+  // stage kc of a task reads chunk (kc + task) mod n_chunks, as in gemm_stream_kernel
+  auto chunk_of = [&](int task, int kc) {
+    const int c = kc + task % n_chunks;
+    return c >= n_chunks ? c - n_chunks : c;
+  };
+  int ia_task = blockIdx.x, ia_kc = 0;     // next A stage to issue
+  int ix_task = blockIdx.x, ix_kc = 0;     // next X stage to issue
+  const uint8_t* arow[W::kAInstr];
+  auto setup_a = [&] {
+#pragma unroll
+    for (int j = 0; j < W::kAInstr; ++j) {
+      const int rl = wave * 8 * MB + 4 * j + rsub;
+      int row = ia_task * W::kRowsWg + rl;
+      row = row < p.n_rows ? row : p.n_rows - 1;
+      arow[j] = p.a + (int64_t)row * p.a_sr + ((n16 ^ (rl & 15)) << 4);
+    }
+  };
+  auto issue_a = [&](int slot) {
+    const int64_t off = (int64_t)chunk_of(ia_task, ia_kc) * kRowBytes;
+    const uint32_t dst = ring + slot * W::kASlot + wave * (8 * MB * kRowBytes);
+#pragma unroll
+    for (int j = 0; j < W::kAInstr; ++j) dma16(arow[j] + off, dst + j * 1024);
+    if (++ia_kc == n_chunks) {
+      ia_kc = 0;
+      ia_task += gridDim.x;
+      if (ia_task < p.n_tasks) setup_a();
+    }
+  };
+  auto issue_x = [&](int slot) {
+    const int64_t off = (int64_t)chunk_of(ix_task, ix_kc) * kRowBytes;
+    const uint32_t dst = ring + W::kXOff + slot * W::kXSlot;
+#pragma unroll
+    for (int k = 0; k < W::kXInstr; ++k)
+      dma16<kCopyDefault>(xcol[k] + off, dst + (8 * k + wave) * 1024);
+    if (++ix_kc == n_chunks) {
+      ix_kc = 0;
+      ix_task += gridDim.x;
+    }
+  };
+
+  f32x4 acc[MB][NB2];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+    for (int nb = 0; nb < NB2; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // the wave serves LDS columns wave, wave + 8, ... of each epilogue tile (32 columns: column
+  // block jj of either half)
+  ColumnState cst[4 * NB2];
+#pragma unroll
+  for (int t = 0; t < 4 * NB2; ++t) column_init(cst[t]);
+  auto column_at = [&](int jj, int t, bool& on) {
+    const int lc = wave + 8 * t;
+    const int h = lc >> 4;
+    const int within = jj * 16 + (lc & 15);
+    const int width = h == 0 ? (p.half_cols < p.n_cols ? p.half_cols : p.n_cols)
+                             : p.n_cols - p.half_cols;
+    on = within < width;
+    return h * p.half_cols + within;
+  };
+
+  int task = blockIdx.x, kc = 0;           // stage being consumed
+  setup_a();
+  wait_copies<0>();
+  issue_x(0);
+  issue_a(0);
+  bool a_ahead = ia_task < p.n_tasks;      // A of the next stage is on its way
+  if (a_ahead) issue_a(1);
+  int sa = 0, sx = 0;                      // slots of the stage being consumed
+  while (task < p.n_tasks) {
+    if (a_ahead) wait_copies<W::kAInstr>(); else wait_copies<0>();
+    __builtin_amdgcn_s_barrier();          // all shares landed; the slots of the last stage are free
+    if (ix_task < p.n_tasks) issue_x(sx ^ 1);
+    a_ahead = ia_task < p.n_tasks;
+    if (a_ahead) issue_a(sa == 0 ? 2 : sa - 1);
+    const uint32_t aslot = ring + sa * W::kASlot;
+    {
+      uint32_t a[4], x[4];
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        a[ks] = aslot + wr * (16 * MB * kRowBytes) + oaddr[ks];
+        x[ks] = ring + W::kXOff + sx * W::kXSlot + wc * (16 * NB2 * kRowBytes) + oaddr[ks];
+      }
+      u32x4 aop[MB][4];
+      if constexpr (MB == 2) {
+        u32x4 r[8];
+        lds_read8_after<63, 16 * kRowBytes>(r, a);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) aop[i >> 2][i & 3] = r[i];
+      } else {
+        lds_read4(aop[0], a);
+      }
+#pragma unroll
+      for (int nb = 0; nb < NB2; ++nb) {
+        u32x4 xop[4];
+        uint32_t xa[4];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) xa[ks] = x[ks] + nb * 16 * kRowBytes;
+        lds_read4(xop, xa);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+          for (int mb = 0; mb < MB; ++mb)
+            acc[mb][nb] = mfma16(aop[mb][ks], xop[ks], acc[mb][nb]);
+      }
+    }
+    if (kc == n_chunks - 1) {
+      // ---- end of a task: 32 columns at a time through the A slot just consumed
+      const int row0 = task * W::kRowsWg;
+      float* zt = reinterpret_cast<float*>(smem + sa * W::kASlot);
+#pragma unroll
+      for (int jj = 0; jj < NB2; ++jj) {
+        __builtin_amdgcn_s_barrier();      // operand reads, or reads of the previous tile, are done
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+          *reinterpret_cast<f32x4*>(zt + (wc * 16 + n16) * W::kZtStride + wr * 16 * MB + 16 * mb +
+                                    4 * g4) = acc[mb][jj];
+          acc[mb][jj] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        barrier_after_lds_writes();
+        uint32_t a[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          a[t] = aslot + (uint32_t)lane * 4u + (wave + 8 * t) * (W::kZtStride * 4);
+        float v[4][MB];
+        read_columns4<MB>(v, a);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          bool on;
+          const int col = column_at(jj, t, on);
+          if (on) {
+            if (p.logits != nullptr) {
+#pragma unroll
+              for (int j = 0; j < MB; ++j)
+                if (row0 + lane + 64 * j < p.n_rows)
+                  p.logits[(int64_t)col * p.n_rows + row0 + lane + 64 * j] = v[t][j];
+            }
+            column_fold<MB>(cst[4 * jj + t], v[t], row0 + lane, p.n_rows, p.topk,
+                            p.stats_z != nullptr, lane);
+          }
+        }
+      }
+    }
+    if (++kc == n_chunks) {
+      kc = 0;
+      task += gridDim.x;
+    }
+    sa = sa == 2 ? 0 : sa + 1;
+    sx ^= 1;
+  }
+#pragma unroll
+  for (int jj = 0; jj < NB2; ++jj)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      bool on;
+      const int col = column_at(jj, t, on);
+      if (on) column_emit(cst[4 * jj + t], p, col, lane);
+    }
+}
+
 // As many workgroups as fit at once, then trimmed so that every workgroup walks the same number
 // of tasks (1188 tasks on 512 slots: 396 workgroups x 3 instead of 164 doing a third task while
 // 348 sit idle).  The kernels are bandwidth-bound, so a few idle CUs cost nothing.
@@ -528,19 +745,40 @@ hipError_t launch_gemm(const GemmKernelArgs& a, int num_cu, hipStream_t stream) 
   return hipGetLastError();
 }
 
+template <int MB, int NB2>
+hipError_t launch_wide(const GemmKernelArgs& a, hipStream_t stream) {
+  using W = Wide<MB, NB2>;
+  static LdsLimitOnce lds_limit;
+  hipError_t e =
+      lds_limit.ensure(reinterpret_cast<const void*>(&lm_head_wide_kernel<MB, NB2>), W::kLds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((lm_head_wide_kernel<MB, NB2>), dim3(a.n_rec), dim3(512), W::kLds, stream, a);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 int rel_rows_per_block(int big) { return big ? Geo<2, 1, 256>::kRowsWg : Geo<1, 1, 256>::kRowsWg; }
-int lmh_records(int n_tasks, int num_cu) {
-  const int slots = num_cu * Geo<1, 1, 256>::kWgPerCu;
+constexpr int kWideCols = 33;   // from here on lm_head_wide_kernel
+
+int lmh_records(int n_cols, int n_tasks, int num_cu) {
+  const int slots = n_cols >= kWideCols ? num_cu : num_cu * Geo<1, 1, 256>::kWgPerCu;
   return stream_grid(n_tasks, slots < kAcceptMaxRecords ? slots : kAcceptMaxRecords);
 }
+
 // Rows of a stage.  Up to 32 columns: 64-row stages with a three- or four-slot ring stream 2-4 %
 // faster than 128-row stages with two slots (d = 2048 .. 7168), except at row pitches that are
 // multiples of 8 KiB (d = 4096, 8192), where the 64 segments of a stage fall into too few HBM
-// channels (d = 4096, five columns: 5.6 against 6.4 TB/s).
-int lmh_block_rows(int n_cols, int64_t row_pitch_bytes) {
-  if (n_cols > 32) return Geo<1, 4, 256>::kRowsWg;
+// channels (d = 4096, five columns: 5.6 against 6.4 TB/s).  More columns: 128 rows (half the X
+// traffic per lm_head byte), unless 64-row tasks leave clearly fewer rows to the busiest CU.
+int lmh_block_rows(int n_cols, int64_t row_pitch_bytes, int n_rows, int num_cu) {
+  if (n_cols >= kWideCols) {
+    auto per_cu = [&](int rows) {
+      const int64_t tasks = ((int64_t)n_rows + rows - 1) / rows;
+      return (tasks + num_cu - 1) / num_cu * rows;
+    };
+    return per_cu(64) * 5 < per_cu(128) * 4 ? 64 : 128;
+  }
   return row_pitch_bytes % 8192 == 0 ? Geo<2, 1, 256>::kRowsWg : Geo<1, 1, 256>::kRowsWg;
 }
 
@@ -562,16 +800,22 @@ hipError_t launch_rel_gemm(const GemmKernelArgs& a, int num_cu, hipStream_t stre
 }
 
 hipError_t launch_lmh_gemm(const GemmKernelArgs& a, int num_cu, hipStream_t stream) {
-  if (a.rows_per_block == Geo<1, 1, 256>::kRowsWg) {
-    if (a.n_cols <= 16) return launch_gemm<MODE_LMH, 1, 1, 256>(a, num_cu, stream);
-    if (a.n_cols <= 32) return launch_gemm<MODE_LMH, 1, 2, 256>(a, num_cu, stream);
-    if (a.n_cols <= 48) return launch_gemm<MODE_LMH, 1, 3, 256>(a, num_cu, stream);
-    if (a.n_cols <= 64) return launch_gemm<MODE_LMH, 1, 4, 256>(a, num_cu, stream);
-    return hipErrorInvalidValue;
+  const bool rows64 = a.rows_per_block == 64;
+  if (!rows64 && a.rows_per_block != 128) return hipErrorInvalidValue;
+  if (a.n_cols >= kWideCols) {
+    const int widest = a.half_cols > a.n_cols - a.half_cols ? a.half_cols : a.n_cols - a.half_cols;
+    if (a.half_cols > a.n_cols || widest > 64) return hipErrorInvalidValue;
+    if (widest <= 32)
+      return rows64 ? launch_wide<1, 2>(a, stream) : launch_wide<2, 2>(a, stream);
+    if (widest <= 48)
+      return rows64 ? launch_wide<1, 3>(a, stream) : launch_wide<2, 3>(a, stream);
+    return rows64 ? launch_wide<1, 4>(a, stream) : launch_wide<2, 4>(a, stream);
   }
-  if (a.n_cols <= 16) return launch_gemm<MODE_LMH, 2, 1, 256>(a, num_cu, stream);
-  if (a.n_cols <= 32) return launch_gemm<MODE_LMH, 2, 2, 256>(a, num_cu, stream);
-  return hipErrorInvalidValue;
+  if (a.n_cols <= 16)
+    return rows64 ? launch_gemm<MODE_LMH, 1, 1, 256>(a, num_cu, stream)
+                  : launch_gemm<MODE_LMH, 2, 1, 256>(a, num_cu, stream);
+  return rows64 ? launch_gemm<MODE_LMH, 1, 2, 256>(a, num_cu, stream)
+                : launch_gemm<MODE_LMH, 2, 2, 256>(a, num_cu, stream);
 }
 
 }  // namespace lvspec

@@ -98,6 +98,7 @@ struct GemmKernelArgs {
   int row_bytes;             // bytes of a row one pipeline stage covers: 256 or 512
   int gamma;                 // columns per batch
   int n_cols;                // relevance: gamma; lm_head: B * gamma
+  int half_cols;             // lm_head with more than 32 columns: columns of the first half
   int B;                     // batches of A (relevance) / 1
   int rows_per_block;        // rows of A per workgroup task (64 or 128)
   int n_rb;                  // row blocks per batch
@@ -121,9 +122,9 @@ hipError_t launch_rel_gemm(const GemmKernelArgs& a, int num_cu, hipStream_t stre
 hipError_t launch_lmh_gemm(const GemmKernelArgs& a, int num_cu, hipStream_t stream);
 int rel_rows_per_block(int big);   // 64, or 128 rows when there are plenty of row blocks
 // vocabulary rows per stage: 64 or 128
-int lmh_block_rows(int n_cols, int64_t row_pitch_bytes);
+int lmh_block_rows(int n_cols, int64_t row_pitch_bytes, int n_rows, int num_cu);
 // workgroups of an lm_head launch over n_tasks tasks = records per column it leaves
-int lmh_records(int n_tasks, int num_cu);
+int lmh_records(int n_cols, int n_tasks, int num_cu);
 
 // ---------------------------------------------------------------- relevance finalize
 struct RelFinalizeArgs {

@@ -17,6 +17,15 @@ pytestmark = pytest.mark.gpu
     (1, 5, 1, True, 33000, 256, 16),      # several blocks per workgroup, k * k candidates
     (2, 16, 1, True, 20001, 128, 4),      # more hidden rows than waves of the merge
     (8, 8, 8, False, 8192, 256, 5),       # 64 hidden rows of one sequence
+    (33, 1, 1, False, 33333, 256, 4),     # smallest of the wide pass, second half one column
+    (7, 5, 1, False, 8192, 384, 4),       # 64-row blocks
+    (12, 5, 1, True, 33000, 256, 4),      # two groups of 36 columns
+    (17, 5, 1, False, 65, 128, 16),       # two groups of 45 and 40, one row beyond a block
+    (8, 16, 1, False, 40001, 128, 2),     # 128 columns
+    (26, 5, 1, False, 33000, 256, 4),     # three groups: a full pass and a narrower one
+    (6, 10, 2, True, 20001, 256, 4),      # trees: two groups of four and two chains
+    (14, 5, 1, False, 8192, 128, 4),      # two groups of 35, 64-row blocks
+    (9, 16, 1, False, 5000, 128, 1),      # a last pass of 16 columns
 ])
 def test_edges(B, K, n_br, bonus, V, d, topk):
     rows = K + (1 if bonus else 0)
