@@ -18,6 +18,8 @@
 //   The four streams merge their (max, sum, O) through LDS in a fixed order and the workgroup
 //   writes one fp32 partial per split.
 // Kernel 2 (combine): log-sum-exp merge of the split partials in split order, bf16 output.
+// Batches take attn_flat_kernel and attn_flat_combine_kernel: the same work per tile and workgroup,
+// divided evenly over all sequences of the call.
 #include "lvspec_dev.h"
 #include "lvspec_kernels.h"
 
@@ -256,6 +258,8 @@ LVS_DEV void issue_part(const uint8_t* __restrict__ base, int64_t row_stride_byt
   }
 }
 
+// Tiles t_begin .. t_end - 1 of one unit, by the whole workgroup: stream, merge, write the partial
+// record that record() points to.
 // RS = 1: four waves, each streaming its own tiles through a private ring and holding all
 //         16*NBW query rows (no barrier in the main loop).
 // RS > 1: 4*RS waves; the RS waves of a stream share one ring and one copy of every K/V tile,
@@ -265,105 +269,20 @@ LVS_DEV void issue_part(const uint8_t* __restrict__ base, int64_t row_stride_byt
 //         overlap.  The waves of the workgroup meet at two barriers per tile round.
 // RS = 3: as RS = 2 (the first two waves of a stream issue its copies) plus a third wave per
 //         stream that only computes: 48 query rows, for row counts between 33 and 48.
-//
-// Fast start.  All waves of all workgroups read the same few lines of the argument buffer when
-// the kernel starts, and that read is slow (in-kernel timestamps: the first wave has its
-// arguments 0.9 us after entry, the median wave after 2.5 us, the last after 4 us), so the
-// memory pipeline fills late.  For one sequence whose length the host knows (fast = 1: the
-// common decode case), everything the first tile copies depend on travels in thirteen leading
-// scalar arguments, which qualify for kernel-argument
-// preloading into scalar registers by the command processor (the file is built with
-// -amdgpu-kernarg-preload-count; without that service the compatibility prologue loads them):
-//   k0, v0, kv_sh0, kv_sl0   cache pointers and strides (elements)
-//   n_split0, split_mul0     key-range splits and their multiply-shift divisor
-//   Hkv0, hkv_mul0           kv heads and their multiply-shift divisor
-//   packed0                  bits 0-7 shift of the split divisor, bit 8 xcd_map, bits 16-21 gamma,
-//                            bits 24-30 shift of the head divisor, bit 31 fast
-//   len0                     kv_len[0]
-// The structure behind them is then first needed for the query rows, behind the first copies.
-// In every other case (fast = 0) the kernel starts from the structure as before.
-template <int RS, int NBW>
-__global__ __launch_bounds__(256 * RS, 1) void attn_split_kernel(
-    const uint16_t* k0, const uint16_t* v0, int64_t kv_sh0, int kv_sl0, int n_split0,
-    uint32_t split_mul0, int Hkv0, uint32_t hkv_mul0, uint32_t packed0, int len0,
-    const AttnKernelArgs p) {
-  extern __shared__ __align__(16) uint8_t smem[];
+// Args: the argument structure, as a parameter or behind a pointer into the argument buffer.
+template <int RS, int NBW, class Args, class Record>
+LVS_DEV void attn_segment(const Args& p, uint8_t* smem, int lane, int wave, int b, int kvh,
+                          int rc, int L, int gamma, int n_tiles, int t_begin, int t_end,
+                          const uint8_t* kbase, const uint8_t* vbase, int64_t rsb,
+                          Record&& record) {
   constexpr int NB = NBW;
   constexpr int RPAD = 16 * NBW * RS;
   constexpr int NT = 256 * RS;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int stream = wave & 3;
   const int rh = wave >> 2;
   const int n16 = lane & 15;
   const int g4 = lane >> 4;
-  LVS_TRACE_BEGIN;
-  LVS_TRACE(0);
-  int split, unit, kvh, b, rc, L, gamma, n_split;
-  FastDiv div_split;
-  const uint8_t* kbase;
-  const uint8_t* vbase;
-  int64_t rsb;
-  if (packed0 >> 31) {
-    gamma = (int)((packed0 >> 16) & 63u);
-    n_split = n_split0;
-    div_split = FastDiv{split_mul0, packed0 & 255u};
-    decode_block((int)((packed0 >> 8) & 1u), blockIdx.x, div_split, n_split, split, unit);
-    // one sequence: unit = row chunk * Hkv + kv head
-    rc = (int)fast_div((uint32_t)unit, FastDiv{hkv_mul0, (packed0 >> 24) & 127u});
-    kvh = unit - rc * Hkv0;
-    b = 0;
-    L = len0;
-    rsb = (int64_t)kv_sl0 * 2;
-    kbase = reinterpret_cast<const uint8_t*>(k0) + (int64_t)kvh * kv_sh0 * 2;
-    vbase = reinterpret_cast<const uint8_t*>(v0) + (int64_t)kvh * kv_sh0 * 2;
-  } else {
-    // Everything the first tile copies need comes from the block id and the launch arguments
-    // in straight-line code.  One statement that needs all of them in scalar registers: the
-    // compiler otherwise fetches each argument right before its first use, which turns the
-    // start of the kernel into a chain of dependent scalar-memory round trips.
-    asm volatile("" ::"s"(p.k), "s"(p.v), "s"(p.kv_len), "s"(p.kv_sb), "s"(p.kv_sh), "s"(p.kv_sl),
-                 "s"(p.gamma), "s"(p.Hkv), "s"(p.xcd_map), "s"(p.n_rc), "s"(p.n_split),
-                 "s"(p.len_mode), "s"(p.div_split.mul), "s"(p.div_split.shift),
-                 "s"(p.div_hkv.mul), "s"(p.div_hkv.shift), "s"(p.div_rc.mul),
-                 "s"(p.div_rc.shift));
-    gamma = p.gamma;
-    n_split = p.n_split;
-    div_split = p.div_split;
-    decode_block(p.xcd_map, blockIdx.x, div_split, n_split, split, unit);
-    const int z = (int)fast_div((uint32_t)unit, p.div_hkv);
-    kvh = unit - z * p.Hkv;
-    b = (int)fast_div((uint32_t)z, p.div_rc);
-    rc = z - b * p.n_rc;
-    // The sequence length, uniform over the workgroup.  Host-known lengths of small batches sit
-    // in the argument lines fetched above (a scalar-cache hit); a larger host table is a
-    // further line of the argument buffer, which nobody has touched yet (a trip to memory,
-    // slower than the device read below, which usually hits in L2: it is used only without a
-    // device array).  The device read goes through a scalar register inside its branch, so the
-    // wait for it stays there.
-    if (p.len_mode == 1) {
-      L = p.len_hot[b < 5 ? b : 0];
-    } else if (p.len_mode == 2) {
-      L = p.len_host[b & 31];
-    } else {
-      // a length from device memory is not the host's to check: a stale or oversized value is
-      // clamped so that no copy reaches past the rows the caller declared (cap)
-      L = __builtin_amdgcn_readfirstlane(p.kv_len[b]);
-      L = L < 0 ? 0 : (L > p.lmax ? p.lmax : L);
-    }
-    rsb = p.kv_sl * 2;
-    kbase = reinterpret_cast<const uint8_t*>(p.k) +
-            ((int64_t)b * p.kv_sb + (int64_t)kvh * p.kv_sh) * 2;
-    vbase = reinterpret_cast<const uint8_t*>(p.v) +
-            ((int64_t)b * p.kv_sb + (int64_t)kvh * p.kv_sh) * 2;
-  }
   const int n_keys = L + gamma;
-  const int n_tiles = (n_keys + kTileKeys - 1) / kTileKeys;
-  // balanced contiguous tile ranges: the first (n_tiles % n_split) splits get one tile more
-  const int t_base = (int)fast_div((uint32_t)n_tiles, div_split);
-  const int t_rem = n_tiles - t_base * n_split;
-  const int t_begin = split * t_base + (split < t_rem ? split : t_rem);
-  const int t_end = t_begin + t_base + (split < t_rem ? 1 : 0);
   // A workgroup whose tile count is 4q + 1 or 4q + 2 would run q + 1 rounds, the last with one
   // or two of its four streams: that round is pure latency (its data arrived long before) and,
   // when most workgroups have 4q tiles, it is what the whole launch ends on (the 32B shape with
@@ -449,7 +368,6 @@ __global__ __launch_bounds__(256 * RS, 1) void attn_split_kernel(
   // the loop see tile copies only.
   asm volatile("" ::"s"(p.q), "s"(p.q_sb), "s"(p.q_sg), "s"(p.q_sh), "s"(p.G), "s"(p.R),
                "s"(p.Hkv), "s"(p.div_g.mul), "s"(p.div_g.shift));   // one batch, see above
-  const int bh = b * p.Hkv + kvh;
   u32x4 qreg[NB][4];
   int draft_row[NB];      // draft row of this lane's query row, -1 past the last row
 #pragma unroll
@@ -457,7 +375,7 @@ __global__ __launch_bounds__(256 * RS, 1) void attn_split_kernel(
     const int r = rc * RPAD + (rh * NBW + nb) * 16 + n16;
     const bool valid = r < p.R;
     const int rcl = valid ? r : p.R - 1;
-    const int i = (int)fast_div((uint32_t)rcl, p.div_g);
+    const int i = (int)fast_div((uint32_t)rcl, FastDiv{p.div_g.mul, p.div_g.shift});
     const int gq = rcl - i * p.G;
     draft_row[nb] = valid ? i : -1;
     const uint16_t* qp = p.q + (int64_t)b * p.q_sb + (int64_t)i * p.q_sg +
@@ -654,7 +572,7 @@ __global__ __launch_bounds__(256 * RS, 1) void attn_split_kernel(
   }
   __syncthreads();
   LVS_TRACE(7);
-  float* part = p.ws + (((size_t)bh * p.n_rc + rc) * n_split + split) * (size_t)(RPAD * 131);
+  float* part = record();
   // only the rows that exist are written (the combine kernel reads no others)
   const int rows_here = p.R - rc * RPAD < RPAD ? p.R - rc * RPAD : RPAD;
   for (int row = threadIdx.x; row < rows_here; row += NT) {
@@ -690,8 +608,382 @@ __global__ __launch_bounds__(256 * RS, 1) void attn_split_kernel(
     asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(po + (size_t)row * 128 + c4), "v"(o4)
                  : "memory");
   }
+}
+
+// Fast start.  All waves of all workgroups read the same few lines of the argument buffer when
+// the kernel starts, and that read is slow (in-kernel timestamps: the first wave has its
+// arguments 0.9 us after entry, the median wave after 2.5 us, the last after 4 us), so the
+// memory pipeline fills late.  For one sequence whose length the host knows (fast = 1: the
+// common decode case), everything the first tile copies depend on travels in thirteen leading
+// scalar arguments, which qualify for kernel-argument
+// preloading into scalar registers by the command processor (the file is built with
+// -amdgpu-kernarg-preload-count; without that service the compatibility prologue loads them):
+//   k0, v0, kv_sh0, kv_sl0   cache pointers and strides (elements)
+//   n_split0, split_mul0     key-range splits and their multiply-shift divisor
+//   Hkv0, hkv_mul0           kv heads and their multiply-shift divisor
+//   packed0                  bits 0-7 shift of the split divisor, bit 8 xcd_map, bits 16-21 gamma,
+//                            bits 24-30 shift of the head divisor, bit 31 fast
+//   len0                     kv_len[0]
+// The structure behind them is then first needed for the query rows, behind the first copies.
+// In every other case (fast = 0) the kernel starts from the structure as before.
+template <int RS, int NBW>
+__global__ __launch_bounds__(256 * RS, 1) void attn_split_kernel(
+    const uint16_t* k0, const uint16_t* v0, int64_t kv_sh0, int kv_sl0, int n_split0,
+    uint32_t split_mul0, int Hkv0, uint32_t hkv_mul0, uint32_t packed0, int len0,
+    const AttnKernelArgs p) {
+  extern __shared__ __align__(16) uint8_t smem[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  LVS_TRACE_BEGIN;
+  LVS_TRACE(0);
+  int split, unit, kvh, b, rc, L, gamma, n_split;
+  FastDiv div_split;
+  const uint8_t* kbase;
+  const uint8_t* vbase;
+  int64_t rsb;
+  if (packed0 >> 31) {
+    gamma = (int)((packed0 >> 16) & 63u);
+    n_split = n_split0;
+    div_split = FastDiv{split_mul0, packed0 & 255u};
+    decode_block((int)((packed0 >> 8) & 1u), blockIdx.x, div_split, n_split, split, unit);
+    // one sequence: unit = row chunk * Hkv + kv head
+    rc = (int)fast_div((uint32_t)unit, FastDiv{hkv_mul0, (packed0 >> 24) & 127u});
+    kvh = unit - rc * Hkv0;
+    b = 0;
+    L = len0;
+    rsb = (int64_t)kv_sl0 * 2;
+    kbase = reinterpret_cast<const uint8_t*>(k0) + (int64_t)kvh * kv_sh0 * 2;
+    vbase = reinterpret_cast<const uint8_t*>(v0) + (int64_t)kvh * kv_sh0 * 2;
+  } else {
+    // Everything the first tile copies need comes from the block id and the launch arguments
+    // in straight-line code.  One statement that needs all of them in scalar registers: the
+    // compiler otherwise fetches each argument right before its first use, which turns the
+    // start of the kernel into a chain of dependent scalar-memory round trips.
+    asm volatile("" ::"s"(p.k), "s"(p.v), "s"(p.kv_len), "s"(p.kv_sb), "s"(p.kv_sh), "s"(p.kv_sl),
+                 "s"(p.gamma), "s"(p.Hkv), "s"(p.xcd_map), "s"(p.n_rc), "s"(p.n_split),
+                 "s"(p.len_mode), "s"(p.div_split.mul), "s"(p.div_split.shift),
+                 "s"(p.div_hkv.mul), "s"(p.div_hkv.shift), "s"(p.div_rc.mul),
+                 "s"(p.div_rc.shift));
+    gamma = p.gamma;
+    n_split = p.n_split;
+    div_split = p.div_split;
+    decode_block(p.xcd_map, blockIdx.x, div_split, n_split, split, unit);
+    const int z = (int)fast_div((uint32_t)unit, p.div_hkv);
+    kvh = unit - z * p.Hkv;
+    b = (int)fast_div((uint32_t)z, p.div_rc);
+    rc = z - b * p.n_rc;
+    // The sequence length, uniform over the workgroup.  Host-known lengths of small batches sit
+    // in the argument lines fetched above (a scalar-cache hit); a larger host table is a
+    // further line of the argument buffer, which nobody has touched yet (a trip to memory,
+    // slower than the device read below, which usually hits in L2: it is used only without a
+    // device array).  The device read goes through a scalar register inside its branch, so the
+    // wait for it stays there.
+    if (p.len_mode == 1) {
+      L = p.len_hot[b < 5 ? b : 0];
+    } else if (p.len_mode == 2) {
+      L = p.len_host[b & 31];
+    } else {
+      // a length from device memory is not the host's to check: a stale or oversized value is
+      // clamped so that no copy reaches past the rows the caller declared (cap)
+      L = __builtin_amdgcn_readfirstlane(p.kv_len[b]);
+      L = L < 0 ? 0 : (L > p.lmax ? p.lmax : L);
+    }
+    rsb = p.kv_sl * 2;
+    kbase = reinterpret_cast<const uint8_t*>(p.k) +
+            ((int64_t)b * p.kv_sb + (int64_t)kvh * p.kv_sh) * 2;
+    vbase = reinterpret_cast<const uint8_t*>(p.v) +
+            ((int64_t)b * p.kv_sb + (int64_t)kvh * p.kv_sh) * 2;
+  }
+  const int n_keys = L + gamma;
+  const int n_tiles = (n_keys + kTileKeys - 1) / kTileKeys;
+  // balanced contiguous tile ranges: the first (n_tiles % n_split) splits get one tile more
+  const int t_base = (int)fast_div((uint32_t)n_tiles, div_split);
+  const int t_rem = n_tiles - t_base * n_split;
+  const int t_begin = split * t_base + (split < t_rem ? split : t_rem);
+  const int t_end = t_begin + t_base + (split < t_rem ? 1 : 0);
+  attn_segment<RS, NBW>(p, smem, lane, wave, b, kvh, rc, L, gamma, n_tiles, t_begin, t_end, kbase,
+                        vbase, rsb, [&] {
+                          const size_t unit_rec = ((size_t)(b * p.Hkv + kvh) * p.n_rc + rc) * n_split;
+                          return p.ws + (unit_rec + split) * (size_t)(16 * NBW * RS * 131);
+                        });
   LVS_TRACE(8);
   LVS_TRACE_END;
+}
+
+// ---- several sequences: one line of tiles -----------------------------------------------------
+// The kv heads of all sequences lie one behind the other on a line; a unit (sequence b, kv head h)
+// takes its tiles and flat_pad empty places behind them.  Workgroup `pos` takes the pos-th of
+// n_pos equal stretches of the line, so the workgroups end together whatever the lengths are, and a
+// batch that does not divide the chip leaves no CU idle.  What bounds it is the copy rate; an equal
+// number of workgroups per unit (attn_split_kernel) ends on the longest sequence.  Per layer, before
+// and after: 16 sequences of 2230 to 30052 keys, 40 / 8 heads, 5 rows 185 -> 120 us (6.0 TB/s); 24 of
+// 3070 to 8795, 28 / 4 heads, one row 59 -> 48 us; 32 of 530 to 15500, 64 / 8 heads, 8 rows
+// 257 -> 119 us; equal lengths as before (4 of 65536 171 us, 8 of 8192 49 -> 47 us).
+// The empty places are the price of a unit (pipeline fill, merge, partial record) in tiles: a
+// stretch over several short units gets fewer tiles.  2, 5 and 10 places at up to 32 rows: 124.9,
+// 122.4, 124.7 us on the first of these batches; at 64 rows on the third: 152.6, 139.0, 126.4 us.
+// The partial record of (pos, unit) is number pos + unit: both only grow along the line, so the
+// numbers are distinct and the records of one unit are neighbours.
+__host__ __device__ constexpr int flat_pad(int rpad) { return rpad <= 32 ? 5 : 10; }
+constexpr int kFlatMinPlaces = 4;     // of a stretch
+
+// What both kernels need before their first loads, in preloaded scalar arguments (see "Fast start"):
+// packed: bits 0-5 B - 1, 6-10 gamma - 1, 11-18 Hkv - 1, 19-21 n_rc - 1, 22-27 stretches / 8, 28-29
+// where the lengths are: 0 device array (x0 x1 its address, x2 the largest length), 1 x0 .. x4,
+// 2 the table in the argument structure.
+struct FlatShape {
+  int B, gamma, Hkv, n_rc, n_pos;
+};
+
+LVS_DEV FlatShape flat_shape(uint32_t packed) {
+  return FlatShape{(int)(packed & 63u) + 1, (int)((packed >> 6) & 31u) + 1,
+                   (int)((packed >> 11) & 255u) + 1, (int)((packed >> 19) & 7u) + 1,
+                   (int)((packed >> 22) & 63u) * 8};
+}
+
+struct FlatLine {
+  int L;              // keys of sequence `lane` (0 past the last)
+  uint32_t tiles;     // of one kv head of that sequence
+  uint32_t pad;       // empty places behind a unit
+  uint32_t end;       // places of all kv heads of sequences 0 .. lane
+  uint32_t total;     // of the whole line, below 2^31 / n_pos (the launch checks it)
+  uint32_t n_pos;     // stretches in use
+};
+
+// x / n by a reciprocal and one correction, for quotients below 2^20 (the product is then off by
+// less than one) and x below 2^31: a third of the instructions of a full division, all of which
+// the first copies wait for.
+LVS_DEV uint32_t line_div(uint32_t x, uint32_t n) {
+  const uint32_t q = (uint32_t)((float)x * __builtin_amdgcn_rcpf((float)n));
+  const int rest = (int)(x - q * n);
+  return rest < 0 ? q - 1 : rest >= (int)n ? q + 1 : q;
+}
+
+// Every lane of every wave calls this; B <= 64.  `whole`: stretches to use for equal lengths, a
+// multiple of the units (0: no such number near n_pos); no stretch then lies over two units.
+template <int PAD>
+LVS_DEV FlatLine flat_line(const FlatShape& sh, uint32_t packed, uint32_t whole, uint32_t x0,
+                           uint32_t x1, uint32_t x2, uint32_t x3, uint32_t x4,
+                           const AttnKernelArgs& p, int lane) {
+  FlatLine f;
+  int L = 0;
+  const uint32_t mode = (packed >> 28) & 3u;
+  if (mode == 0) {
+    typedef const __attribute__((address_space(1))) int32_t* GlobalPtr;
+    const GlobalPtr kv_len = (GlobalPtr)(((uint64_t)x1 << 32) | x0);
+    L = kv_len[lane < sh.B ? lane : 0];
+    L = L < 0 ? 0 : (L > (int)x2 ? (int)x2 : L);    // as in attn_split_kernel
+  } else if (mode == 1) {
+    L = (int)(lane == 0 ? x0 : lane == 1 ? x1 : lane == 2 ? x2 : lane == 3 ? x3 : x4);
+  } else {
+    L = p.len_host[lane & 31];
+  }
+  f.L = lane < sh.B ? L : 0;
+  f.tiles = lane < sh.B ? (uint32_t)(L + sh.gamma + kTileKeys - 1) / kTileKeys : 0u;
+  const uint32_t one = (uint32_t)__builtin_amdgcn_readfirstlane((int)f.tiles);
+  const bool equal = whole != 0u && __ballot(lane < sh.B && f.tiles != one) == 0ull;
+  f.pad = equal ? 0u : PAD;
+  uint32_t sum = lane < sh.B ? (f.tiles + f.pad) * (uint32_t)sh.Hkv : 0u;
+  sum += dpp_move<0x111, 0xf>(0u, sum);    // inclusive sums: row shifts by 1, 2, 4, 8 ...
+  sum += dpp_move<0x112, 0xf>(0u, sum);
+  sum += dpp_move<0x114, 0xf>(0u, sum);
+  sum += dpp_move<0x118, 0xf>(0u, sum);
+  sum += dpp_move<0x142, 0xa>(0u, sum);    // ... and the two row broadcasts
+  sum += dpp_move<0x143, 0xc>(0u, sum);
+  f.end = sum;
+  f.total = (uint32_t)__builtin_amdgcn_readlane((int)sum, 63);
+  const uint32_t want = equal ? whole : (uint32_t)sh.n_pos;
+  const uint32_t most = f.total / kFlatMinPlaces;
+  f.n_pos = most < 1u ? 1u : most < want ? most : want;
+  return f;
+}
+
+// First place of stretch pos: floor(total * pos / n_pos), and the stretch that holds place v.
+LVS_DEV uint32_t flat_begin(const FlatLine& f, uint32_t pos, uint32_t quot) {
+  return quot * pos + line_div((f.total - quot * f.n_pos) * pos, f.n_pos);
+}
+LVS_DEV uint32_t flat_pos_of(const FlatLine& f, uint32_t v) {
+  return line_div((v + 1) * f.n_pos - 1, f.total);
+}
+
+LVS_DEV uint32_t read_lane(uint32_t x, int lane) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, lane);
+}
+
+// two pointers and ten words precede the structure in the argument buffer
+constexpr int kFlatArgsOffset = 56;
+static_assert(alignof(AttnKernelArgs) == 8, "the structure follows the leading arguments directly");
+
+// A workgroup per (stretch, row chunk); the row chunks of a stretch share an XCD's L2.  Strides in
+// units of eight elements; rc_mul_whole: ceil(65536 / n_rc), and `whole` of flat_line from bit 17.
+template <int RS, int NBW>
+__global__ __launch_bounds__(256 * RS, 1) void attn_flat_kernel(
+    const uint16_t* k0, const uint16_t* v0, uint32_t sb8, uint32_t sh8, uint32_t sl8,
+    uint32_t packed, uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3, uint32_t x4,
+    uint32_t rc_mul_whole, const AttnKernelArgs p) {
+  extern __shared__ __align__(16) uint8_t smem[];
+  constexpr int PAD = flat_pad(16 * NBW * RS);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const FlatShape sh = flat_shape(packed);
+  const FlatLine f = flat_line<PAD>(sh, packed, rc_mul_whole >> 17, x0, x1, x2, x3, x4, p, lane);
+  const uint32_t j = blockIdx.x >> 3;
+  const uint32_t j_pos = j * (rc_mul_whole & 0x1ffffu) >> 16;
+  const int rc = (int)(j - j_pos * (uint32_t)sh.n_rc);
+  const uint32_t per_xcd = (f.n_pos + 7) >> 3;      // neighbours on the line on one XCD
+  const uint32_t pos = (blockIdx.x & 7u) * per_xcd + j_pos;
+  if (j_pos >= per_xcd || pos >= f.n_pos) return;
+  const uint32_t quot = line_div(f.total, f.n_pos);
+  uint32_t v = flat_begin(f, pos, quot);
+  const uint32_t v_end = flat_begin(f, pos + 1, quot);
+  int b = __popcll(__ballot(f.end <= v));      // v < total: a sequence that exists
+  uint32_t n_tiles = read_lane(f.tiles, b);
+  const uint32_t off = v - (read_lane(f.end, b) - (n_tiles + f.pad) * (uint32_t)sh.Hkv);
+  int kvh = (int)line_div(off, n_tiles + f.pad);
+  uint32_t t0 = off - (uint32_t)kvh * (n_tiles + f.pad);
+  const int64_t rsb = (int64_t)sl8 * 16;
+  while (true) {
+    const int L = (int)read_lane((uint32_t)f.L, b);
+    const uint32_t t1 = t0 + (v_end - v) < n_tiles ? t0 + (v_end - v) : n_tiles;
+    if (t0 < t1) {
+      const int64_t base = ((int64_t)b * sb8 + (int64_t)kvh * sh8) * 16;
+      // The lane, the wave and the argument buffer are opaque once per unit: what depends on them
+      // is computed or fetched again.  The compiler otherwise moves all of it in front of the loop,
+      // where it waits for cold argument lines before the first copies and fills registers (the
+      // start of a call cost 1.3 us more).
+      int ln = lane, wv = wave;
+      auto at = __builtin_amdgcn_kernarg_segment_ptr();
+      asm volatile("" : "+v"(ln), "+s"(wv), "+s"(at));
+      typedef const __attribute__((address_space(4))) uint8_t* BytesPtr;
+      typedef const __attribute__((address_space(4))) AttnKernelArgs* ArgsPtr;
+      const auto& args = *(ArgsPtr)((BytesPtr)at + kFlatArgsOffset);
+      attn_segment<RS, NBW>(
+          args, smem, ln, wv, b, kvh, rc, L, sh.gamma, (int)n_tiles, (int)t0, (int)t1,
+          reinterpret_cast<const uint8_t*>(k0) + base, reinterpret_cast<const uint8_t*>(v0) + base,
+          rsb, [&] {
+            const size_t rec = (size_t)rc * (sh.n_pos + sh.B * sh.Hkv) + pos + b * sh.Hkv + kvh;
+            return args.ws + rec * (size_t)(16 * NBW * RS * 131);
+          });
+    }
+    v += n_tiles + f.pad - t0;
+    if (v >= v_end) break;
+    t0 = 0;
+    if (++kvh == sh.Hkv) {
+      kvh = 0;
+      n_tiles = read_lane(f.tiles, ++b);
+    }
+    __syncthreads();   // the merge buffers have been read: the next unit's copies may overwrite them
+  }
+}
+
+// One group of 32 lanes per output row and share of its records, four channels a lane.  SG groups
+// (consecutive in the workgroup) share a row: record s of the unit goes to group s % SG.  Few
+// records per row (a large batch) want few groups per row; sums run in a fixed order.  A chain of
+// latencies like attn_combine_kernel: the lengths, then all of the first records at once (running
+// maximum per group), then the output.  Grid: row groups, kv heads, sequences.
+template <int SG, int PAD>
+__global__ __launch_bounds__(256) void attn_flat_combine_kernel(
+    const float* ws, uint32_t packed, uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3,
+    uint32_t x4, int R, int rpad, uint32_t whole, const AttnKernelArgs p) {
+  constexpr int kRows = 8 / SG;
+  constexpr int kBatch = 4;          // records a group asks for at a time
+  __shared__ float sm_o[8][128];
+  __shared__ float sm_s[8][3];
+  const int lane = threadIdx.x & 63;
+  const int group = threadIdx.x >> 5;
+  const int sg = group % SG;
+  const int l32 = threadIdx.x & 31;
+  const FlatShape sh = flat_shape(packed);
+  const int kvh = blockIdx.y, b = blockIdx.z;
+  const int bh = b * sh.Hkv + kvh;
+  const int row_u = blockIdx.x * kRows + group / SG;
+  const bool valid = row_u < R;
+  const int r = valid ? row_u : R - 1;       // query row of this kv head
+  int rc = 0, rr = r;
+  while (rr >= rpad) {                       // at most eight row chunks
+    rr -= rpad;
+    ++rc;
+  }
+  const FlatLine f = flat_line<PAD>(sh, packed, whole, x0, x1, x2, x3, x4, p, lane);
+  const uint32_t n_tiles = read_lane(f.tiles, b);
+  const uint32_t u0 = read_lane(f.end, b) - (n_tiles + f.pad) * (uint32_t)(sh.Hkv - kvh);
+  const uint32_t first = flat_pos_of(f, u0);
+  const int ns = (int)(flat_pos_of(f, u0 + n_tiles - 1) - first) + 1;
+  const size_t stride = (size_t)rpad * 131;
+  const float* base = ws + ((size_t)rc * (sh.n_pos + sh.B * sh.Hkv) + first + bh) * stride;
+  const float* stat = base + rr;
+  const float* orow = base + 3 * rpad + rr * 128 + l32 * 4;
+
+  f32x4 o = {0.f, 0.f, 0.f, 0.f};
+  float mm = kNegBig, l = 0.f, lv = 0.f;
+  for (int s0 = sg; s0 < ns; s0 += kBatch * SG) {
+    float m[kBatch], ls[kBatch], vs[kBatch];
+    f32x4 os[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int s = s0 + u * SG < ns ? s0 + u * SG : ns - 1;
+      m[u] = stat[s * stride];
+      ls[u] = stat[s * stride + rpad];
+      vs[u] = stat[s * stride + 2 * rpad];
+      os[u] = *reinterpret_cast<const f32x4*>(orow + s * stride);
+    }
+    // the output's arguments, a cold read, while the records are on their way
+    asm volatile("" ::"s"(p.out), "s"(p.o_sb), "s"(p.o_sg), "s"(p.o_sh), "s"(p.lse),
+                 "s"(p.vis_mass), "s"(p.div_g.mul), "s"(p.div_g.shift), "s"(p.G));
+    float top = mm;
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) top = fmaxf(top, m[u]);   // a clamped copy changes nothing
+    const float keep = fast_exp2(mm - top);
+    l *= keep;
+    lv *= keep;
+    o *= keep;
+    mm = top;
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const float w = s0 + u * SG < ns ? fast_exp2(m[u] - mm) : 0.f;
+      l += ls[u] * w;
+      lv += vs[u] * w;
+      o += os[u] * w;
+    }
+  }
+  if constexpr (SG > 1) {
+    *reinterpret_cast<f32x4*>(&sm_o[group][l32 * 4]) = o;
+    if (l32 == 0) {
+      sm_s[group][0] = mm;
+      sm_s[group][1] = l;
+      sm_s[group][2] = lv;
+    }
+    __syncthreads();
+    if (sg != 0) return;
+    float top = mm;
+#pragma unroll
+    for (int k = 1; k < SG; ++k) top = fmaxf(top, sm_s[group + k][0]);
+    const float keep = fast_exp2(mm - top);
+    l *= keep;
+    lv *= keep;
+    o *= keep;
+    mm = top;
+#pragma unroll
+    for (int k = 1; k < SG; ++k) {
+      const float w = fast_exp2(sm_s[group + k][0] - top);    // 0 for a group without records
+      l += sm_s[group + k][1] * w;
+      lv += sm_s[group + k][2] * w;
+      o += *reinterpret_cast<const f32x4*>(&sm_o[group + k][l32 * 4]) * w;
+    }
+  }
+  if (!valid) return;
+  const int i = (int)fast_div((uint32_t)r, p.div_g);
+  const int h = kvh * p.G + (r - i * p.G);
+  const float inv = 1.0f / l;
+  uint16_t* op = p.out + (int64_t)b * p.o_sb + (int64_t)i * p.o_sg + (int64_t)h * p.o_sh + l32 * 4;
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  *reinterpret_cast<u32x2*>(op) =
+      u32x2{pack_bf16(o[0] * inv, o[1] * inv), pack_bf16(o[2] * inv, o[3] * inv)};
+  if (l32 == 0) {
+    const size_t idx = ((size_t)b * p.Hq + h) * sh.gamma + i;
+    if (p.lse) p.lse[idx] = (mm + log2f(l)) * 0.69314718055994530942f;
+    if (p.vis_mass) p.vis_mass[idx] = lv * inv;
+  }
 }
 
 // One workgroup of 128 * kSG threads per (unit, row slot), i.e. per output row (b, i, h).  Wave w
@@ -871,8 +1163,77 @@ static hipError_t launch_split(const AttnKernelArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+namespace {
+// leading arguments of both kernels of the line, see flat_shape
+struct FlatArgs {
+  uint32_t packed, x[5];
+};
+
+FlatArgs flat_args(const AttnKernelArgs& a) {
+  FlatArgs f{};
+  f.packed = (uint32_t)(a.B - 1) | (uint32_t)(a.gamma - 1) << 6 | (uint32_t)(a.Hkv - 1) << 11 |
+             (uint32_t)(a.n_rc - 1) << 19 | (uint32_t)(a.flat_pos / 8) << 22 |
+             (uint32_t)a.len_mode << 28;
+  if (a.len_mode == 1) {
+    for (int b = 0; b < 5; ++b) f.x[b] = (uint32_t)a.len_hot[b];
+  } else if (a.len_mode == 0) {
+    const uint64_t at = reinterpret_cast<uint64_t>(a.kv_len);
+    f.x[0] = (uint32_t)at;
+    f.x[1] = (uint32_t)(at >> 32);
+    f.x[2] = (uint32_t)a.lmax;
+  }
+  return f;
+}
+}  // namespace
+
+template <int RS, int NBW>
+static hipError_t launch_flat(const AttnKernelArgs& a, hipStream_t stream) {
+  constexpr int rpad = 16 * NBW * RS;
+  const size_t lds = split_lds_bytes(rpad, true);
+  static LdsLimitOnce lds_limit;
+  hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(&attn_flat_kernel<RS, NBW>), lds);
+  if (e != hipSuccess) return e;
+  const FlatArgs f = flat_args(a);
+  const int units = a.B * a.Hkv;
+  const int over = a.flat_pos % units;
+  const uint32_t whole = over == 0 || a.flat_pos >= 4 * units ? a.flat_pos - over : 0;
+  hipLaunchKernelGGL((attn_flat_kernel<RS, NBW>), dim3(a.flat_pos * a.n_rc), dim3(256 * RS), lds,
+                     stream, a.k, a.v, (uint32_t)(a.kv_sb / 8), (uint32_t)(a.kv_sh / 8),
+                     (uint32_t)(a.kv_sl / 8), f.packed, f.x[0], f.x[1], f.x[2], f.x[3], f.x[4],
+                     (uint32_t)((65536 + a.n_rc - 1) / a.n_rc) | whole << 17, a);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  // eight groups per row where a unit has about eight records or more, two elsewhere
+  constexpr int PAD = flat_pad(rpad);
+  if (a.flat_pos >= 8 * units)
+    hipLaunchKernelGGL((attn_flat_combine_kernel<8, PAD>), dim3(a.R, a.Hkv, a.B), dim3(256), 0,
+                       stream, a.ws, f.packed, f.x[0], f.x[1], f.x[2], f.x[3], f.x[4], a.R, rpad,
+                       whole, a);
+  else
+    hipLaunchKernelGGL((attn_flat_combine_kernel<2, PAD>), dim3((a.R + 3) / 4, a.Hkv, a.B), dim3(256),
+                       0, stream, a.ws, f.packed, f.x[0], f.x[1], f.x[2], f.x[3], f.x[4], a.R, rpad,
+                       whole, a);
+  return hipGetLastError();
+}
+
+int attn_flat_positions(int B, int Hkv, int rpad, int n_rc, int64_t cap, int num_cu) {
+  if (B < 2 || B > 64 || Hkv > 256 || n_rc > 8) return 0;
+  int pos = num_cu / n_rc / 8 * 8;
+  if (pos > 504) pos = 504;
+  if (pos < 8) return 0;
+  // place numbers times positions stay in 32 bits
+  const int64_t places = (cap + kTileKeys - 1) / kTileKeys + flat_pad(rpad);   // of the longest unit
+  return places * B * Hkv < (int64_t)0x7fffffff / (pos + 1) ? pos : 0;
+}
+
 // variant = 10 * RS + NBW; 0 picks the default for the row-chunk size
 hipError_t launch_attn(const AttnKernelArgs& a, hipStream_t stream) {
+  if (a.flat_pos > 0) {
+    if (a.rpad == 16) return launch_flat<1, 1>(a, stream);
+    if (a.rpad == 32) return launch_flat<2, 1>(a, stream);
+    if (a.rpad == 48) return launch_flat<3, 1>(a, stream);
+    return launch_flat<2, 2>(a, stream);
+  }
   int variant = a.variant;
   if (variant == 0) variant = a.rpad == 16 ? 11 : a.rpad == 32 ? 21 : a.rpad == 48 ? 31 : 22;
   hipError_t e;

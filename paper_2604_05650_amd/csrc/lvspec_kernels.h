@@ -71,6 +71,8 @@ struct AttnKernelArgs {
   // -- used later
   float scale_log2e;
   int B;
+  int flat_pos;  // > 0: equal stretches of one line over all sequences (a multiple of 8, B <= 64);
+                 // then ws is [n_rc][flat_pos + B*Hkv][rpad * 131]
   int variant;   // kernel variant, 0 = default for rpad (development knob; host side only)
   const int32_t* vis_begin;   // nullptr = no span
   const int32_t* vis_end;
@@ -83,6 +85,8 @@ struct AttnKernelArgs {
 static_assert(offsetof(AttnKernelArgs, len_host) == 192, "prologue arguments fill three 64-byte lines");
 
 hipError_t launch_attn(const AttnKernelArgs& a, hipStream_t stream);
+// stretches of the line over all sequences of a batch; 0: this shape has none
+int attn_flat_positions(int B, int Hkv, int rpad, int n_rc, int64_t cap, int num_cu);
 
 // ---------------------------------------------------------------- streamed skinny GEMM
 // C[r][c] = sum_t A[r][t] * X[c][t]: A is a tall bf16 matrix streamed once from HBM (video

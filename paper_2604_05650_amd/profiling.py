@@ -110,7 +110,8 @@ def mfma(db_path: str) -> str:
 
 
 GROUPS = {   # kernels launched by one call of each entry point
-    "verify_attn": ("attn_split_kernel", "attn_combine_kernel"),
+    "verify_attn": ("attn_split_kernel", "attn_combine_kernel", "attn_flat_kernel",
+                    "attn_flat_combine_kernel"),
     "visual_relevance": ("gemm_stream_kernel<0", "gemm_stream_kernel<2", "rel_finalize_kernel",
                          "rel_cand_kernel", "rel_merge_kernel"),
     "lm_head_accept": ("gemm_stream_kernel<1", "accept_finalize_kernel"),
@@ -215,7 +216,7 @@ def summary(run_dir: str, out_dir: str, workloads: list) -> None:
             + _own(counters(db("write"), "WRITE_SIZE"), True) + "\n\n"
             "HBM bytes per library call (fetch + write, scaled) vs algorithmic bytes:\n" + ratio + "\n")
         tab = mfma_table(db("mfma"))
-        key = {"verify_attn": "attn_split_kernel", "visual_relevance": "gemm_stream_kernel<0",
+        key = {"verify_attn": ("attn_split_kernel", "attn_flat_kernel"), "visual_relevance": "gemm_stream_kernel<0",
                "lm_head_accept": "gemm_stream_kernel<1"}
         tr[name + ":mfma"] = {
             k: {"kernel": r["kernel"], "mfma_flops_per_launch": round(r["mfma_flops_per_launch"]),

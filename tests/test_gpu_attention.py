@@ -129,6 +129,35 @@ def test_batch_with_different_lengths_and_spans():
     _check(q, k, v, kv_len, [16, 5, 0, 0], [900, 5, 0, 600], tag="ragged batch")
 
 
+@pytest.mark.parametrize("Hq,Hkv,gamma", [(7, 1, 2), (16, 4, 5), (16, 2, 5), (40, 8, 8), (6, 1, 20)])
+@pytest.mark.parametrize("kv_len", [
+    [3, 0],                                  # fewer tiles than workgroups
+    [4095, 31, 0, 64, 1],                    # one long sequence: units over many workgroups
+    [250 + 13 * b for b in range(33)],       # workgroups over several units each
+    [65 * (b % 3) for b in range(64)],       # the largest batch one line takes
+    [4 * (b % 5) for b in range(65)],        # one more
+])
+def test_batches_share_the_workgroups(Hq, Hkv, gamma, kv_len):
+    # 16-, 32-, 48- and 64-row variants and two row chunks; then equal splits per unit by a workspace
+    # that holds only their partials: another summation order, so the bf16 results differ by roundings
+    from paper_2604_05650_amd import binding as L
+    B, D = len(kv_len), 128
+    cap = max(kv_len) + gamma + 2
+    q = synth.normal_bf16((109, Hq, B, 0), (B, gamma, Hq, D), 1.0)
+    k = synth.normal_bf16((109, Hq, B, 1), (B, Hkv, cap, D), 1.0)
+    v = synth.normal_bf16((109, Hq, B, 2), (B, Hkv, cap, D), 1.0)
+    vb, ve = [n // 5 for n in kv_len], [n // 2 + 1 for n in kv_len]
+    _check(q, k, v, kv_len, vb, ve, tag=f"line Hq{Hq} Hkv{Hkv} g{gamma} B{B}")
+    tq, tk, tv = t_bf16(q), t_bf16(k), t_bf16(v)
+    a = L.verify_attn_args(tq, tk, tv, t_i32(kv_len), out=torch.empty_like(tq))
+    plan = L.describe_plan(attn=a)
+    rows = B * Hkv * plan["attn_row_chunks"] * plan["attn_splits"] * plan["attn_rows_padded"]
+    split = torch.empty((rows * 131 * 4,), dtype=torch.uint8, device=dev())
+    out = L.verify_attn(tq, tk, tv, t_i32(kv_len), workspace=split)
+    o_out, _, _ = oracle.verify_attn(q, k, v, kv_len)
+    assert_rows_close(bf16_out_to_f64(out), o_out, "equal splits")
+
+
 def test_draft_tree_mask():
     B, gamma, Hq, Hkv, D, L = 1, 6, 8, 2, 128, 200
     q = synth.normal_bf16((104, 0), (B, gamma, Hq, D), 1.0)
