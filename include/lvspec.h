@@ -314,7 +314,8 @@ typedef struct {
   int32_t rel_slices;            /* slices of the two-kernel Top-N; 0 = single-kernel selection */
   int32_t rel_slice_rows;        /* video rows per slice */
   int32_t acc_rows_per_task;     /* vocabulary rows per lm_head task: 64 or 128 (a stage of the
-                                    pass holds half of one, one, or two) */
+                                    pass holds half of one, one, or two); the rows of a task
+                                    add their products up in one order */
   int32_t acc_chains_per_pass;   /* chains of a group (up to 64 hidden rows) */
   int32_t acc_passes;            /* groups; two of them share one pass over lm_head */
 } lvspec_plan_info;

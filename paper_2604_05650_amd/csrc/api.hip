@@ -215,14 +215,15 @@ int plan_rel(const lvspec_rel_args* a, RelPlan* pl) {
 struct AccPlan {
   int n_tasks, n_cols;     // n_cols: columns of one (full) pass
   int per_pass;            // chains of one pass: one group, or two side by side
-  int rows_per_block;      // vocabulary rows per task: one or two blocks
+  int rows_per_block;      // vocabulary rows with one order of summation, 64 or 128
   int block_rows;          // vocabulary rows per pipeline stage
   int group;               // chains of a group (a multiple of the branches per sequence)
   int n_rec;               // records per column (workgroups of the lm_head launch)
   size_t off_cand, off_sz, ws_bytes;
 };
 
-int plan_acc(const lvspec_accept_args* a, AccPlan* pl) {
+// two: groups of chains share a pass in pairs, which takes records for twice the columns
+int plan_acc(const lvspec_accept_args* a, AccPlan* pl, bool two = true) {
   if (a == nullptr) return LVSPEC_EINVAL;
   if (a->B < 1 || a->gamma < 1 || a->gamma > LVSPEC_MAX_GAMMA || a->d < 1 || a->V < 1 ||
       a->topk < 1 || a->topk > LVSPEC_MAX_TOPK)
@@ -251,15 +252,15 @@ int plan_acc(const lvspec_accept_args* a, AccPlan* pl) {
   const int groups = (a->B + gmax - 1) / gmax;
   pl->group = ((a->B + groups - 1) / groups + nbr - 1) / nbr * nbr;
   if (pl->group > a->B) pl->group = a->B;
-  pl->per_pass = pl->group < a->B ? 2 * pl->group : pl->group;
+  pl->per_pass = two && pl->group < a->B ? 2 * pl->group : pl->group;
   pl->n_cols = (pl->per_pass < a->B ? pl->per_pass : a->B) * rpc;
-  // Tasks are counted in blocks of 64 rows, except that long candidate lists (k > 8) and row
-  // pitches that want 128-row stages pair them up.  A pair of 64-row blocks is still streamed
-  // block by block: at k = 16 (d = 3584, V = 152064) 163 us against 171 us in 128-row stages.
-  // More than 32 columns: the wide kernel's blocks hold one or two tasks.
-  pl->block_rows = lvspec::lmh_block_rows(pl->n_cols, (a->w_sv > 0 ? a->w_sv : a->d) * 2, a->V,
-                                          num_compute_units());
-  pl->rows_per_block = pl->n_cols > 32 ? 64 : a->topk > 8 ? 128 : pl->block_rows;
+  // The block whose rows add their chunks of d up in one order (see issue_stage): 64 rows, except
+  // 128 for up to 32 columns where the row pitch wants 128-row stages or many candidates are
+  // asked for.  A pair of 64-row blocks is still streamed block by block: at k = 16 (d = 3584,
+  // V = 152064) 163 us against 171 us in 128-row stages.
+  const int64_t pitch = (a->w_sv > 0 ? a->w_sv : a->d) * 2;
+  pl->rows_per_block = lvspec::lmh_order_rows(pl->n_cols, pitch, a->V, a->topk);
+  pl->block_rows = lvspec::lmh_block_rows(pl->n_cols, pitch, a->V, num_compute_units());
   pl->n_tasks = (a->V + pl->block_rows - 1) / pl->block_rows;
   pl->n_rec = lvspec::lmh_records(pl->n_cols, pl->n_tasks, num_compute_units());
   const size_t rec = (size_t)pl->n_rec * pl->n_cols;
@@ -505,6 +506,8 @@ int lvspec_loose_accept(const lvspec_accept_args* a, void* stream) {
   if (!stride_ok(a->hd_sb) || !stride_ok(a->hd_sg) || !stride_ok(w_sv) || a->hd_sg < a->d ||
       w_sv < a->d)
     return LVSPEC_EINVAL;
+  // a workspace too small for two groups in a pass is served group by group
+  if (a->workspace_bytes < pl.ws_bytes && (rc = plan_acc(a, &pl, false)) != LVSPEC_OK) return rc;
   rc = check_ws(a->workspace, a->workspace_bytes, pl.ws_bytes);
   if (rc != LVSPEC_OK) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
@@ -517,7 +520,8 @@ int lvspec_loose_accept(const lvspec_accept_args* a, void* stream) {
     // a last, narrower pass has its own stage size and grid, within the records of a full pass
     int block_rows = pl.block_rows, n_tasks = pl.n_tasks, n_rec = pl.n_rec;
     if (n_cols < pl.n_cols) {
-      block_rows = lvspec::lmh_block_rows(n_cols, w_sv * 2, a->V, num_compute_units());
+      block_rows = n_cols <= 32 && pl.rows_per_block == 64
+                       ? 64 : lvspec::lmh_block_rows(n_cols, w_sv * 2, a->V, num_compute_units());
       n_tasks = (a->V + block_rows - 1) / block_rows;
       n_rec = lvspec::lmh_records(n_cols, n_tasks, num_compute_units());
       const int room = (int)((int64_t)pl.n_rec * pl.n_cols / n_cols);
@@ -539,6 +543,7 @@ int lvspec_loose_accept(const lvspec_accept_args* a, void* stream) {
     g.half_cols = nb > pl.group ? pl.group * rpc : n_cols < 32 ? n_cols : 32;
     g.B = 1;
     g.rows_per_block = block_rows;
+    g.rot_shift = pl.rows_per_block > block_rows ? 1 : 0;
     g.n_rb = n_tasks;
     g.n_ds = 1;
     g.kc = a->d / 128;

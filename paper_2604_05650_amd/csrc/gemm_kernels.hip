@@ -137,7 +137,7 @@ LVS_DEV void setup_task(const GemmKernelArgs& p, Cursor& c, IssuePtrs<MB, NBX, R
   int b, rb, ds;
   decode_task<MODE>(p, c.task, b, rb, ds);
   const int n_rows = rows_of<MODE>(p, c, b);
-  ip.rot = c.task % p.kc;
+  ip.rot = (c.task >> p.rot_shift) % p.kc;
   const int rsub = lane / G::kLanesPerRow;
   const int cpos = lane % G::kLanesPerRow;
   const int64_t col_byte = (int64_t)ds * p.kc * RB;
@@ -172,7 +172,9 @@ LVS_DEV void setup_task(const GemmKernelArgs& p, Cursor& c, IssuePtrs<MB, NBX, R
 // walk the hidden dimension from different starting points, so at any moment their row
 // segments spread over all HBM channels (with a power-of-two row pitch, e.g. d = 8192, all
 // rows of a column chunk fall into the same few channels).  The order is a fixed function of
-// the task, so results stay reproducible.
+// the task, so results stay reproducible.  lm_head: of the block of 64 (rot_shift = 0) or 128
+// vocabulary rows, whatever the rows of a stage: a logit's bits, and with them the order of
+// tokens that nearly tie, do not depend on the kernel that took the row.
 template <int MB, int NBX, int RB>
 LVS_DEV void issue_stage(const IssuePtrs<MB, NBX, RB>& ip, int kc, int n_chunks, uint32_t slot,
                          int wave) {
@@ -512,6 +514,12 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(const GemmKernelArg
 // in issue order, so X(i+1) is issued ahead of A(i+2) and the wait for X(i) leaves A(i+1) out.
 // Two groups of chains with up to 64 columns each share a pass, one in each half; a single group of
 // more than 32 columns is split over the halves.
+//
+// A block of 64 vocabulary rows adds its chunks up from chunk (block mod n_chunks) on, as in
+// gemm_stream_kernel.  The second block of a 128-row task thus starts one chunk later than the
+// first: it joins in at the task's second stage and ends one stage behind, while the X chunk of
+// a stage serves both (n_chunks + 1 stages; with one start for both blocks the logits are other
+// 32-bit sums, and tokens that tie within 6e-6 change places: 2 of 576 ids at k = 16).
 template <int MB, int NB2>
 struct Wide {
   static constexpr int kRowsWg = 64 * MB;
@@ -522,6 +530,7 @@ struct Wide {
   static constexpr int kAInstr = 2 * MB;        // copy instructions per wave and stage
   static constexpr int kXInstr = NB2;
   static constexpr int kZtStride = kRowsWg + 4; // floats per column of the epilogue tile
+  static constexpr int kLate = MB == 2 ? 1 : 0; // stages the second 64-row block starts late
   static_assert(kLds <= 160 * 1024, "LDS of one CU");
   static_assert(32 * kZtStride * 4 <= kASlot, "epilogue tile of 32 columns in one A slot");
 };
@@ -538,6 +547,10 @@ __global__ __launch_bounds__(512, 2) void lm_head_wide_kernel(const GemmKernelAr
   const int g4 = lane >> 4;
   const uint32_t ring = lds_addr(smem);
   const int n_chunks = p.kc;     // 256-byte chunks of a row
+  const int n_stages = n_chunks + W::kLate;
+  // the stages of a task in which this wave copies, and computes, rows of its block
+  const int copy_from = wave >= 4 ? W::kLate : 0;
+  const int comp_from = wr >= 2 ? W::kLate : 0;
 
   uint32_t oaddr[4];             // operand chunk 4*ks + g4 of row n16
 #pragma unroll
@@ -557,9 +570,9 @@ __global__ __launch_bounds__(512, 2) void lm_head_wide_kernel(const GemmKernelAr
     const int xi = col - xb * p.gamma;
     xcol[k] = p.x + (int64_t)xb * p.x_sb + (int64_t)xi * p.x_sg + ((n16 ^ (cl & 15)) << 4);
   }
-  // stage kc of a task reads chunk (kc + task) mod n_chunks, as in gemm_stream_kernel
+  // stage kc of a task reads chunk (kc + first 64-row block) mod n_chunks
   auto chunk_of = [&](int task, int kc) {
-    const int c = kc + task % n_chunks;
+    const int c = kc + (task * MB) % n_chunks;
     return c >= n_chunks ? c - n_chunks : c;
   };
   int ia_task = blockIdx.x, ia_kc = 0;     // next A stage to issue
@@ -574,16 +587,22 @@ __global__ __launch_bounds__(512, 2) void lm_head_wide_kernel(const GemmKernelAr
       arow[j] = p.a + (int64_t)row * p.a_sr + ((n16 ^ (rl & 15)) << 4);
     }
   };
+  // the next A stage, if there is one; returns whether this wave has a share of it
   auto issue_a = [&](int slot) {
-    const int64_t off = (int64_t)chunk_of(ia_task, ia_kc) * kRowBytes;
-    const uint32_t dst = ring + slot * W::kASlot + wave * (8 * MB * kRowBytes);
+    if (ia_task >= p.n_tasks) return false;
+    const bool mine = ia_kc >= copy_from && ia_kc < copy_from + n_chunks;
+    if (mine) {
+      const int64_t off = (int64_t)chunk_of(ia_task, ia_kc) * kRowBytes;
+      const uint32_t dst = ring + slot * W::kASlot + wave * (8 * MB * kRowBytes);
 #pragma unroll
-    for (int j = 0; j < W::kAInstr; ++j) dma16(arow[j] + off, dst + j * 1024);
-    if (++ia_kc == n_chunks) {
+      for (int j = 0; j < W::kAInstr; ++j) dma16(arow[j] + off, dst + j * 1024);
+    }
+    if (++ia_kc == n_stages) {
       ia_kc = 0;
       ia_task += gridDim.x;
       if (ia_task < p.n_tasks) setup_a();
     }
+    return mine;
   };
   auto issue_x = [&](int slot) {
     const int64_t off = (int64_t)chunk_of(ix_task, ix_kc) * kRowBytes;
@@ -591,7 +610,7 @@ __global__ __launch_bounds__(512, 2) void lm_head_wide_kernel(const GemmKernelAr
 #pragma unroll
     for (int k = 0; k < W::kXInstr; ++k)
       dma16<kCopyDefault>(xcol[k] + off, dst + (8 * k + wave) * 1024);
-    if (++ix_kc == n_chunks) {
+    if (++ix_kc == n_stages) {
       ix_kc = 0;
       ix_task += gridDim.x;
     }
@@ -622,17 +641,15 @@ __global__ __launch_bounds__(512, 2) void lm_head_wide_kernel(const GemmKernelAr
   wait_copies<0>();
   issue_x(0);
   issue_a(0);
-  bool a_ahead = ia_task < p.n_tasks;      // A of the next stage is on its way
-  if (a_ahead) issue_a(1);
+  bool a_ahead = issue_a(1);               // this wave's share of the next A stage is on its way
   int sa = 0, sx = 0;                      // slots of the stage being consumed
   while (task < p.n_tasks) {
     if (a_ahead) wait_copies<W::kAInstr>(); else wait_copies<0>();
     __builtin_amdgcn_s_barrier();          // all shares landed; the slots of the last stage are free
     if (ix_task < p.n_tasks) issue_x(sx ^ 1);
-    a_ahead = ia_task < p.n_tasks;
-    if (a_ahead) issue_a(sa == 0 ? 2 : sa - 1);
+    a_ahead = issue_a(sa == 0 ? 2 : sa - 1);
     const uint32_t aslot = ring + sa * W::kASlot;
-    {
+    if (kc >= comp_from && kc < comp_from + n_chunks) {
       uint32_t a[4], x[4];
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
@@ -662,7 +679,7 @@ __global__ __launch_bounds__(512, 2) void lm_head_wide_kernel(const GemmKernelAr
             acc[mb][nb] = mfma16(aop[mb][ks], xop[ks], acc[mb][nb]);
       }
     }
-    if (kc == n_chunks - 1) {
+    if (kc == n_stages - 1) {
       // ---- end of a task: 32 columns at a time through the A slot just consumed
       const int row0 = task * W::kRowsWg;
       float* zt = reinterpret_cast<float*>(smem + sa * W::kASlot);
@@ -699,7 +716,7 @@ __global__ __launch_bounds__(512, 2) void lm_head_wide_kernel(const GemmKernelAr
         }
       }
     }
-    if (++kc == n_chunks) {
+    if (++kc == n_stages) {
       kc = 0;
       task += gridDim.x;
     }
@@ -780,6 +797,14 @@ int lmh_block_rows(int n_cols, int64_t row_pitch_bytes, int n_rows, int num_cu) 
     return per_cu(64) * 5 < per_cu(128) * 4 ? 64 : 128;
   }
   return row_pitch_bytes % 8192 == 0 ? Geo<2, 1, 256>::kRowsWg : Geo<1, 1, 256>::kRowsWg;
+}
+
+// A matter of results, not of speed: other rows here are other 32-bit sums.  20480 was once the
+// number of candidates that the merge held.
+int lmh_order_rows(int n_cols, int64_t row_pitch_bytes, int n_rows, int topk) {
+  if (n_cols >= kWideCols) return 64;
+  const int64_t blocks64 = ((int64_t)n_rows + 63) / 64;
+  return blocks64 * topk > 20480 || row_pitch_bytes % 8192 == 0 ? 128 : 64;
 }
 
 template <int MODE>

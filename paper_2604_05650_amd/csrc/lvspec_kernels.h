@@ -108,6 +108,7 @@ struct GemmKernelArgs {
   int n_rb;                  // row blocks per batch
   int n_ds;                  // splits of the contraction dimension
   int kc;                    // 128-element chunks per split
+  int rot_shift;             // lm_head, narrow kernel: 1 = pairs of row blocks start at one chunk
   int n_tasks;               // B * n_rb * n_ds
   // relevance outputs
   float* dots;               // [B][n_ds][gamma][ld]
@@ -127,6 +128,8 @@ hipError_t launch_lmh_gemm(const GemmKernelArgs& a, int num_cu, hipStream_t stre
 int rel_rows_per_block(int big);   // 64, or 128 rows when there are plenty of row blocks
 // vocabulary rows per stage: 64 or 128
 int lmh_block_rows(int n_cols, int64_t row_pitch_bytes, int n_rows, int num_cu);
+// vocabulary rows whose chunks are added up in one order: 64 or 128
+int lmh_order_rows(int n_cols, int64_t row_pitch_bytes, int n_rows, int topk);
 // workgroups of an lm_head launch over n_tasks tasks = records per column it leaves
 int lmh_records(int n_cols, int n_tasks, int num_cu);
 

@@ -59,3 +59,32 @@ def test_equal_logits_take_the_lowest_ids(V, topk, step):
     assert outs["topk_ids"].cpu().tolist() == [[want] * 3]
     # the softmax of `len(best)` logits 64 and V - len(best) zeros
     np.testing.assert_allclose(outs["topk_probs"][0, 0, 0].item(), 1.0 / len(best), rtol=1e-5)
+
+
+@pytest.mark.parametrize("B,K,V,d,room", [
+    (9, 5, 65500, 384, 1.0),      # one group over both halves, 128-row tasks, three chunks
+    (13, 5, 65500, 1152, 1.0),    # two groups in a pass, 48 columns each at most
+    (8, 16, 65500, 128, 1.0),     # 128 columns, one chunk
+    (13, 5, 8192, 384, 1.0),      # 64-row tasks
+    (13, 5, 65500, 384, 0.6),     # a workspace that holds one group only
+    (26, 5, 65500, 384, 1.0),     # a full pass and a narrower one
+])
+def test_logits_do_not_depend_on_the_other_rows(B, K, V, d, room):
+    # every kernel adds up a vocabulary row's products in the same order: the same bits
+    import ctypes as C
+    from paper_2604_05650_amd import binding as L
+    h = t_bf16(synth.normal_bf16((613, B, K, d), (B, K, d), 1.0))
+    w = t_bf16(synth.normal_bf16((614, V, d), (V, d), 0.1))
+    draft = t_i32(np.zeros((B, K)))
+    rel = t_f32(np.zeros((B, K)))
+    outs = L.alloc_accept_outputs(B, K, V, 4, h.device, True)
+    args = L.loose_accept_args(h, w, draft, rel, 0, K, topk=4, loose_topk_gate=0, outs=outs)
+    full = L.raw().lvspec_loose_accept_workspace(C.byref(args))
+    ws = torch.empty((int(full * room),), dtype=torch.uint8, device=h.device)
+    args.workspace, args.workspace_bytes = ws.data_ptr(), ws.numel()
+    assert L.raw().lvspec_loose_accept(C.byref(args), torch.cuda.current_stream().cuda_stream) == L.OK
+    for b in (0, 1, B // 2, B - 1):
+        one = L.loose_accept(h[b:b + 1], w, draft[b:b + 1], rel[b:b + 1], 0, K, topk=4,
+                             return_logits=True)
+        assert torch.equal(one["logits"][0], outs["logits"][b])
+        assert torch.equal(one["topk_ids"][0], outs["topk_ids"][b])
