@@ -753,6 +753,303 @@ __global__ __launch_bounds__(256) void rel_merge_kernel(const RelFinalizeArgs p)
   if (lane == 0) *rel_out = (float)((double)tot / (double)kFixScale / (double)n_eff);
 }
 
+// ------------------------------------------------------------------------------------------
+constexpr int kRelKeepN = 128;
+
+// Two-kernel Top-N for 16 < N <= 128 and up to 65536 video rows.  One CU that reads a row's dot products
+// and norms alone is bound by its own requests in flight (rel_finalize_kernel: 230 KB at 14336 rows
+// in two splits), and the scores are needed once: so a workgroup per (slice, draft row) makes the
+// scores of 1024 (4096) video rows and leaves those that can be among the N largest, and one workgroup per
+// draft row selects among these.  At least N scores reach the N-th largest of the threads' maxima
+// (all scores, where there are fewer maxima than N).  The kept keys take the slice's places
+// of the cosine plane, their number the place of the slice's first dot product, which no one else
+// reads.  Scores rank like cosines and the N winners are the same, see rel_cand_kernel.
+// Both kernels are chains of latencies.  Per call against rel_finalize_kernel, N = 100: 14336 rows,
+// d = 5120, 5 draft rows (two splits) 42.6 -> 38.4 us; d = 1024: 4096 rows 18.7 -> 17.6, 63488 rows
+// 49.8 -> 34.4, 8 x 30000 rows with 8 draft rows each 100 -> 92; up to 1024 rows (one slice) 1 to 3 us
+// less as well.  N > 128: a slice would keep most of its scores, and selecting among more than are
+// held in LDS costs more than the one kernel (N = 1000, 14336 rows: 26.7 us there, 34.3 here).
+template <int NS, int M>
+__global__ __launch_bounds__(256) void rel_keep_kernel(const RelFinalizeArgs p) {
+  __shared__ uint32_t tmax[256];
+  __shared__ int kept;
+  const int part = blockIdx.x;
+  const int i = blockIdx.y;
+  const int b = blockIdx.z;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  int lv = p.l_v[b];
+  if (lv > p.lv_max) lv = (int)p.lv_max;
+  const int j0 = part * M * kRelSliceRows;
+  if (j0 >= lv) return;
+  float* dbase = const_cast<float*>(p.dots) + (((int64_t)b * p.n_ds) * p.gamma + i) * p.ld;
+  const bool pre = p.inv_norm != nullptr;   // prepared inverse norms instead of squared norms
+  const float* nbase = pre ? p.inv_norm + (int64_t)b * p.lv_max
+                           : p.nv2 + ((int64_t)b * p.n_ds) * p.ld;
+  const int64_t nstep = pre ? 0 : p.ld;
+  const int64_t dstep = (int64_t)p.gamma * p.ld;
+  uint32_t k[4 * M];
+#pragma unroll
+  for (int c = 0; c < M; ++c) {
+    const int jc = j0 + c * kRelSliceRows;
+    float dv[4][NS], nv[4][NS];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int j = jc + u * 256 + tid;
+      const uint32_t off = (uint32_t)(j < lv ? j : lv - 1) * 4u;
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const int sc = s < p.n_ds ? s : 0;
+        dv[u][s] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(dbase + sc * dstep) + off);
+        nv[u][s] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(nbase + sc * nstep) + off);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      float dot = dv[u][0], n2 = nv[u][0];
+#pragma unroll
+      for (int s = 1; s < NS; ++s) {
+        const float ws = s < p.n_ds ? 1.f : 0.f;
+        dot = __builtin_fmaf(dv[u][s], ws, dot);
+        n2 = __builtin_fmaf(nv[u][s], pre ? 0.f : ws, n2);
+      }
+      const float sc = dot * (pre ? n2 : __builtin_amdgcn_rsqf(fmaxf(n2, 1e-16f)));
+      k[4 * c + u] = jc + u * 256 + tid < lv ? order_key(sc) : 0u;
+    }
+  }
+  uint32_t most = k[0];
+#pragma unroll
+  for (int u = 1; u < 4 * M; ++u) most = max(most, k[u]);
+  tmax[tid] = most;
+  if (tid == 0) kept = 0;
+  __syncthreads();
+  uint32_t m4[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) m4[u] = tmax[64 * u + lane];
+  const uint32_t bound = kth_bound<4>(m4, p.top_n);
+  unsigned long long mask[4 * M];
+  int n = 0;
+#pragma unroll
+  for (int u = 0; u < 4 * M; ++u) {
+    mask[u] = __ballot(k[u] >= bound);       // bound >= 1: no row past the last
+    n += __popcll(mask[u]);
+  }
+  int at = 0;
+  if (lane == 0) at = atomicAdd(&kept, n);
+  at = __builtin_amdgcn_readfirstlane(at);
+  uint32_t* out = reinterpret_cast<uint32_t*>(p.cosbuf + ((int64_t)b * p.gamma + i) * p.ld) + j0;
+#pragma unroll
+  for (int u = 0; u < 4 * M; ++u) {
+    if ((mask[u] >> lane) & 1ull) out[at + __popcll(mask[u] & ((1ull << lane) - 1ull))] = k[u];
+    at += __popcll(mask[u]);
+  }
+  __syncthreads();                           // every dot product of the slice has been read
+  if (tid == 0) dbase[j0] = __builtin_bit_cast(float, kept);
+}
+
+// As radix_select, for keys in LDS between lo and hi: the digits start at the first bit in which keys
+// differ, one wave adds a histogram up over the DPP network, and the search ends when all keys of
+// the digit it is down to are among the n largest (after two digits as a rule): the key returned is
+// then the largest one below, with none of its copies needed.  hi, lo: the same in all threads.
+LVS_DEV uint32_t select_in_lds(const uint32_t* keys, int count, int n, uint32_t hi, uint32_t lo,
+                               SelectScratch& sc, uint32_t* need_eq) {
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  uint32_t* hist = &sc.hist[0][0];                 // four histograms, by wave
+  if (hi == lo) {
+    *need_eq = (uint32_t)n;
+    return hi;
+  }
+  const int top = 31 - __clz((int)(hi ^ lo));
+  uint32_t mask = top == 31 ? 0u : 0xffffffffu << (top + 1);   // bits that are settled
+  uint32_t prefix = hi & mask;
+  uint32_t rem = (uint32_t)n;
+  int shift = top > 7 ? top - 7 : 0;
+  while (true) {
+    hist[tid] = 0u;
+    __syncthreads();
+    for (int idx = tid; idx < count; idx += kFinThreads) {
+      const uint32_t k = keys[idx];
+      if ((k & mask) == prefix)
+        atomicAdd(&hist[((tid >> 6) & 3) * 256 + ((k >> shift) & 0xffu)], 1u);
+    }
+    __syncthreads();
+    if (tid < 64) {
+      // lane l: digits 255 - 4 l .. 252 - 4 l
+      uint32_t own[4], sum = 0u;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int d = 255 - 4 * lane - u;
+        own[u] = (hist[d] + hist[256 + d]) + (hist[512 + d] + hist[768 + d]);
+        sum += own[u];
+      }
+      uint32_t upto = sum;
+      upto += dpp_move<0x111, 0xf>(0u, upto);    // inclusive sums: row shifts, row broadcasts
+      upto += dpp_move<0x112, 0xf>(0u, upto);
+      upto += dpp_move<0x114, 0xf>(0u, upto);
+      upto += dpp_move<0x118, 0xf>(0u, upto);
+      upto += dpp_move<0x142, 0xa>(0u, upto);
+      upto += dpp_move<0x143, 0xc>(0u, upto);
+      uint32_t above = upto - sum;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (above < rem && above + own[u] >= rem) {
+          sc.prefix = prefix | ((uint32_t)(255 - 4 * lane - u) << shift);
+          sc.remaining = rem - above;              // keys of this digit still needed
+          sc.wave_tot[0] = own[u];                 // keys of this digit
+        }
+        above += own[u];
+      }
+    }
+    __syncthreads();
+    prefix = sc.prefix;
+    rem = sc.remaining;
+    const uint32_t in_digit = sc.wave_tot[0];
+    if (shift == 0) {
+      *need_eq = rem;
+      return prefix;
+    }
+    if (rem == in_digit) {
+      *need_eq = 0u;
+      return prefix != 0u ? prefix - 1u : 0u;      // (keys are above 0)
+    }
+    mask = 0xffffffffu << shift;
+    shift = shift > 8 ? shift - 8 : 0;
+  }
+}
+
+// Slices of `rows` video rows.
+__global__ __launch_bounds__(kFinThreads) void rel_take_kernel(const RelFinalizeArgs p, int rows) {
+  constexpr int kWaves = kFinThreads / 64;
+  constexpr int kOwn = kRelMaxParts / kWaves;   // slices of a wave
+  constexpr int kAtOnce = 4;                    // keys per lane and slice asked for together
+  __shared__ float red[kWaves];
+  __shared__ SelectScratch sc;
+  __shared__ uint32_t sm_hi[kWaves], sm_nlo[kWaves];
+  __shared__ uint32_t cand[kCandCap];
+  __shared__ int sm_count[kRelMaxParts];
+  __shared__ long long fix_part[kWaves];
+  const int i = blockIdx.x;
+  const int b = blockIdx.y;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int lv = p.l_v[b];
+  if (lv > p.lv_max) lv = (int)p.lv_max;
+  float* rel_out = p.relevance + (int64_t)b * p.gamma + i;
+  if (lv <= 0) {
+    if (tid == 0) *rel_out = 0.f;
+    return;
+  }
+  const int n_eff = p.top_n < lv ? p.top_n : lv;
+  const int parts = (lv + rows - 1) / rows;      // at most kRelMaxParts
+  const float* dbase = p.dots + (((int64_t)b * p.n_ds) * p.gamma + i) * p.ld;
+  const uint32_t* keys = reinterpret_cast<const uint32_t*>(p.cosbuf + ((int64_t)b * p.gamma + i) * p.ld);
+  // lane l: number of keys of slice l
+  int count = __builtin_bit_cast(int, dbase[(int64_t)(lane < parts ? lane : 0) * rows]);
+  // |h_d row|^2 as in rel_finalize_kernel, while the counts are on their way
+  const uint16_t* hd = p.h_d + (int64_t)b * p.hd_sb + (int64_t)i * p.hd_sg;
+  float part = 0.f;
+  for (int t = tid * 8; t < p.d; t += kFinThreads * 8) {
+    const u32x4 w = *reinterpret_cast<const u32x4*>(hd + t);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float lo = __builtin_bit_cast(float, w[e] << 16);
+      const float hi = __builtin_bit_cast(float, w[e] & 0xffff0000u);
+      part = __builtin_fmaf(lo, lo, part);
+      part = __builtin_fmaf(hi, hi, part);
+    }
+  }
+  count = lane < parts ? count : 0;
+  int end = count;                               // keys of slices 0 .. lane
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int o = __shfl_up(end, off, 64);
+    if (lane >= off) end += o;
+  }
+  const int total = __builtin_amdgcn_readlane(end, 63);
+  if (wave == 0) sm_count[lane] = count;
+  if (total <= kCandCap) {
+    uint32_t key[kOwn][kAtOnce];
+    uint32_t hi = 0u, nlo = 0u;      // largest key and largest complement
+#pragma unroll
+    for (int o = 0; o < kOwn; ++o) {
+      const int s = wave + kWaves * o;
+      const int c = __builtin_amdgcn_readlane(count, s);
+#pragma unroll
+      for (int u = 0; u < kAtOnce; ++u)
+        if (64 * u + lane < c) key[o][u] = keys[s * rows + 64 * u + lane];
+    }
+#pragma unroll
+    for (int o = 0; o < kOwn; ++o) {
+      const int s = wave + kWaves * o;
+      const int c = __builtin_amdgcn_readlane(count, s);
+      const int at = __builtin_amdgcn_readlane(end, s) - c;
+#pragma unroll
+      for (int u = 0; u < kAtOnce; ++u)
+        if (64 * u + lane < c) {
+          cand[at + 64 * u + lane] = key[o][u];
+          hi = max(hi, key[o][u]);
+          nlo = max(nlo, ~key[o][u]);
+        }
+      for (int t = 64 * kAtOnce + lane; t < c; t += 64) {
+        const uint32_t k = keys[s * rows + t];
+        cand[at + t] = k;
+        hi = max(hi, k);
+        nlo = max(nlo, ~k);
+      }
+    }
+    hi = wave_max_u32(hi);
+    nlo = wave_max_u32(nlo);
+    if (lane == 0) {
+      sm_hi[wave] = hi;
+      sm_nlo[wave] = nlo;
+    }
+  }
+  part = wave_sum(part);
+  if (lane == 0) red[wave] = part;
+  __syncthreads();
+  float nd2 = 0.f;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) nd2 += red[w];
+  const float inv_nd = 1.0f / fmaxf(sqrtf(nd2), 1e-8f);
+  uint32_t need_eq, tkey;
+  long long fix = 0;     // sum of the values above the n-th largest, exact in 2^-40 units
+  auto add = [&](uint32_t k) {
+    if (k > tkey) fix += (long long)(key_value(k) * inv_nd * kFixScale);
+  };
+  if (total <= kCandCap) {
+    uint32_t hi = 0u, nlo = 0u;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      hi = max(hi, sm_hi[w]);
+      nlo = max(nlo, sm_nlo[w]);
+    }
+    tkey = select_in_lds(cand, total, n_eff, hi, ~nlo, sc, &need_eq);
+    for (int idx = tid; idx < total; idx += kFinThreads) add(cand[idx]);
+  } else {
+    // (many equal values at the bounds) over the kept keys where they are
+    const int shift = 31 - __clz(rows);            // rows: a power of two
+    const int all = (parts - 1) * rows + sm_count[parts - 1];
+    auto key_at = [&](int idx) {
+      return (idx & (rows - 1)) < sm_count[idx >> shift] ? keys[idx] : 0u;
+    };
+    tkey = radix_select(all, n_eff, key_at, sc, &need_eq);
+    for (int idx = tid; idx < all; idx += kFinThreads) add(key_at(idx));
+  }
+  // integer addition is associative: any reduction order gives the same bits
+#pragma unroll
+  for (int sft = 1; sft < 64; sft <<= 1) fix += __shfl_xor(fix, sft, 64);
+  if (lane == 0) fix_part[wave] = fix;
+  __syncthreads();
+  if (tid == 0) {
+    long long tot = 0;
+    for (int w = 0; w < kWaves; ++w) tot += fix_part[w];
+    tot += (long long)need_eq * (long long)(key_value(tkey) * inv_nd * kFixScale);
+    *rel_out = (float)((double)tot / (double)kFixScale / (double)n_eff);
+  }
+}
+
 }  // namespace
 
 hipError_t launch_rel_finalize(const RelFinalizeArgs& a, hipStream_t stream) {
@@ -774,6 +1071,28 @@ hipError_t launch_rel_finalize(const RelFinalizeArgs& a, hipStream_t stream) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(rel_merge_kernel, dim3(a.gamma, a.B), dim3(256), 0, stream, a);
+    return hipGetLastError();
+  }
+  if (a.top_n > kSmallN && a.top_n <= kRelKeepN && a.lv_max >= 1 &&
+      a.lv_max <= 16 * 4 * (int64_t)kRelSliceRows) {
+    // longer slices where the kept keys of short ones (about 1.3 N each) would not fit
+    const bool longer = a.lv_max > 20 * kRelSliceRows;
+    const int rows = longer ? 4 * kRelSliceRows : kRelSliceRows;
+    const dim3 grid((unsigned)((a.lv_max + rows - 1) / rows), a.gamma, a.B);
+#define LVS_KEEP(NS)                                                                           \
+  if (longer) hipLaunchKernelGGL((rel_keep_kernel<NS, 4>), grid, dim3(256), 0, stream, a);     \
+  else hipLaunchKernelGGL((rel_keep_kernel<NS, 1>), grid, dim3(256), 0, stream, a)
+    if (a.n_ds == 1) {
+      LVS_KEEP(1);
+    } else if (a.n_ds == 2) {
+      LVS_KEEP(2);
+    } else {
+      LVS_KEEP(8);
+    }
+#undef LVS_KEEP
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(rel_take_kernel, dim3(a.gamma, a.B), dim3(kFinThreads), 0, stream, a, rows);
     return hipGetLastError();
   }
   if (a.top_n <= kSmallN)

@@ -237,3 +237,30 @@ def test_prepared_full_size(name):
     o = oracle.visual_relevance(hd[sel], hv[sel], h["l_v"][sel], cfg.top_n)
     e = assert_scalars_close(g[sel], o, f"prepared relevance {name}")
     print(f"[rel] prepared {name} ok: {e:.2e}", flush=True)
+
+
+@pytest.mark.parametrize("lv,d,N,kind", [
+    (1024, 128, 17, "random"),       # one full slice
+    (1025, 128, 100, "random"),      # a slice of one row
+    (3000, 640, 128, "random"),      # the largest N, splits of d
+    (3000, 128, 129, "random"),      # the one-kernel selection
+    (120, 384, 128, "random"),       # fewer scores than N
+    (14336, 512, 100, "sorted"),     # all winners in one slice
+    (20000, 128, 40, "equal"),       # every score is a winner, more of them than are held
+    (3000, 128, 40, "equal"),        # ... and as many as are held
+    (20480, 128, 128, "random"),     # the longest row of short slices
+    (20481, 128, 128, "random"),     # the shortest of long ones
+    (65536, 128, 100, "random"),     # the most slices
+])
+def test_wide_top_n_slices(lv, d, N, kind):
+    gamma = 3
+    h_d = synth.normal_bf16((205, lv, N, 0), (2, gamma, d), 1.0)
+    if kind == "equal":
+        h_v = np.broadcast_to(synth.normal_bf16((205, lv, N, 1), (2, 1, d), 1.0), (2, lv, d)).copy()
+    else:
+        h_v = synth.normal_bf16((205, lv, N, 1), (2, lv, d), 1.0)
+    if kind == "sorted":
+        dots = synth.bf16_bits_to_f32(h_v[0]) @ synth.bf16_bits_to_f32(h_d[0, 0])
+        h_v[0] = h_v[0][np.argsort(-dots)]
+    # the second sequence ends inside a slice, and there are slices past its end
+    _check(h_d, h_v, [lv, max(1, lv * 2 // 5)], N, f"wide lv{lv} d{d} N{N} {kind}")
