@@ -259,7 +259,7 @@ LVS_DEV void issue_part(const uint8_t* __restrict__ base, int64_t row_stride_byt
 }
 
 // Tiles t_begin .. t_end - 1 of one unit, by the whole workgroup: stream, merge, write the partial
-// record that record() points to.
+// record that record(sequence and kv head) points to.
 // RS = 1: four waves, each streaming its own tiles through a private ring and holding all
 //         16*NBW query rows (no barrier in the main loop).
 // RS > 1: 4*RS waves; the RS waves of a stream share one ring and one copy of every K/V tile,
@@ -386,6 +386,7 @@ LVS_DEV void attn_segment(const Args& p, uint8_t* smem, int lane, int wave, int 
   }
   LVS_TRACE(3);
 
+  const int bh = b * p.Hkv + kvh;
   WaveState<NB> st;
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
@@ -572,7 +573,7 @@ LVS_DEV void attn_segment(const Args& p, uint8_t* smem, int lane, int wave, int 
   }
   __syncthreads();
   LVS_TRACE(7);
-  float* part = record();
+  float* part = record(bh);
   // only the rows that exist are written (the combine kernel reads no others)
   const int rows_here = p.R - rc * RPAD < RPAD ? p.R - rc * RPAD : RPAD;
   for (int row = threadIdx.x; row < rows_here; row += NT) {
@@ -702,9 +703,9 @@ __global__ __launch_bounds__(256 * RS, 1) void attn_split_kernel(
   const int t_begin = split * t_base + (split < t_rem ? split : t_rem);
   const int t_end = t_begin + t_base + (split < t_rem ? 1 : 0);
   attn_segment<RS, NBW>(p, smem, lane, wave, b, kvh, rc, L, gamma, n_tiles, t_begin, t_end, kbase,
-                        vbase, rsb, [&] {
-                          const size_t unit_rec = ((size_t)(b * p.Hkv + kvh) * p.n_rc + rc) * n_split;
-                          return p.ws + (unit_rec + split) * (size_t)(16 * NBW * RS * 131);
+                        vbase, rsb, [&](int bh) {
+                          return p.ws + (((size_t)bh * p.n_rc + rc) * n_split + split) *
+                                            (size_t)(16 * NBW * RS * 131);
                         });
   LVS_TRACE(8);
   LVS_TRACE_END;
@@ -860,7 +861,7 @@ __global__ __launch_bounds__(256 * RS, 1) void attn_flat_kernel(
       attn_segment<RS, NBW>(
           args, smem, ln, wv, b, kvh, rc, L, sh.gamma, (int)n_tiles, (int)t0, (int)t1,
           reinterpret_cast<const uint8_t*>(k0) + base, reinterpret_cast<const uint8_t*>(v0) + base,
-          rsb, [&] {
+          rsb, [&](int) {
             const size_t rec = (size_t)rc * (sh.n_pos + sh.B * sh.Hkv) + pos + b * sh.Hkv + kvh;
             return args.ws + rec * (size_t)(16 * NBW * RS * 131);
           });
