@@ -311,7 +311,7 @@ typedef struct {
   int32_t attn_splits;           /* key-range splits per (sequence, kv head, row chunk) */
   int32_t rel_splits;            /* splits of the hidden dimension */
   int32_t rel_stage_bytes;       /* bytes of a video row per pipeline stage: 256 or 512 */
-  int32_t rel_slices;            /* slices of the two-kernel Top-N; 0 = single-kernel selection */
+  int32_t rel_slices;            /* slices of the Top-N by lists (N <= 16); 0 = other selections */
   int32_t rel_slice_rows;        /* video rows per slice */
   int32_t acc_rows_per_task;     /* vocabulary rows per lm_head task: 64 or 128 (a stage of the
                                     pass holds half of one, one, or two); the rows of a task

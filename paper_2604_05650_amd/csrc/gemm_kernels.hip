@@ -520,6 +520,8 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(const GemmKernelArg
 // first: it joins in at the task's second stage and ends one stage behind, while the X chunk of
 // a stage serves both (n_chunks + 1 stages; with one start for both blocks the logits are other
 // 32-bit sums, and tokens that tie within 6e-6 change places: 2 of 576 ids at k = 16).
+// 96 rows, d = 5120, V = 152064: 689 us in two passes of 48 columns, 335 here (328 without the
+// extra stage).
 template <int MB, int NB2>
 struct Wide {
   static constexpr int kRowsWg = 64 * MB;

@@ -153,7 +153,7 @@ struct RelFinalizeArgs {
 constexpr int kRelSliceRows = 1024;   // video rows the candidate kernel takes at a time (four per thread)
 constexpr int kRelMaxParts = 64;      // slices the merge kernel can take
 constexpr int kRelMaxChunks = 16;     // 1024-row chunks per slice at most (lv_max <= 1048576)
-constexpr int kRelSmallN = 16;        // Top-N sizes served by the two-kernel path
+constexpr int kRelSmallN = 16;        // Top-N sizes served by per-slice lists
 hipError_t launch_rel_finalize(const RelFinalizeArgs& a, hipStream_t stream);
 
 // ---------------------------------------------------------------- prefill-side H_V preparation
