@@ -240,14 +240,14 @@ def test_prepared_full_size(name):
 
 
 @pytest.mark.parametrize("lv,d,N,kind", [
-    (1024, 128, 17, "random"),       # one full slice
-    (1025, 128, 100, "random"),      # a slice of one row
-    (3000, 640, 128, "random"),      # the largest N, splits of d
-    (3000, 128, 129, "random"),      # the one-kernel selection
-    (120, 384, 128, "random"),       # fewer scores than N
+    (4096, 128, 17, "random"),       # the longest row of the one kernel
+    (4097, 128, 17, "random"),       # a slice of one row
+    (4097, 128, 100, "short"),       # a second sequence of fewer scores than N
+    (5000, 640, 128, "random"),      # the largest N, splits of d
+    (5000, 128, 129, "random"),      # the one-kernel selection
     (14336, 512, 100, "sorted"),     # all winners in one slice
     (20000, 128, 40, "equal"),       # every score is a winner, more of them than are held
-    (3000, 128, 40, "equal"),        # ... and as many as are held
+    (5000, 128, 40, "equal"),        # ... and, in the second sequence, as many as are held
     (20480, 128, 128, "random"),     # the longest row of short slices
     (20481, 128, 128, "random"),     # the shortest of long ones
     (65536, 128, 100, "random"),     # the most slices
@@ -263,4 +263,4 @@ def test_wide_top_n_slices(lv, d, N, kind):
         dots = synth.bf16_bits_to_f32(h_v[0]) @ synth.bf16_bits_to_f32(h_d[0, 0])
         h_v[0] = h_v[0][np.argsort(-dots)]
     # the second sequence ends inside a slice, and there are slices past its end
-    _check(h_d, h_v, [lv, max(1, lv * 2 // 5)], N, f"wide lv{lv} d{d} N{N} {kind}")
+    _check(h_d, h_v, [lv, 50 if kind == "short" else lv * 2 // 5], N, f"wide lv{lv} d{d} N{N} {kind}")
