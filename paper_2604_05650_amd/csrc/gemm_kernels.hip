@@ -281,7 +281,12 @@ LVS_DEV void column_emit(const ColumnState& c, const GemmKernelArgs& p, int col,
   const float s = wave_sum(c.s * f);
   const int64_t rec = (int64_t)col * p.n_rec + blockIdx.x;
   if (lane == 0) {
-    p.stats[rec * 2] = mx;
+    // The merge ranks the records by this maximum.  The maximum of floats passes over NaN, the
+    // candidates do not: a record whose best candidate is NaN (there is nothing else in it, or
+    // the NaN ranks above the rest) says so, or the merge would not look at its candidates.
+    const uint32_t best = (uint32_t)(c.top >> 32);
+    const float v = key_value(best);
+    p.stats[rec * 2] = best != 0u && v != v ? v : mx;
     p.stats[rec * 2 + 1] = s;
   }
   if (p.stats_z != nullptr) {

@@ -88,3 +88,43 @@ def test_logits_do_not_depend_on_the_other_rows(B, K, V, d, room):
                              return_logits=True)
         assert torch.equal(one["logits"][0], outs["logits"][b])
         assert torch.equal(one["topk_ids"][0], outs["topk_ids"][b])
+
+
+@pytest.mark.parametrize("B,K,V,topk", [(1, 3, 33000, 4), (1, 3, 33000, 16), (7, 5, 33000, 4),
+                                        (17, 5, 9000, 16)])
+def test_nan_logits_keep_their_places(B, K, V, topk):
+    # NaN ranks as its bits do: equal ones by id, and behind every number as the products leave it
+    # (sign bit set).  A row of nothing but NaN has token 0, as argmax gives; the rows beside it
+    # have the bits that they have without it.
+    from paper_2604_05650_amd import binding as L
+    d = 256
+    h = t_bf16(synth.normal_bf16((615, B, K, 0), (B, K, d), 1.0))
+    w = t_bf16(synth.normal_bf16((615, V, 1), (V, d), 0.1))
+    draft, rel = t_i32(np.zeros((B, K))), t_f32(np.zeros((B, K)))
+
+    def call(h, w):
+        outs = L.loose_accept(h, w, draft, rel, 0, 0, topk=topk, return_entropy=True)
+        torch.cuda.synchronize()
+        return {k: v.cpu() for k, v in outs.items()}
+
+    clean = call(h, w)
+    bad = h.clone()
+    bad[-1, 1] = float("nan")
+    outs = call(bad, w)
+    assert outs["topk_ids"][-1, 1].tolist() == list(range(topk))
+    assert outs["target_ids"][-1, 1] == 0 and torch.isnan(outs["topk_probs"][-1, 1]).all()
+    keep = torch.ones((B, K), dtype=torch.bool)
+    keep[-1, 1] = False
+    for name in ("target_ids", "topk_ids", "topk_probs", "entropy"):
+        assert torch.equal(outs[name][keep], clean[name][keep]), name
+    # three rows of lm_head that are not NaN: they come first, then the lowest ids
+    left = [5, V // 2, V - 2]
+    holes = torch.full_like(w, float("nan"))
+    holes[left] = w[left]
+    outs = call(h, holes)
+    logits = (h.double() @ w[left].double().T).cpu()
+    for b in (0, B - 1):
+        for i in range(K):
+            order = [left[j] for j in torch.argsort(logits[b, i], descending=True)]
+            rest = [j for j in range(topk) if j not in left]
+            assert outs["topk_ids"][b, i].tolist() == (order + rest)[:topk]
