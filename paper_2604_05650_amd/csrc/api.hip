@@ -86,14 +86,15 @@ int plan_attn(const lvspec_attn_args* a, AttnPlan* pl) {
   pl->n_split = (int)ns;
   const size_t rec_bytes = (size_t)pl->rpad * 131 * sizeof(float);
   pl->split_bytes = (size_t)units * (size_t)ns * rec_bytes;
-  // Short calls of few units keep equal splits: below 12 tiles per workgroup an idle CU costs less
-  // than the second kernel's wait for the lengths (2 x 2048 keys, 40 / 8 heads: 13.0 us against 14.1,
-  // 4 x 2048: 14.4 against 15.4; but 16 x 512, two workgroups per unit: 19.5 against 15.1).
+  // A batch that the caller says is short keeps attn_split_kernel: its combine kernel does not wait
+  // for the lengths (2 x 2048 keys, 40 / 8 heads: 13.0 us against 14.1, 4 x 2048: 14.4 against 15.4;
+  // but 16 x 512, two workgroups per unit: 19.5 against 15.1).  By cap where there is no max_kv_len;
+  // the lengths themselves then ask for the same cut, see flat_equal_splits.
   // Shapes that the static scratch serves with equal splits stay within it: fewer stretches leave a
   // few CUs idle (one in sixteen for 256 units of 64 rows).
   pl->flat_pos = lvspec::attn_flat_positions(a->B, a->Hkv, pl->rpad, pl->n_rc, a->cap,
                                              num_compute_units());
-  if (ns > 2 && n_tiles < 12 * ns) pl->flat_pos = 0;
+  if ((ns > 2 && n_tiles < lvspec::attn_short_tiles(a->B) * ns) || ns > 128) pl->flat_pos = 0;
   auto flat_bytes = [&] {
     return ((size_t)pl->flat_pos + (size_t)a->B * a->Hkv) * (size_t)pl->n_rc * rec_bytes;
   };
@@ -392,7 +393,7 @@ int enqueue_attn(const lvspec_attn_args* a, const AttnPlan& pl, void* workspace,
   // splits is served by those.  The choice never looks at the lengths: results are the same
   // bits whether the host knows them or not.
   constexpr int64_t kMaxStride = (int64_t)8 << 32;     // travels as a 32-bit number of 8 elements
-  k.flat_pos = have >= pl.flat_bytes && a->kv_sb < kMaxStride && a->kv_sh < kMaxStride &&
+  k.flat_pos = have >= pl.ws_bytes && a->kv_sb < kMaxStride && a->kv_sh < kMaxStride &&
                        a->kv_sl < kMaxStride ? pl.flat_pos : 0;
   for (int i = 0; i < 32; ++i)
     k.draft_mask[i] = a->draft_mask ? (i < a->gamma ? a->draft_mask[i] : 0u)

@@ -742,10 +742,13 @@ LVS_DEV FlatShape flat_shape(uint32_t packed) {
                    (int)((packed >> 22) & 63u) * 8};
 }
 
+// Sequence `lane` of the batch (nothing past the last).
+struct SeqKeys {
+  int L;              // keys in the cache
+  uint32_t tiles;     // of one kv head
+};
+
 struct FlatLine {
-  int L;              // keys of sequence `lane` (0 past the last)
-  uint32_t tiles;     // of one kv head of that sequence
-  uint32_t pad;       // empty places behind a unit
   uint32_t end;       // places of all kv heads of sequences 0 .. lane
   uint32_t total;     // of the whole line, below 2^31 / n_pos (the launch checks it)
   uint32_t n_pos;     // stretches in use
@@ -760,13 +763,9 @@ LVS_DEV uint32_t line_div(uint32_t x, uint32_t n) {
   return rest < 0 ? q - 1 : rest >= (int)n ? q + 1 : q;
 }
 
-// Every lane of every wave calls this; B <= 64.  `whole`: stretches to use for equal lengths, a
-// multiple of the units (0: no such number near n_pos); no stretch then lies over two units.
-template <int PAD>
-LVS_DEV FlatLine flat_line(const FlatShape& sh, uint32_t packed, uint32_t whole, uint32_t x0,
-                           uint32_t x1, uint32_t x2, uint32_t x3, uint32_t x4,
-                           const AttnKernelArgs& p, int lane) {
-  FlatLine f;
+// Every lane of every wave calls these; B <= 64.
+LVS_DEV SeqKeys flat_keys(const FlatShape& sh, uint32_t packed, uint32_t x0, uint32_t x1,
+                          uint32_t x2, uint32_t x3, uint32_t x4, const AttnKernelArgs& p, int lane) {
   int L = 0;
   const uint32_t mode = (packed >> 28) & 3u;
   if (mode == 0) {
@@ -779,12 +778,33 @@ LVS_DEV FlatLine flat_line(const FlatShape& sh, uint32_t packed, uint32_t whole,
   } else {
     L = p.len_host[lane & 31];
   }
-  f.L = lane < sh.B ? L : 0;
-  f.tiles = lane < sh.B ? (uint32_t)(L + sh.gamma + kTileKeys - 1) / kTileKeys : 0u;
-  const uint32_t one = (uint32_t)__builtin_amdgcn_readfirstlane((int)f.tiles);
-  const bool equal = whole != 0u && __ballot(lane < sh.B && f.tiles != one) == 0ull;
-  f.pad = equal ? 0u : PAD;
-  uint32_t sum = lane < sh.B ? (f.tiles + f.pad) * (uint32_t)sh.Hkv : 0u;
+  SeqKeys k;
+  k.L = lane < sh.B ? L : 0;
+  k.tiles = lane < sh.B ? (uint32_t)(L + sh.gamma + kTileKeys - 1) / kTileKeys : 0u;
+  return k;
+}
+
+// Whether every unit is cut into the `ns` equal splits of attn_split_kernel instead; splits: bits 0-6
+// ns - 1, bit 7 set where units * ns workgroups fill the chip.
+//   Equal lengths: the line would end at the same time and only shift its cuts against the units.
+//   Short sequences: a stretch over parts of two units costs the start of a unit twice, which
+//   counts where a workgroup's share is a few rounds (in a cache of 32768 rows, equal splits against
+//   the line: 2 x 256 keys, 40 / 8 heads 9.2 us, 13.0; 4 x 1024, 28 / 4 heads 10.9, 15.5).  With one
+//   or two splits per unit the line is the faster one there, too (16 x 256, 40 / 8 heads: 16.8 us
+//   in equal splits, 12.4).  A caller whose max_kv_len says as much gets attn_split_kernel, whose
+//   combine kernel does not wait for the lengths (4 x 1024, 8 / 2 heads 8.8 us, here 9.3).
+LVS_DEV bool flat_equal_splits(const FlatShape& sh, const SeqKeys& k, uint32_t splits, int lane) {
+  const uint32_t ns = (splits & 127u) + 1;
+  const uint32_t one = (uint32_t)__builtin_amdgcn_readfirstlane((int)k.tiles);
+  const bool equal = __ballot(lane < sh.B && k.tiles != one) == 0ull;
+  const bool is_long = __ballot(k.tiles >= (uint32_t)attn_short_tiles(sh.B) * ns) != 0ull;
+  return (equal && (splits & 128u) != 0u) || (ns > 2 && !is_long);
+}
+
+template <int PAD>
+LVS_DEV FlatLine flat_line(const FlatShape& sh, const SeqKeys& k, int lane) {
+  FlatLine f;
+  uint32_t sum = lane < sh.B ? (k.tiles + PAD) * (uint32_t)sh.Hkv : 0u;
   sum += dpp_move<0x111, 0xf>(0u, sum);    // inclusive sums: row shifts by 1, 2, 4, 8 ...
   sum += dpp_move<0x112, 0xf>(0u, sum);
   sum += dpp_move<0x114, 0xf>(0u, sum);
@@ -793,9 +813,8 @@ LVS_DEV FlatLine flat_line(const FlatShape& sh, uint32_t packed, uint32_t whole,
   sum += dpp_move<0x143, 0xc>(0u, sum);
   f.end = sum;
   f.total = (uint32_t)__builtin_amdgcn_readlane((int)sum, 63);
-  const uint32_t want = equal ? whole : (uint32_t)sh.n_pos;
   const uint32_t most = f.total / kFlatMinPlaces;
-  f.n_pos = most < 1u ? 1u : most < want ? most : want;
+  f.n_pos = most < 1u ? 1u : most < (uint32_t)sh.n_pos ? most : (uint32_t)sh.n_pos;
   return f;
 }
 
@@ -816,35 +835,71 @@ constexpr int kFlatArgsOffset = 56;
 static_assert(alignof(AttnKernelArgs) == 8, "the structure follows the leading arguments directly");
 
 // A workgroup per (stretch, row chunk); the row chunks of a stretch share an XCD's L2.  Strides in
-// units of eight elements; rc_mul_whole: ceil(65536 / n_rc), and `whole` of flat_line from bit 17.
+// units of eight elements; rc_mul_splits: ceil(32768 / n_rc), and `splits` from bit 16.
 template <int RS, int NBW>
 __global__ __launch_bounds__(256 * RS, 1) void attn_flat_kernel(
     const uint16_t* k0, const uint16_t* v0, uint32_t sb8, uint32_t sh8, uint32_t sl8,
     uint32_t packed, uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3, uint32_t x4,
-    uint32_t rc_mul_whole, const AttnKernelArgs p) {
+    uint32_t rc_mul_splits, const AttnKernelArgs p) {
   extern __shared__ __align__(16) uint8_t smem[];
-  constexpr int PAD = flat_pad(16 * NBW * RS);
+  constexpr uint32_t PAD = flat_pad(16 * NBW * RS);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const FlatShape sh = flat_shape(packed);
-  const FlatLine f = flat_line<PAD>(sh, packed, rc_mul_whole >> 17, x0, x1, x2, x3, x4, p, lane);
-  const uint32_t j = blockIdx.x >> 3;
-  const uint32_t j_pos = j * (rc_mul_whole & 0x1ffffu) >> 16;
-  const int rc = (int)(j - j_pos * (uint32_t)sh.n_rc);
-  const uint32_t per_xcd = (f.n_pos + 7) >> 3;      // neighbours on the line on one XCD
-  const uint32_t pos = (blockIdx.x & 7u) * per_xcd + j_pos;
-  if (j_pos >= per_xcd || pos >= f.n_pos) return;
-  const uint32_t quot = line_div(f.total, f.n_pos);
-  uint32_t v = flat_begin(f, pos, quot);
-  const uint32_t v_end = flat_begin(f, pos + 1, quot);
-  int b = __popcll(__ballot(f.end <= v));      // v < total: a sequence that exists
-  uint32_t n_tiles = read_lane(f.tiles, b);
-  const uint32_t off = v - (read_lane(f.end, b) - (n_tiles + f.pad) * (uint32_t)sh.Hkv);
-  int kvh = (int)line_div(off, n_tiles + f.pad);
-  uint32_t t0 = off - (uint32_t)kvh * (n_tiles + f.pad);
+  const SeqKeys keys = flat_keys(sh, packed, x0, x1, x2, x3, x4, p, lane);
+  const uint32_t units = (uint32_t)(sh.B * sh.Hkv);
+  // what this workgroup takes: places v .. v_end - 1 of the line, from tile t0 of unit (b, kvh) on;
+  // the record of its part of a unit is number rec0 + unit
+  int b, kvh, rc;
+  uint32_t n_tiles, t0, v, v_end, rec0;
+  if (flat_equal_splits(sh, keys, rc_mul_splits >> 16, lane)) {
+    const uint32_t ns = ((rc_mul_splits >> 16) & 127u) + 1;
+    const uint32_t unit_rc = units * (uint32_t)sh.n_rc;      // order and place as attn_split_kernel
+    uint32_t unit, split;
+    if (unit_rc % 8 == 0) {
+      const uint32_t j = blockIdx.x >> 3;
+      const uint32_t u8 = line_div(j, ns);
+      split = j - u8 * ns;
+      unit = u8 * 8 + (blockIdx.x & 7u);
+    } else {
+      unit = line_div(blockIdx.x, ns);
+      split = blockIdx.x - unit * ns;
+    }
+    if (unit >= unit_rc) return;
+    const uint32_t z = line_div(unit, (uint32_t)sh.Hkv);
+    kvh = (int)(unit - z * (uint32_t)sh.Hkv);
+    b = (int)line_div(z, (uint32_t)sh.n_rc);
+    rc = (int)(z - (uint32_t)b * (uint32_t)sh.n_rc);
+    n_tiles = read_lane(keys.tiles, b);
+    const uint32_t each = line_div(n_tiles, ns);
+    const uint32_t more = n_tiles - each * ns;               // splits with one tile more
+    v = 0;
+    v_end = each + (split < more ? 1u : 0u);
+    if (v_end == 0) return;                                  // fewer tiles than splits
+    t0 = split * each + (split < more ? split : more);
+    const uint32_t u = (uint32_t)(b * sh.Hkv + kvh);
+    rec0 = ((uint32_t)rc * units + u) * ns + split - u;
+  } else {
+    const FlatLine f = flat_line<PAD>(sh, keys, lane);
+    const uint32_t j = blockIdx.x >> 3;
+    const uint32_t j_pos = j * (rc_mul_splits & 0xffffu) >> 15;
+    rc = (int)(j - j_pos * (uint32_t)sh.n_rc);
+    const uint32_t per_xcd = (f.n_pos + 7) >> 3;      // neighbours on the line on one XCD
+    const uint32_t pos = (blockIdx.x & 7u) * per_xcd + j_pos;
+    if (j_pos >= per_xcd || pos >= f.n_pos) return;
+    const uint32_t quot = line_div(f.total, f.n_pos);
+    v = flat_begin(f, pos, quot);
+    v_end = flat_begin(f, pos + 1, quot);
+    b = __popcll(__ballot(f.end <= v));      // v < total: a sequence that exists
+    n_tiles = read_lane(keys.tiles, b);
+    const uint32_t off = v - (read_lane(f.end, b) - (n_tiles + PAD) * (uint32_t)sh.Hkv);
+    kvh = (int)line_div(off, n_tiles + PAD);
+    t0 = off - (uint32_t)kvh * (n_tiles + PAD);
+    rec0 = (uint32_t)rc * ((uint32_t)sh.n_pos + units) + pos;
+  }
   const int64_t rsb = (int64_t)sl8 * 16;
   while (true) {
-    const int L = (int)read_lane((uint32_t)f.L, b);
+    const int L = (int)read_lane((uint32_t)keys.L, b);
     const uint32_t t1 = t0 + (v_end - v) < n_tiles ? t0 + (v_end - v) : n_tiles;
     if (t0 < t1) {
       const int64_t base = ((int64_t)b * sb8 + (int64_t)kvh * sh8) * 16;
@@ -862,16 +917,16 @@ __global__ __launch_bounds__(256 * RS, 1) void attn_flat_kernel(
           args, smem, ln, wv, b, kvh, rc, L, sh.gamma, (int)n_tiles, (int)t0, (int)t1,
           reinterpret_cast<const uint8_t*>(k0) + base, reinterpret_cast<const uint8_t*>(v0) + base,
           rsb, [&](int) {
-            const size_t rec = (size_t)rc * (sh.n_pos + sh.B * sh.Hkv) + pos + b * sh.Hkv + kvh;
+            const uint32_t rec = rec0 + (uint32_t)(b * sh.Hkv + kvh);
             return args.ws + rec * (size_t)(16 * NBW * RS * 131);
           });
     }
-    v += n_tiles + f.pad - t0;
+    v += n_tiles + PAD - t0;
     if (v >= v_end) break;
     t0 = 0;
     if (++kvh == sh.Hkv) {
       kvh = 0;
-      n_tiles = read_lane(f.tiles, ++b);
+      n_tiles = read_lane(keys.tiles, ++b);
     }
     __syncthreads();   // the merge buffers have been read: the next unit's copies may overwrite them
   }
@@ -881,11 +936,15 @@ __global__ __launch_bounds__(256 * RS, 1) void attn_flat_kernel(
 // (consecutive in the workgroup) share a row: record s of the unit goes to group s % SG.  Few
 // records per row (a large batch) want few groups per row; sums run in a fixed order.  A chain of
 // latencies like attn_combine_kernel: the lengths, then all of the first records at once (running
-// maximum per group), then the output.  Grid: row groups, kv heads, sequences.
+// maximum per group), then the output.  Grid: row groups (n_groups of 8 / SG rows), kv heads,
+// sequences; a unit of equal splits is taken on the XCD whose L2 holds its records.  (The line's records
+// lie elsewhere, and units dealt to XCDs crowd the long ones together: 8 of 192 to 3066 keys, 64 / 8
+// heads 13.4 -> 15.4 us.  To read the records of equal splits before the lengths are there
+// costs the line more, 12.0 -> 12.5 us for 3 of 958 to 3834 keys at 40 / 8 heads, and gains nothing.)
 template <int SG, int PAD>
 __global__ __launch_bounds__(256) void attn_flat_combine_kernel(
     const float* ws, uint32_t packed, uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3,
-    uint32_t x4, int R, int rpad, uint32_t whole, const AttnKernelArgs p) {
+    uint32_t x4, int R, int rpad, uint32_t splits, uint32_t n_groups, const AttnKernelArgs p) {
   constexpr int kRows = 8 / SG;
   constexpr int kBatch = 4;          // records a group asks for at a time
   __shared__ float sm_o[8][128];
@@ -895,9 +954,21 @@ __global__ __launch_bounds__(256) void attn_flat_combine_kernel(
   const int sg = group % SG;
   const int l32 = threadIdx.x & 31;
   const FlatShape sh = flat_shape(packed);
-  const int kvh = blockIdx.y, b = blockIdx.z;
-  const int bh = b * sh.Hkv + kvh;
-  const int row_u = blockIdx.x * kRows + group / SG;
+  const SeqKeys keys = flat_keys(sh, packed, x0, x1, x2, x3, x4, p, lane);
+  const uint32_t units = (uint32_t)(sh.B * sh.Hkv);
+  const bool equal = flat_equal_splits(sh, keys, splits, lane);
+  int kvh = (int)blockIdx.y, b = (int)blockIdx.z;
+  uint32_t row_group = blockIdx.x;
+  if (equal && units % 8 == 0) {
+    const uint32_t id = blockIdx.x + n_groups * (uint32_t)(b * sh.Hkv + kvh);
+    const uint32_t u8 = line_div(id >> 3, n_groups);
+    const uint32_t u = u8 * 8 + (id & 7u);
+    row_group = (id >> 3) - u8 * n_groups;
+    b = (int)line_div(u, (uint32_t)sh.Hkv);
+    kvh = (int)u - b * sh.Hkv;
+  }
+  const uint32_t bh = (uint32_t)(b * sh.Hkv + kvh);
+  const int row_u = (int)row_group * kRows + group / SG;
   const bool valid = row_u < R;
   const int r = valid ? row_u : R - 1;       // query row of this kv head
   int rc = 0, rr = r;
@@ -905,13 +976,22 @@ __global__ __launch_bounds__(256) void attn_flat_combine_kernel(
     rr -= rpad;
     ++rc;
   }
-  const FlatLine f = flat_line<PAD>(sh, packed, whole, x0, x1, x2, x3, x4, p, lane);
-  const uint32_t n_tiles = read_lane(f.tiles, b);
-  const uint32_t u0 = read_lane(f.end, b) - (n_tiles + f.pad) * (uint32_t)(sh.Hkv - kvh);
-  const uint32_t first = flat_pos_of(f, u0);
-  const int ns = (int)(flat_pos_of(f, u0 + n_tiles - 1) - first) + 1;
+  const uint32_t n_tiles = read_lane(keys.tiles, b);
+  uint32_t first;                            // record, of `ns`
+  int ns;
+  if (equal) {
+    const int most = (int)(splits & 127u) + 1;
+    first = ((uint32_t)rc * units + bh) * (uint32_t)most;
+    ns = (int)n_tiles < most ? (int)n_tiles : most;
+  } else {
+    const FlatLine f = flat_line<PAD>(sh, keys, lane);
+    const uint32_t u0 = read_lane(f.end, b) - (n_tiles + PAD) * (uint32_t)(sh.Hkv - kvh);
+    const uint32_t pos = flat_pos_of(f, u0);
+    ns = (int)(flat_pos_of(f, u0 + n_tiles - 1) - pos) + 1;
+    first = (uint32_t)rc * ((uint32_t)sh.n_pos + units) + pos + bh;
+  }
   const size_t stride = (size_t)rpad * 131;
-  const float* base = ws + ((size_t)rc * (sh.n_pos + sh.B * sh.Hkv) + first + bh) * stride;
+  const float* base = ws + first * stride;
   const float* stat = base + rr;
   const float* orow = base + 3 * rpad + rr * 128 + l32 * 4;
 
@@ -1195,25 +1275,24 @@ static hipError_t launch_flat(const AttnKernelArgs& a, hipStream_t stream) {
   hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(&attn_flat_kernel<RS, NBW>), lds);
   if (e != hipSuccess) return e;
   const FlatArgs f = flat_args(a);
-  const int units = a.B * a.Hkv;
-  const int over = a.flat_pos % units;
-  const uint32_t whole = over == 0 || a.flat_pos >= 4 * units ? a.flat_pos - over : 0;
-  hipLaunchKernelGGL((attn_flat_kernel<RS, NBW>), dim3(a.flat_pos * a.n_rc), dim3(256 * RS), lds,
-                     stream, a.k, a.v, (uint32_t)(a.kv_sb / 8), (uint32_t)(a.kv_sh / 8),
+  const uint32_t units = (uint32_t)(a.B * a.Hkv);
+  const uint32_t ns = (uint32_t)a.n_split;     // at most 128: a batch has two units or more
+  const bool fills = units * ns == (uint32_t)a.flat_pos || ns >= 4;
+  const uint32_t splits = (ns - 1) | (fills ? 128u : 0u);
+  const uint32_t line = (uint32_t)a.flat_pos * a.n_rc, equal = units * ns * a.n_rc;
+  hipLaunchKernelGGL((attn_flat_kernel<RS, NBW>), dim3(line > equal ? line : equal), dim3(256 * RS),
+                     lds, stream, a.k, a.v, (uint32_t)(a.kv_sb / 8), (uint32_t)(a.kv_sh / 8),
                      (uint32_t)(a.kv_sl / 8), f.packed, f.x[0], f.x[1], f.x[2], f.x[3], f.x[4],
-                     (uint32_t)((65536 + a.n_rc - 1) / a.n_rc) | whole << 17, a);
+                     (uint32_t)((32768 + a.n_rc - 1) / a.n_rc) | splits << 16, a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   // eight groups per row where a unit has about eight records or more, two elsewhere
   constexpr int PAD = flat_pad(rpad);
-  if (a.flat_pos >= 8 * units)
-    hipLaunchKernelGGL((attn_flat_combine_kernel<8, PAD>), dim3(a.R, a.Hkv, a.B), dim3(256), 0,
-                       stream, a.ws, f.packed, f.x[0], f.x[1], f.x[2], f.x[3], f.x[4], a.R, rpad,
-                       whole, a);
-  else
-    hipLaunchKernelGGL((attn_flat_combine_kernel<2, PAD>), dim3((a.R + 3) / 4, a.Hkv, a.B), dim3(256),
-                       0, stream, a.ws, f.packed, f.x[0], f.x[1], f.x[2], f.x[3], f.x[4], a.R, rpad,
-                       whole, a);
+  const uint32_t groups = (uint32_t)a.flat_pos >= 8 * units ? a.R : (a.R + 3) / 4;
+  const auto kernel = (uint32_t)a.flat_pos >= 8 * units ? &attn_flat_combine_kernel<8, PAD>
+                                                        : &attn_flat_combine_kernel<2, PAD>;
+  hipLaunchKernelGGL(kernel, dim3(groups, a.Hkv, a.B), dim3(256), 0, stream, a.ws, f.packed, f.x[0],
+                     f.x[1], f.x[2], f.x[3], f.x[4], a.R, rpad, splits, groups, a);
   return hipGetLastError();
 }
 

@@ -72,7 +72,8 @@ struct AttnKernelArgs {
   float scale_log2e;
   int B;
   int flat_pos;  // > 0: equal stretches of one line over all sequences (a multiple of 8, B <= 64);
-                 // then ws is [n_rc][flat_pos + B*Hkv][rpad * 131]
+                 // then ws is [n_rc][flat_pos + B*Hkv][rpad * 131], or
+                 // [n_rc][B*Hkv][n_split][rpad * 131] where the lengths ask for equal splits
   int variant;   // kernel variant, 0 = default for rpad (development knob; host side only)
   const int32_t* vis_begin;   // nullptr = no span
   const int32_t* vis_end;
@@ -85,6 +86,10 @@ struct AttnKernelArgs {
 static_assert(offsetof(AttnKernelArgs, len_host) == 192, "prologue arguments fill three 64-byte lines");
 
 hipError_t launch_attn(const AttnKernelArgs& a, hipStream_t stream);
+// A batch is short when no workgroup of its equal splits has this many tiles of 32 keys.  Two
+// sequences have less to win from the line (1534 and 6138 keys, 12 tiles, 40 / 8 heads: 12.6 us in
+// equal splits, 14.0 on the line; 2046 and 8186 keys 14.5, 14.9; four of 766 to 3066 13.5, 12.3).
+constexpr int attn_short_tiles(int B) { return B == 2 ? 16 : 12; }
 // stretches of the line over all sequences of a batch; 0: this shape has none
 int attn_flat_positions(int B, int Hkv, int rpad, int n_rc, int64_t cap, int num_cu);
 
