@@ -52,6 +52,23 @@ class Batch:
                                        for t in self.kv), self.kv_len)
         assert_rows_close(bf16_out_to_f64(out), o, what)
 
+    def segments(self):
+        """Tiles of every workgroup's parts of units, as the line cuts them."""
+        pad = 5 if self.rpad <= 32 else 10
+        tiles = [(n + self.gamma + 31) // 32 for n in self.kv_len for _ in range(self.Hkv)]
+        total = sum(t + pad for t in tiles)
+        n_pos = max(1, min(self.stretches, total // 4))
+        cuts = [total * p // n_pos for p in range(n_pos + 1)]
+        ends = np.cumsum([t + pad for t in tiles])
+        parts = []
+        for lo, hi in zip(cuts, cuts[1:]):
+            for u in range(int(np.searchsorted(ends, lo, "right")), len(tiles)):
+                at = int(ends[u]) - tiles[u] - pad
+                if at >= hi:
+                    break
+                parts.append(min(hi - at, tiles[u]) - max(lo - at, 0))
+        return [t for t in parts if t > 0]
+
 
 # bf16 results of the same partial sums, merged in another order: a 32-bit rounding (1e-7) moves a
 # value over a bf16 boundary (4e-3 apart) in about one of 1e4; another cut gives other bf16
@@ -79,3 +96,49 @@ def test_short_or_equal_sequences_take_equal_splits(Hq, Hkv, gamma, kv_len, cap)
     assert _other_bits(line, b.run(split=True)) < 2e-3
     assert torch.equal(line, b.run(lens="host")) and torch.equal(line, b.run(lens="both"))
     b.check(line, "equal splits")
+
+
+@pytest.mark.parametrize("Hq,Hkv,gamma,n", [(8, 8, 3, 4100), (32, 8, 5, 4100), (64, 8, 5, 3600),
+                                            (64, 8, 8, 3600), (48, 4, 16, 3600)])
+def test_surplus_tiles_on_the_line_and_in_equal_splits(Hq, Hkv, gamma, n):
+    # 16-, 32-, 48-, 64-row variants and two row chunks: parts of 4q + 1 and 4q + 2 tiles (q >= 3)
+    # keep the surplus in extra LDS slots, whichever kernel has them
+    b = Batch((Hq, gamma), [n, 3372, 3500, 1700], Hq, Hkv, gamma)
+    assert b.stretches > 0
+    parts = b.segments()
+    assert sum(parts) == sum((x + gamma + 31) // 32 for x in b.kv_len) * Hkv
+    assert {t % 4 for t in parts if t >= 12} >= {1, 2}, parts
+    b.check(b.run(), "line")
+    tiles = [(x + gamma + 31) // 32 for x in b.kv_len]
+    each = {t // b.n_split + more for t in tiles for more in ((0, 1) if t % b.n_split else (0,))}
+    assert {t % 4 for t in each if t >= 12} >= {1, 2}, each
+    b.check(b.run(split=True), "equal splits")
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,gamma,n", [(3, 8, 8, 5, 4000), (5, 24, 8, 5, 2400), (6, 40, 4, 4, 4000),
+                                              (20, 16, 2, 8, 2400), (32, 8, 2, 5, 1700)])
+def test_the_line_is_the_same_however_the_lengths_arrive(B, Hq, Hkv, gamma, n):
+    # in the launch arguments (up to five sequences), in a table (without a device array) and on the
+    # device: the same stretches
+    kv_len = [int(x) for x in np.random.default_rng((122, B)).integers(1, n, B)]
+    kv_len[B // 2] = n
+    b = Batch((B, n), kv_len, Hq, Hkv, gamma)
+    assert b.stretches > 0
+    out = b.run()
+    # the line it is, not the equal splits
+    assert _other_bits(out, b.run(split=True)) > 1e-2
+    assert torch.equal(out, b.run(lens="host")) and torch.equal(out, b.run(lens="both"))
+    b.check(out, "line")
+
+
+@pytest.mark.parametrize("Hq,Hkv,gamma", [(8, 8, 5), (40, 8, 8)])
+def test_equal_splits_do_not_look_at_the_other_sequences(Hq, Hkv, gamma):
+    # the stretches of the line follow from all lengths; with a workspace for equal splits, or one
+    # sequence, a sequence's bits follow from the shapes and its own length
+    lens = [4000, 1300, 2500]
+    a = Batch((Hq, 1), lens, Hq, Hkv, gamma)
+    out = a.run(split=True)
+    a.kv_len = [4000, 17, 3100]
+    other = a.run(split=True)
+    assert torch.equal(out[0], other[0]) and not torch.equal(out[1], other[1])
+    assert_rows_close(bf16_out_to_f64(a.run()[0]), bf16_out_to_f64(other[0]), "line, same sequence")
