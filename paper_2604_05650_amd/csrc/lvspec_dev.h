@@ -214,6 +214,22 @@ LVS_DEV uint64_t read_lane64(uint64_t x, int lane) {
   return ((uint64_t)hi << 32) | lo;
 }
 
+// The k <= 16 largest of a wave's 64-bit keys (0 = none), the r-th in lane r.
+template <int NV>
+LVS_DEV uint64_t topk_of(uint64_t (&key)[NV], int k, int lane) {
+  uint64_t top = 0ull;
+  for (int r = 0; r < k; ++r) {
+    uint64_t best = key[0];
+#pragma unroll
+    for (int j = 1; j < NV; ++j) best = key[j] > best ? key[j] : best;
+    const uint64_t w = wave_max_u64(best);
+#pragma unroll
+    for (int j = 0; j < NV; ++j) key[j] = key[j] == w ? 0ull : key[j];
+    top = lane == r ? w : top;
+  }
+  return top;
+}
+
 // A wave's running list of the k <= 16 largest 64-bit keys, lane r < 16 holding the r-th largest
 // (0 = none): take in NV keys per lane.  Only keys above the k-th so far cost a round, largest
 // first; every round retires one key, so the loop ends.  Equal keys are the same candidate.
