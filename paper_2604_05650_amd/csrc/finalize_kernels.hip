@@ -12,7 +12,7 @@
 //                  (optionally the row's softmax entropy), then the paper's Eq. 9 (loosened
 //                  set), Eq. 10/11 (verdicts incl. position-shift tolerance) and Eq. 2 (accepted
 //                  length = longest accepted prefix); the chains of a draft tree share a
-//                  workgroup, which then keeps the longest one.
+//                  workgroup, which then keeps the longest one (long trees: in a launch of its own).
 #include "lvspec_dev.h"
 #include "lvspec_kernels.h"
 
@@ -349,7 +349,7 @@ __global__ __launch_bounds__(kFinThreads) void rel_finalize_kernel(const RelFina
 }
 
 // ------------------------------------------------------------------------------------------
-constexpr int kAccWaves = 16;          // waves of the merge at most
+constexpr int kAcceptOneKernelRows = 16;   // hidden rows of a sequence, a wave each
 constexpr int kRecRegs = 8;            // records per lane: kAcceptMaxRecords / 64
 constexpr int kPickedMax = 32;         // records the short way of the selection can take
 
@@ -368,6 +368,7 @@ LVS_DEV uint32_t kth_bound(const uint32_t (&key)[NV], int k) {
   }
   if (have <= k) return 1u;
   hi = wave_max_u32(hi);
+  if (k == 1) return hi;
   const uint32_t lo = ~wave_max_u32(nlo);
   if (hi == lo) return hi;
   const int top = 31 - __clz((int)(hi ^ lo));
@@ -383,136 +384,164 @@ LVS_DEV uint32_t kth_bound(const uint32_t (&key)[NV], int k) {
   return T;
 }
 
-// One workgroup per sequence, for both halves of the acceptance.
-// First the merge, one wave per hidden row (rows beyond sixteen in turn): the records lm_head
-// left of the row (one per workgroup of that launch) become the greedy target token, the k most
-// probable tokens and (optionally) the softmax entropy.  The k best candidates can only come from
+// ---- the two halves of the acceptance
+// The merge, one wave per hidden row: the records lm_head left of the row (one per workgroup of that
+// launch) become the greedy target token, the k most probable tokens and (optionally) the softmax
+// entropy.  The k best candidates can only come from
 // the k records with the largest maxima, and the maxima are needed for the softmax sum anyway: so
 // the wave looks for the k-th largest maximum (kth_bound) and fetches the candidates of those
-// records alone, k * k instead of all (5 rows, 475 records, k = 4: 16 of 1900).  What bounds this
-// kernel is the number of instructions and dependent loads on one CU.  Measured (rocprofv3, against
-// a merge over one record per 64 vocabulary rows followed by a launch of its own for the rule):
-// 5 rows, V = 152064: k = 4 9.5 + 4.8 -> 7.0 us, k = 16 28.4 + 4.6 -> 11.4; 48 rows, k = 4
-// 18.8 + 4.8 -> 8.4.
-// Then, behind one barrier, the rule: one wave per chain of the sequence's draft tree (a plain
-// chain draft is a tree with one branch), one lane per draft position: loosened set (Eq. 9),
+// records alone, k * k instead of all (5 rows, 476 records, k = 4: 16 of 1904).  What bounds it is
+// the number of instructions and dependent loads of a wave.
+// The rule, one wave per chain of the sequence's draft tree (a plain chain draft is a tree with one
+// branch), one lane per draft position: loosened set (Eq. 9),
 // verdicts (Eq. 10 / 11), accepted length (Eq. 2) per chain, then the chain with the longest
 // accepted length (appendix on draft token trees).  Everything a position needs from the others
 // comes through v_readlane in a loop over the positions.
-__global__ __launch_bounds__(64 * kAccWaves) void accept_finalize_kernel(const AcceptFinalizeArgs p) {
-  __shared__ int sm_pick[kAccWaves][kPickedMax];
-  __shared__ int sh_y[kAcceptMaxRows];
-  __shared__ int sh_top[kAcceptMaxRows][16];
-  __shared__ float sh_ent[kAcceptMaxRows];
-  __shared__ int sh_tau[kMaxBranches];
-  const int seq = blockIdx.x;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int n_waves = (int)(blockDim.x >> 6);
-  const int R = p.n_branches * p.rows;      // hidden rows of this sequence
+//
+// Up to kAcceptOneKernelRows hidden rows per sequence, one workgroup does both (accept_finalize_kernel;
+// rocprofv3, against a merge over one record per 64 vocabulary rows followed by a launch of its own for
+// the rule: 5 rows, V = 152064: k = 4 9.5 + 4.8 -> 7.0 us, k = 16 28.4 + 4.6 -> 11.4).  More rows
+// would take turns on the waves of one CU: then the merge is spread over the chip and the rule waits
+// for it in a launch of its own (accept_merge_kernel, accept_rule_kernel; 8 chains of 8, V = 8192:
+// k = 4 31.9 -> 4.0 + 3.1 us, k = 16 60.0 -> 6.8 + 4.5; with V = 152064 31.1 -> 6.1 + 4.6 and
+// 60.7 -> 8.7 + 4.6; 2 chains of 10, k = 4, V = 8192 12.2 -> 4.0 + 2.6, V = 152064 11.8 -> 6.5 + 4.5).
+
+// What the rule needs of a merged row: in LDS, or where the row's records were.
+struct RowsInLds {
+  int (&top)[kAcceptOneKernelRows][16];
+  float (&ent)[kAcceptOneKernelRows];
+  LVS_DEV void put_top(int row, int lane, int id) const { top[row][lane] = id; }
+  LVS_DEV void put_ent(int row, float e) const { ent[row] = e; }
+  LVS_DEV int top_at(int row, int e) const { return top[row][e]; }
+  LVS_DEV float ent_at(int row) const { return ent[row]; }
+};
+
+// A row's first candidates and its first maximum have been read by the wave that puts the results
+// there, and no other wave looks at them.
+struct RowsInRecords {
+  const AcceptFinalizeArgs& p;
+  int64_t col0;     // column of row 0
+  LVS_DEV int* ids(int row) const {
+    return reinterpret_cast<int*>(const_cast<uint64_t*>(p.cand) + (col0 + row) * p.n_rec * p.topk);
+  }
+  LVS_DEV float* stat(int row) const {
+    return const_cast<float*>(p.stats) + (col0 + row) * p.n_rec * 2;
+  }
+  LVS_DEV void put_top(int row, int lane, int id) const { ids(row)[lane] = id; }
+  LVS_DEV void put_ent(int row, float e) const { *stat(row) = e; }
+  LVS_DEV int top_at(int row, int e) const { return ids(row)[e]; }
+  LVS_DEV float ent_at(int row) const { return *stat(row); }
+};
+
+// NR: records per lane (n_rec <= 64 * NR).
+template <int NR, class Rows>
+LVS_DEV void merge_row(const AcceptFinalizeArgs& p, int64_t col, int row, int lane, int* pick,
+                       const Rows& rows) {
   const bool want_z = p.stats_z != nullptr;
   const int n_rec = p.n_rec;
-
-  for (int row = wave; row < R; row += n_waves) {
-    const int64_t col = (int64_t)seq * R + row;
-    const float2* st = reinterpret_cast<const float2*>(p.stats) + col * n_rec;
-    const uint64_t* ck = p.cand + col * n_rec * p.topk;
-    // ---- softmax statistics over the records
-    float2 ms[kRecRegs];
-    float z[kRecRegs];
+  const float2* st = reinterpret_cast<const float2*>(p.stats) + col * n_rec;
+  const uint64_t* ck = p.cand + col * n_rec * p.topk;
+  // ---- softmax statistics over the records
+  float2 ms[NR];
+  float z[NR];
 #pragma unroll
-    for (int u = 0; u < kRecRegs; ++u) {
-      const int i = 64 * u + lane;
-      const int ic = i < n_rec ? i : n_rec - 1;
-      ms[u] = st[ic];
-      z[u] = want_z ? p.stats_z[col * n_rec + ic] : 0.f;
-    }
-    float mx = -INFINITY;
-    uint32_t mkey[kRecRegs];
+  for (int u = 0; u < NR; ++u) {
+    const int i = 64 * u + lane;
+    const int ic = i < n_rec ? i : n_rec - 1;
+    ms[u] = st[ic];
+    z[u] = want_z ? p.stats_z[col * n_rec + ic] : 0.f;
+  }
+  float mx = -INFINITY;
+  uint32_t mkey[NR];
 #pragma unroll
-    for (int u = 0; u < kRecRegs; ++u) {
-      const bool on = 64 * u + lane < n_rec;
-      ms[u].x = on ? ms[u].x : -INFINITY;
-      mkey[u] = ms[u].x != -INFINITY ? order_key(ms[u].x) : 0u;
-      mx = fmaxf(mx, ms[u].x);
-    }
-    // ---- records that can hold one of the k best
-    const uint32_t bound = kth_bound<kRecRegs>(mkey, p.topk);
-    int picked = 0;
+  for (int u = 0; u < NR; ++u) {
+    const bool on = 64 * u + lane < n_rec;
+    ms[u].x = on ? ms[u].x : -INFINITY;
+    mkey[u] = ms[u].x != -INFINITY ? order_key(ms[u].x) : 0u;
+    mx = fmaxf(mx, ms[u].x);
+  }
+  // ---- records that can hold one of the k best
+  const uint32_t bound = kth_bound<NR>(mkey, p.topk);
+  int picked = 0;
 #pragma unroll
-    for (int u = 0; u < kRecRegs; ++u) {
-      const bool q = mkey[u] >= bound;
-      const unsigned long long mask = __ballot(q);
-      const int slot = picked + __popcll(mask & ((1ull << lane) - 1ull));
-      if (q && slot < kPickedMax) sm_pick[wave][slot] = 64 * u + lane;
-      picked += __popcll(mask);
-    }
-    uint64_t top = 0ull;
-    if (picked <= kPickedMax) {
-      const int nk = picked * p.topk;
-      for (int k0 = 0; k0 < nk; k0 += 256) {
-        uint64_t key[4];
+  for (int u = 0; u < NR; ++u) {
+    const bool q = mkey[u] >= bound;
+    const unsigned long long mask = __ballot(q);
+    const int slot = picked + __popcll(mask & ((1ull << lane) - 1ull));
+    if (q && slot < kPickedMax) pick[slot] = 64 * u + lane;
+    picked += __popcll(mask);
+  }
+  uint64_t top = 0ull;
+  if (picked <= kPickedMax) {
+    const int nk = picked * p.topk;
+    for (int k0 = 0; k0 < nk; k0 += 256) {
+      uint64_t key[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int i = k0 + 64 * u + lane;
-          const int ic = i < nk ? i : nk - 1;
-          const int t = (int)fast_div((uint32_t)ic, p.div_topk);
-          const int e = ic - t * p.topk;
-          key[u] = ck[(int64_t)sm_pick[wave][t] * p.topk + e];
-        }
+      for (int u = 0; u < 4; ++u) {
+        const int i = k0 + 64 * u + lane;
+        const int ic = i < nk ? i : nk - 1;
+        const int t = (int)fast_div((uint32_t)ic, p.div_topk);
+        const int e = ic - t * p.topk;
+        key[u] = ck[(int64_t)pick[t] * p.topk + e];
+      }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) key[u] = k0 + 64 * u + lane < nk ? key[u] : 0ull;
+      for (int u = 0; u < 4; ++u) key[u] = k0 + 64 * u + lane < nk ? key[u] : 0ull;
+      if (k0 == 0)
+        top = topk_of<4>(key, p.topk, lane);
+      else
         topk_insert<4>(top, key, p.topk, lane);
-      }
-    } else {
-      // (many records share the k-th largest maximum) all candidates
-      const int nk = n_rec * p.topk;
-      for (int k0 = 0; k0 < nk; k0 += 256) {
-        uint64_t key[4];
+    }
+  } else {
+    // (many records share the k-th largest maximum) all candidates
+    const int nk = n_rec * p.topk;
+    for (int k0 = 0; k0 < nk; k0 += 256) {
+      uint64_t key[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int i = k0 + 64 * u + lane;
-          key[u] = i < nk ? ck[i] : 0ull;
-        }
+      for (int u = 0; u < 4; ++u) {
+        const int i = k0 + 64 * u + lane;
+        key[u] = i < nk ? ck[i] : 0ull;
+      }
+      if (k0 == 0)
+        top = topk_of<4>(key, p.topk, lane);
+      else
         topk_insert<4>(top, key, p.topk, lane);
-      }
-    }
-    // ---- results of the row
-    mx = wave_max(mx);
-    float se = 0.f, sz = 0.f;
-#pragma unroll
-    for (int u = 0; u < kRecRegs; ++u) {
-      const float f = ms[u].x == -INFINITY ? 0.f : fast_exp2((ms[u].x - mx) * kLog2e);
-      se += ms[u].y * f;
-      sz += z[u] * f;
-    }
-    se = wave_sum(se);
-    if (want_z) {
-      // H = -sum p ln p with p = exp(z - max) / se:  ln se + max - (sum exp(z - max) z) / se
-      sz = wave_sum(sz);
-      const float ent = __logf(se) + mx - sz / se;
-      if (lane == 0) {
-        sh_ent[row] = ent;
-        if (p.entropy) p.entropy[col] = ent;
-      }
-    }
-    if (lane < p.topk) {
-      const bool none = top == 0ull;
-      const float win_v = key_value((uint32_t)(top >> 32));
-      const int id = none ? -1 : 0x7fffffff - (int)(uint32_t)top;
-      const float prob = none ? 0.f : __expf(win_v - mx) / se;
-      if (lane == 0) {
-        p.target_ids[col] = id;
-        sh_y[row] = id;
-      }
-      sh_top[row][lane] = id;
-      if (p.topk_ids) p.topk_ids[col * p.topk + lane] = id;
-      if (p.topk_probs) p.topk_probs[col * p.topk + lane] = prob;
     }
   }
-  __syncthreads();
+  // ---- results of the row
+  mx = wave_max(mx);
+  float se = 0.f, sz = 0.f;
+#pragma unroll
+  for (int u = 0; u < NR; ++u) {
+    const float f = ms[u].x == -INFINITY ? 0.f : fast_exp2((ms[u].x - mx) * kLog2e);
+    se += ms[u].y * f;
+    sz += z[u] * f;
+  }
+  se = wave_sum(se);
+  if (want_z) {
+    // H = -sum p ln p with p = exp(z - max) / se:  ln se + max - (sum exp(z - max) z) / se
+    sz = wave_sum(sz);
+    const float ent = __logf(se) + mx - sz / se;
+    if (lane == 0) {
+      rows.put_ent(row, ent);
+      if (p.entropy) p.entropy[col] = ent;
+    }
+  }
+  if (lane < p.topk) {
+    const bool none = top == 0ull;
+    const float win_v = key_value((uint32_t)(top >> 32));
+    const int id = none ? -1 : 0x7fffffff - (int)(uint32_t)top;
+    const float prob = none ? 0.f : __expf(win_v - mx) / se;
+    if (lane == 0) p.target_ids[col] = id;
+    rows.put_top(row, lane, id);
+    if (p.topk_ids) p.topk_ids[col * p.topk + lane] = id;
+    if (p.topk_probs) p.topk_probs[col * p.topk + lane] = prob;
+  }
+}
 
-  const int br = wave;                                     // branch of this wave
+// br: the branch of this wave.  All waves of the workgroup call it.
+template <class Rows>
+LVS_DEV void apply_rule(const AcceptFinalizeArgs& p, int seq, int br, int lane, const Rows& rows,
+                        int (&sh_tau)[kMaxBranches]) {
   if (br < p.n_branches) {
     const int b = seq * p.n_branches + br;                 // chain index
     const int g = p.gamma;
@@ -520,14 +549,14 @@ __global__ __launch_bounds__(64 * kAccWaves) void accept_finalize_kernel(const A
     const int idx = b * g + (on ? lane : 0);                      // draft position of this lane
     const int row = br * p.rows + (lane < p.rows ? lane : 0);     // hidden row of this lane
     const int dk = p.draft_ids[idx];
-    const int yk = sh_y[row];
+    const int yk = rows.top_at(row, 0);
     unsigned char vd = 0;
     if (p.rule == 0) {
       const float ak = p.relevance[idx];
       int gate_ok = 1;
       if (p.gate > 0) {
         gate_ok = 0;
-        for (int e = 0; e < p.gate; ++e) gate_ok |= (sh_top[row][e] == dk);
+        for (int e = 0; e < p.gate; ++e) gate_ok |= (rows.top_at(row, e) == dk);
       }
       // position of this lane in the stable ascending order of the relevance scores (Eq. 9: the
       // n_loose first are loosened), and whether its target token occurs among the other drafts
@@ -553,7 +582,7 @@ __global__ __launch_bounds__(64 * kAccWaves) void accept_finalize_kernel(const A
       // Entropy-gated rules of the text-only loose methods the paper compares against: a
       // mismatch passes when its row's entropy exceeds the threshold and (rule 2) the w
       // positions behind it are all draft positions that match exactly.
-      const float hk = sh_ent[row];
+      const float hk = rows.ent_at(row);
       const unsigned long long exact = __ballot(on && dk == yk);
       const int w = p.rule == 2 ? p.defer_window : 0;
       const unsigned long long need = ((1ull << w) - 1ull) << (on ? lane + 1 : 0);   // < 2^33
@@ -583,6 +612,41 @@ __global__ __launch_bounds__(64 * kAccWaves) void accept_finalize_kernel(const A
       if (sh_tau[a] > sh_tau[best]) best = a;
     p.best_branch[seq] = best;
   }
+}
+
+template <int NR>
+__global__ __launch_bounds__(64 * kAcceptOneKernelRows) void accept_finalize_kernel(
+    const AcceptFinalizeArgs p) {
+  __shared__ int sm_pick[kAcceptOneKernelRows][kPickedMax];
+  __shared__ int sh_top[kAcceptOneKernelRows][16];
+  __shared__ float sh_ent[kAcceptOneKernelRows];
+  __shared__ int sh_tau[kMaxBranches];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const RowsInLds rows{sh_top, sh_ent};
+  const int R = p.n_branches * p.rows;      // hidden rows of this sequence, one per wave
+  merge_row<NR>(p, (int64_t)blockIdx.x * R + wave, wave, lane, sm_pick[wave], rows);
+  __syncthreads();
+  apply_rule(p, blockIdx.x, wave, lane, rows, sh_tau);
+}
+
+constexpr int kMergeWaves = 4;         // one per SIMD
+
+template <int NR>
+__global__ __launch_bounds__(64 * kMergeWaves) void accept_merge_kernel(const AcceptFinalizeArgs p) {
+  __shared__ int sm_pick[kMergeWaves][kPickedMax];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int row = blockIdx.x * kMergeWaves + wave;
+  if (row < p.B * p.rows) merge_row<NR>(p, row, row, lane, sm_pick[wave], RowsInRecords{p, 0});
+}
+
+__global__ __launch_bounds__(64 * kMaxBranches) void accept_rule_kernel(const AcceptFinalizeArgs p) {
+  __shared__ int sh_tau[kMaxBranches];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int R = p.n_branches * p.rows;
+  apply_rule(p, blockIdx.x, wave, lane, RowsInRecords{p, (int64_t)blockIdx.x * R}, sh_tau);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1106,13 +1170,27 @@ hipError_t launch_rel_finalize(const RelFinalizeArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+template <int NR>
+static void launch_accept(const AcceptFinalizeArgs& a, hipStream_t stream) {
+  const int R = a.n_branches * a.rows;
+  if (R <= kAcceptOneKernelRows) {
+    hipLaunchKernelGGL(accept_finalize_kernel<NR>, dim3(a.B / a.n_branches), dim3(64 * R), 0, stream,
+                       a);
+    return;
+  }
+  hipLaunchKernelGGL(accept_merge_kernel<NR>, dim3((a.B * a.rows + kMergeWaves - 1) / kMergeWaves),
+                     dim3(64 * kMergeWaves), 0, stream, a);
+  hipLaunchKernelGGL(accept_rule_kernel, dim3(a.B / a.n_branches), dim3(64 * a.n_branches), 0, stream,
+                     a);
+}
+
 hipError_t launch_accept_finalize(const AcceptFinalizeArgs& a, hipStream_t stream) {
   static_assert(kRecRegs * 64 == kAcceptMaxRecords, "records per lane");
   const int R = a.n_branches * a.rows;
   if (R > kAcceptMaxRows || a.topk > 16 || a.n_rec > kAcceptMaxRecords || a.n_branches > kMaxBranches)
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL(accept_finalize_kernel, dim3(a.B / a.n_branches),
-                     dim3(64 * (R < kAccWaves ? R : kAccWaves)), 0, stream, a);
+  if (a.n_rec <= 64 * 2) launch_accept<2>(a, stream);
+  else launch_accept<kRecRegs>(a, stream);
   return hipGetLastError();
 }
 

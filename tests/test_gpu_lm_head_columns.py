@@ -128,3 +128,35 @@ def test_nan_logits_keep_their_places(B, K, V, topk):
             order = [left[j] for j in torch.argsort(logits[b, i], descending=True)]
             rest = [j for j in range(topk) if j not in left]
             assert outs["topk_ids"][b, i].tolist() == (order + rest)[:topk]
+
+
+@pytest.mark.parametrize("S,n_br,K,bonus,V", [
+    (3, 2, 8, False, 8192),      # 16 rows of a sequence: merge and rule in one kernel
+    (3, 3, 6, False, 8192),      # 18: two kernels; 128 records per row
+    (2, 2, 16, True, 8300),      # 34, chains of 17 rows; 130 records
+    (1, 8, 8, False, 33000),     # the most rows and chains
+    (5, 8, 2, True, 40),         # one record, rows that end inside a workgroup of the merge
+])
+def test_chains_of_a_tree_are_judged_as_chains(S, n_br, K, bonus, V):
+    # the same hidden rows as trees and as single chains: the same bits, and the longest chain is kept
+    from paper_2604_05650_amd import binding as L
+    B, d, rows = S * n_br, 256, K + (1 if bonus else 0)
+    key = (616, S, n_br, K, V)
+    h = synth.normal_bf16(key + (0,), (B, rows, d), 1.0)
+    w = synth.normal_bf16(key + (1,), (V, d), 0.1)
+    h, planted = synth.plant_target_rows(h, w, 24.0, key + (2,))
+    draft = t_i32(synth.draft_ids_from_target(planted[:, :K], key + (3,), p_wrong=0.3, V=V))
+    rel = t_f32(np.random.default_rng(key).random((B, K)))
+    h, w = t_bf16(h), t_bf16(w)
+    seen = set()
+    for kw in (dict(), dict(loose_topk_gate=3), dict(rule=L.RULE_ENTROPY_GATE, entropy_threshold=0.05),
+               dict(rule=L.RULE_ENTROPY_WINDOW, entropy_threshold=0.01, defer_window=1)):
+        tree, chains = (L.loose_accept(h, w, draft, rel, K // 2, K, topk=5, return_entropy=True,
+                                       n_branches=n, bonus_row=bonus, **kw) for n in (n_br, 1))
+        torch.cuda.synchronize()
+        for name, v in chains.items():
+            assert torch.equal(tree[name], v), (name, kw)
+        taus = chains["accept_len"].view(S, n_br).cpu().numpy()
+        assert tree["best_branch"].cpu().tolist() == taus.argmax(1).tolist()
+        seen |= set(chains["verdict"].unique().tolist())
+    assert seen >= {0, 1, 2}
