@@ -830,9 +830,21 @@ LVS_DEV uint32_t read_lane(uint32_t x, int lane) {
   return (uint32_t)__builtin_amdgcn_readlane((int)x, lane);
 }
 
-// two pointers and ten words precede the structure in the argument buffer
+// Where the last argument of a kernel lies in its argument buffer: arguments follow each other
+// at their natural alignment, as members of a structure.
+template <class Kernel>
+struct LastArgument;
+template <class... Args>
+struct LastArgument<void (*)(Args...)> {
+  static constexpr size_t offset() {
+    size_t at = 0, last = 0;
+    ((last = (at + alignof(Args) - 1) / alignof(Args) * alignof(Args), at = last + sizeof(Args)), ...);
+    return last;
+  }
+};
+
+// of attn_flat_kernel, which reads its argument structure through a pointer (see the loop)
 constexpr int kFlatArgsOffset = 56;
-static_assert(alignof(AttnKernelArgs) == 8, "the structure follows the leading arguments directly");
 
 // A workgroup per (stretch, row chunk); the row chunks of a stretch share an XCD's L2.  Strides in
 // units of eight elements; rc_mul_splits: ceil(32768 / n_rc), and `splits` from bit 16.
@@ -931,6 +943,9 @@ __global__ __launch_bounds__(256 * RS, 1) void attn_flat_kernel(
     __syncthreads();   // the merge buffers have been read: the next unit's copies may overwrite them
   }
 }
+
+static_assert(LastArgument<decltype(&attn_flat_kernel<1, 1>)>::offset() == kFlatArgsOffset,
+              "the structure's place behind the leading arguments");
 
 // One group of 32 lanes per output row and share of its records, four channels a lane.  SG groups
 // (consecutive in the workgroup) share a row: record s of the unit goes to group s % SG.  Few
