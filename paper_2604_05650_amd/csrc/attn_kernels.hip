@@ -754,7 +754,7 @@ struct FlatLine {
   uint32_t n_pos;     // stretches in use
 };
 
-// x / n by a reciprocal and one correction, for quotients below 2^20 (the product is then off by
+// x / n by a reciprocal and one correction, for quotients below 2^22 (the product is then off by
 // less than one) and x below 2^31: a third of the instructions of a full division, all of which
 // the first copies wait for.
 LVS_DEV uint32_t line_div(uint32_t x, uint32_t n) {
@@ -1316,9 +1316,11 @@ int attn_flat_positions(int B, int Hkv, int rpad, int n_rc, int64_t cap, int num
   int pos = num_cu / n_rc / 8 * 8;
   if (pos > 504) pos = 504;
   if (pos < 8) return 0;
-  // place numbers times positions stay in 32 bits
+  // place numbers times positions stay in 32 bits, and places per stretch within line_div's quotients
+  // (with 256 CUs the first is the narrower; a partition of 32 CUs may have eight stretches)
   const int64_t places = (cap + kTileKeys - 1) / kTileKeys + flat_pad(rpad);   // of the longest unit
-  return places * B * Hkv < (int64_t)0x7fffffff / (pos + 1) ? pos : 0;
+  const int64_t most = (int64_t)0x7fffffff / (pos + 1), exact = (int64_t)pos << 21;
+  return places * B * Hkv < (most < exact ? most : exact) ? pos : 0;
 }
 
 // variant = 10 * RS + NBW; 0 picks the default for the row-chunk size
