@@ -38,9 +38,11 @@ KERNELS_OF = {
     "verify_attn": ("lvspec_verify_attn = attn_split_kernel + attn_combine_kernel (batches: "
                     "attn_flat_kernel + attn_flat_combine_kernel)"),
     "visual_relevance": ("lvspec_visual_relevance = gemm_stream_kernel<REL> + rel_cand_kernel + "
-                         "rel_merge_kernel"),
-    "lm_head_accept": ("lvspec_loose_accept = gemm_stream_kernel<LMH> + "
-                       "accept_finalize_kernel"),
+                         "rel_merge_kernel (N above 16: rel_keep_kernel + rel_take_kernel, or "
+                         "rel_finalize_kernel)"),
+    "lm_head_accept": ("lvspec_loose_accept = gemm_stream_kernel<LMH> (33 hidden rows and more: "
+                       "lm_head_wide_kernel) + accept_finalize_kernel (more than 16 per sequence: "
+                       "accept_merge_kernel + accept_rule_kernel)"),
 }
 # the configurations timed besides the headline (name, draft rows override, steps)
 EXTRA_WORKLOADS = [("c1", 0), ("c2", 0), ("c3", 0), ("c4", 3), ("c4", 8), ("c4t", 0), ("c5", 0)]
@@ -148,6 +150,7 @@ class Workload:
                          dtype=torch.uint8, device=dev)
         self.acc_args.workspace, self.acc_args.workspace_bytes = ws.data_ptr(), ws.numel()
         self.keep.append(ws)
+        # (acc_passes counts groups of chains; two groups share a pass over lm_head)
         self.plan = L.describe_plan(attn=self.attn_args[0], rel=self.rel_args[0],
                                     accept=self.acc_args)
         # algorithmic bytes: every K/V row once, Q and O once (per layer); H_V + H_D once;

@@ -26,6 +26,13 @@ short text summaries kept under profiles/.
              figures bench.py replays, stamped with the commit, the library version and the
              launch plan of every workload they were taken at.
 
+    python -m paper_2604_05650_amd.profiling run-case <case> <passes> [--calibrate-copy]
+    python -m paper_2604_05650_amd.profiling case-summary <dir with the runs> <out dir> <case> ...
+
+`run-case` : passes of one listed case of perf/cases.py, for a profiler to look at;
+`case-summary` puts its runs (kt_<case>, fetch_<case>, write_<case>, mfma_<case>, lds_<case>) into one
+             text file per case: for the kernels that no workload of bench.py launches.
+
 `traffic`  : HBM bytes per library call from a FETCH_SIZE run and a WRITE_SIZE run of
              `bench.py --calibrate-copy`: each counter is scaled by what it reads for the
              calibration kernel (which moves exactly 1 GiB each way); printed as the JSON that
@@ -113,8 +120,18 @@ GROUPS = {   # kernels launched by one call of each entry point
     "verify_attn": ("attn_split_kernel", "attn_combine_kernel", "attn_flat_kernel",
                     "attn_flat_combine_kernel"),
     "visual_relevance": ("gemm_stream_kernel<0", "gemm_stream_kernel<2", "rel_finalize_kernel",
-                         "rel_cand_kernel", "rel_merge_kernel"),
-    "lm_head_accept": ("gemm_stream_kernel<1", "accept_finalize_kernel"),
+                         "rel_cand_kernel", "rel_merge_kernel", "rel_keep_kernel",
+                         "rel_take_kernel"),
+    "lm_head_accept": ("gemm_stream_kernel<1", "lm_head_wide_kernel", "accept_finalize_kernel",
+                       "accept_merge_kernel", "accept_rule_kernel"),
+    "kv_commit": ("kv_commit_kernel",),
+    "hv_prepare": ("hv_prepare_kernel",),
+}
+# of these, the kernels that stream, by the start of their names
+STREAMS = {
+    "verify_attn": ("attn_split_kernel", "attn_flat_kernel"),
+    "visual_relevance": ("gemm_stream_kernel<0", "gemm_stream_kernel<2"),
+    "lm_head_accept": ("gemm_stream_kernel<1", "lm_head_wide_kernel"),
 }
 CALIBRATION_KERNEL = "CUDAFunctorOnSelf_add<int>"
 GIB = float(1 << 30)
@@ -201,7 +218,8 @@ def summary(run_dir: str, out_dir: str, workloads: list) -> None:
         tr[name + ":kernels"] = t[name + ":kernels"]
         ratio = "\n".join(
             f"  {k}: measured {t[name][k]:,} B, algorithmic {bench['rooflines'][k]['algorithmic_bytes']:,} B, "
-            f"ratio {t[name][k] / bench['rooflines'][k]['algorithmic_bytes']:.3f}" for k in t[name])
+            f"ratio {t[name][k] / bench['rooflines'][k]['algorithmic_bytes']:.3f}"
+            for k in bench["rooflines"])
         open(os.path.join(out_dir, f"hbm_counters_{w}.txt"), "w").write(
             f"rocprofv3 HBM byte counters, workload {name} (bench.py {flags}), MI355X, one GPU, commit {commit}.\n\n"
             "Commands (run from /tmp with TMPDIR=/tmp, repository at $R; one counter per run):\n"
@@ -216,13 +234,12 @@ def summary(run_dir: str, out_dir: str, workloads: list) -> None:
             + _own(counters(db("write"), "WRITE_SIZE"), True) + "\n\n"
             "HBM bytes per library call (fetch + write, scaled) vs algorithmic bytes:\n" + ratio + "\n")
         tab = mfma_table(db("mfma"))
-        key = {"verify_attn": ("attn_split_kernel", "attn_flat_kernel"), "visual_relevance": "gemm_stream_kernel<0",
-               "lm_head_accept": "gemm_stream_kernel<1"}
         tr[name + ":mfma"] = {
             k: {"kernel": r["kernel"], "mfma_flops_per_launch": round(r["mfma_flops_per_launch"]),
                 "frac_of_bf16_peak": round(r["frac_of_bf16_peak"], 4),
                 "mfma_busy_frac": round(r["mfma_busy_frac"], 4)}
-            for k, pref in key.items() for r in tab if r["kernel"].startswith(pref)}
+            for k, pref in STREAMS.items()
+            for r in [x for x in tab if x["kernel"].startswith(pref)][:1]}   # the one with most flops
         open(os.path.join(out_dir, f"mfma_counters_{w}.txt"), "w").write(
             f"rocprofv3 matrix-core counters, workload {name} (bench.py {flags}), MI355X, one GPU, commit {commit}.\n\n"
             "Command (run from /tmp with TMPDIR=/tmp, repository at $R):\n"
@@ -275,6 +292,56 @@ def lds(db_path: str) -> str:
     return "\n".join(out)
 
 
+def _case(name: str):
+    import importlib.util
+    import os
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    sys.path.insert(0, root)
+    spec = importlib.util.spec_from_file_location("cases", os.path.join(root, "perf", "cases.py"))
+    cases = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(cases)
+    return cases, next(c for c in cases.listed() if c["name"] == name)
+
+
+def run_case(name: str, passes: int, calibrate: bool) -> None:
+    import torch
+    cases, case = _case(name)
+    state = cases.prepare(case, 1)
+    if calibrate:
+        src = torch.zeros((1 << 28,), dtype=torch.int32, device="cuda")       # 1 GiB
+        torch.add(src, 1, out=torch.empty_like(src))
+    for _ in range(passes):
+        cases.run(state)
+    torch.cuda.synchronize()
+
+
+def case_summary(run_dir: str, out_dir: str, names: list) -> None:
+    import json
+    import os
+    ours = tuple(k.split("<")[0] for ks in GROUPS.values() for k in ks)
+    own = lambda text: "\n".join(l for i, l in enumerate(text.split("\n"))
+                                 if i == 0 or l.split()[0].split("<")[0] in ours)
+    run = "python3 -m paper_2604_05650_amd.profiling run-case"
+    for name in names:
+        db = lambda kind: os.path.join(run_dir, f"{kind}_{name}_results.db")
+        cases, case = _case(name)
+        t = json.loads(traffic(db("fetch"), db("write"), name))
+        calls = {k: v for k, v in t[name].items() if v}
+        open(os.path.join(out_dir, f"case_{name}.txt"), "w").write(
+            f"rocprofv3 runs of the case {name} of perf/cases.py, MI355X, one GPU, commit "
+            f"{os.environ.get('LVSPEC_COMMIT')}.\n\n"
+            "Commands (from /tmp with TMPDIR=/tmp, PYTHONPATH at the repository):\n"
+            f"  rocprofv3 --kernel-trace --stats -d <out> -o kt_{name} -- {run} {name} 20\n"
+            f"  rocprofv3 --pmc <counters> -d <out> -o <set>_{name} -- {run} {name} 5 [--calibrate-copy]\n"
+            f"  python -m paper_2604_05650_amd.profiling case-summary <out> profiles {name}\n\n"
+            "Durations (us; the profiler's bookkeeping lengthens short launches):\n"
+            + own(kernels(db("kt"))) + "\n\nHBM bytes per launch of each kernel, summed (counters scaled by a 1 GiB copy;\n"
+            f"one pass cannot do without {cases.work(case)['bytes']:,.0f} bytes in {case['layers']} layer(s)):\n"
+            + "\n".join(f"  {k}: {v:,}" for k, v in calls.items())
+            + "\n\nMatrix cores:\n" + mfma(db("mfma")) + "\n\nLDS (per launch, summed over the chip):\n"
+            + own(lds(db("lds"))) + "\n")
+
+
 def _unprofiled(run_dir: str, w: str) -> str:
     """per-call figures of the same command without the profiler, when that run is there"""
     import json
@@ -292,6 +359,12 @@ def _unprofiled(run_dir: str, w: str) -> str:
 if __name__ == "__main__":
     if len(sys.argv) >= 5 and sys.argv[1] == "summary":
         summary(sys.argv[2], sys.argv[3], sys.argv[4:])
+        sys.exit(0)
+    if len(sys.argv) >= 4 and sys.argv[1] == "run-case":
+        run_case(sys.argv[2], int(sys.argv[3]), "--calibrate-copy" in sys.argv)
+        sys.exit(0)
+    if len(sys.argv) >= 5 and sys.argv[1] == "case-summary":
+        case_summary(sys.argv[2], sys.argv[3], sys.argv[4:])
         sys.exit(0)
     if len(sys.argv) >= 5 and sys.argv[1] == "traffic":
         print(traffic(sys.argv[2], sys.argv[3], sys.argv[4]))

@@ -60,3 +60,19 @@ def test_mfma_utilisation(tmp_path):
     assert abs(tab[0]["frac_of_bf16_peak"] - 0.05369) < 1e-4
     assert abs(tab[0]["mfma_busy_frac"] - 0.05) < 1e-6
     assert "attn_split_kernel" in P.mfma(db)
+
+
+def test_every_kernel_of_the_library_belongs_to_a_call():
+    # a kernel that no group names would be missing from the bytes of its call without a word
+    import glob
+    import os
+    import re
+    here = os.path.dirname(os.path.abspath(P.__file__))
+    names = set()
+    for path in glob.glob(os.path.join(here, "csrc", "*.hip")):
+        names |= set(re.findall(r"__global__\s+(?:__launch_bounds__\([^{;]*?\)\s+)?void\s+(\w+)\(",
+                                open(path).read()))
+    assert len(names) >= 16 and "lm_head_wide_kernel" in names
+    groups = {k.split("<")[0] for kernels in P.GROUPS.values() for k in kernels}
+    assert names == groups
+    assert all(set(P.STREAMS[call]) <= set(P.GROUPS[call]) for call in P.STREAMS)
