@@ -144,12 +144,19 @@ def _avg_by_kernel(db_path: str, counter: str) -> dict:
     return {n: v for n, v in rows}
 
 
+def _calibration(db_path: str, counter: str) -> float:
+    """The reading of the 1 GiB copy: the largest of its kernel's (small tensors may be added, too)."""
+    cur = sqlite3.connect(db_path).cursor()
+    return cur.execute("select max(value) from counters_collection where counter_name = ? and "
+                       "kernel_name like ?", (counter, f"%{CALIBRATION_KERNEL}%")).fetchone()[0]
+
+
 def traffic(fetch_db: str, write_db: str, workload: str) -> str:
     import json
     fetch = _avg_by_kernel(fetch_db, "FETCH_SIZE")
     write = _avg_by_kernel(write_db, "WRITE_SIZE")
-    cal_f = next(v for n, v in fetch.items() if CALIBRATION_KERNEL in n)
-    cal_w = next(v for n, v in write.items() if CALIBRATION_KERNEL in n)
+    cal_f = _calibration(fetch_db, "FETCH_SIZE")
+    cal_w = _calibration(write_db, "WRITE_SIZE")
     res = {"calibration": {"kernel": "torch.add on 2^28 int32 (reads 1 GiB, writes 1 GiB)",
                            "FETCH_SIZE_reading": cal_f, "WRITE_SIZE_reading": cal_w,
                            "bytes_per_FETCH_SIZE_unit": GIB / cal_f,

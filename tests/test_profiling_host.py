@@ -76,3 +76,13 @@ def test_every_kernel_of_the_library_belongs_to_a_call():
     groups = {k.split("<")[0] for kernels in P.GROUPS.values() for k in kernels}
     assert names == groups
     assert all(set(P.STREAMS[call]) <= set(P.GROUPS[call]) for call in P.STREAMS)
+
+
+def test_small_additions_do_not_move_the_calibration(tmp_path):
+    dbs = {}
+    for kind, unit in (("FETCH_SIZE", 2048), ("WRITE_SIZE", 1024)):
+        dbs[kind] = str(tmp_path / kind)
+        _db(dbs[kind], counters=[(ADD, kind, float((1 << 30) // unit), 1), (ADD, kind, 1.0, 1),
+                                 (SPLIT, kind, 1000.0, 1)])
+    t = json.loads(P.traffic(dbs["FETCH_SIZE"], dbs["WRITE_SIZE"], "wl"))
+    assert t["wl"]["verify_attn"] == 1000 * (2048 + 1024)
