@@ -799,15 +799,12 @@ int lmh_records(int n_cols, int n_tasks, int num_cu) {
 // faster than 128-row stages with two slots (d = 2048 .. 7168), except at row pitches that are
 // multiples of 8 KiB (d = 4096, 8192), where the 64 segments of a stage fall into too few HBM
 // channels (d = 4096, five columns: 5.6 against 6.4 TB/s).  More columns: 128 rows (half the X
-// traffic per lm_head byte), unless 64-row tasks leave clearly fewer rows to the busiest CU.
+// traffic per lm_head byte), unless 64-row tasks give every CU one at most and 128-row tasks would
+// leave half of them idle.  d = 5120, 96 columns, 64 and 128 rows: V = 8192 54.0 and 68.6 us, 16384
+// 59.7 and 71.2; 24000 101 and 75, 36000 144 and 132 (although 128 rows leave the busiest CU a third
+// more), 152064 427 and 326; d = 1024, 36 columns: 16384 20.9 and 22.1, 24000 31.0 and 25.2.
 int lmh_block_rows(int n_cols, int64_t row_pitch_bytes, int n_rows, int num_cu) {
-  if (n_cols >= kWideCols) {
-    auto per_cu = [&](int rows) {
-      const int64_t tasks = ((int64_t)n_rows + rows - 1) / rows;
-      return (tasks + num_cu - 1) / num_cu * rows;
-    };
-    return per_cu(64) * 5 < per_cu(128) * 4 ? 64 : 128;
-  }
+  if (n_cols >= kWideCols) return n_rows <= 64 * num_cu ? 64 : 128;
   return row_pitch_bytes % 8192 == 0 ? Geo<2, 1, 256>::kRowsWg : Geo<1, 1, 256>::kRowsWg;
 }
 

@@ -300,3 +300,17 @@ def test_planning_from_several_threads(L):
     for t in threads:
         t.join()
     assert not errs and len(got) == 1600 and set(got) == {want}
+
+
+def test_wide_lm_head_stages(L):
+    # from 33 hidden rows on: 64-row stages where they give every CU one at most, 128 rows above;
+    # the workspace holds one record of (8 + 8 k) bytes per workgroup and hidden row
+    lib = L.raw()
+    for V, rows, workgroups in ((8192, 64, 128), (16384, 64, 256), (16385, 128, 129),
+                                (36000, 128, 141), (152064, 128, 238)):
+        tasks = -(-V // rows)
+        assert workgroups == -(-tasks // -(-tasks // 256))
+        a = _acc(L, B=16, bonus_row=1, hd_sb=6 * 5120, V=V)
+        rec = workgroups * 96
+        want = sum(-(-rec * n // 256) * 256 for n in (8, 8 * 4, 4))
+        assert lib.lvspec_loose_accept_workspace(C.byref(a)) == want, V

@@ -22,6 +22,7 @@ pytestmark = pytest.mark.gpu
     (12, 5, 1, True, 33000, 256, 4),      # two groups of 36 columns
     (17, 5, 1, False, 65, 128, 16),       # two groups of 45 and 40, one row beyond a block
     (8, 16, 1, False, 40001, 128, 2),     # 128 columns
+    (8, 16, 1, False, 16384, 128, 4),     # ... in 64-row blocks, the most there are of them
     (26, 5, 1, False, 33000, 256, 4),     # three groups: a full pass and a narrower one
     (6, 10, 2, True, 20001, 256, 4),      # trees: two groups of four and two chains
     (14, 5, 1, False, 8192, 128, 4),      # two groups of 35, 64-row blocks
