@@ -77,6 +77,15 @@ int lvspec_last_hip_error(void);
  * Draft trees (appendix on draft token trees): the rows of all chains are stored one after the
  * other, gamma counts them all, and draft_mask says which rows a row sees (for two independent
  * chains: a block-diagonal lower-triangular pattern).
+ * Batches: with 2 <= B <= 64 the keys of all sequences are divided evenly over the chip, so where a
+ * sequence's keys are cut, and with that the rounding of its bf16 probabilities (a relative 2e-3 of
+ * the result), follows from the lengths of all sequences, from the shapes and from max_kv_len; not
+ * from where the lengths are given.  A workspace that holds no more than
+ * B * Hkv * attn_row_chunks * attn_splits * attn_rows_padded * 131 * 4 bytes (lvspec_describe_plan;
+ * it may be less than lvspec_verify_attn_workspace asks for, and is accepted) is served by equal
+ * splits instead: a sequence's bits then follow from its own data and length, the shapes and
+ * max_kv_len alone, and a batch takes as long as its longest sequence.  One sequence, a batch of
+ * equal lengths and a batch of short ones are cut into equal splits in any case.
  * ------------------------------------------------------------------------------------------- */
 typedef struct {
   int32_t B, gamma, Hq, Hkv, D;     /* D must be 128; Hq % Hkv == 0; 1 <= gamma <= 32 */
@@ -317,7 +326,9 @@ typedef struct {
                                     pass holds half of one, one, or two); the rows of a task
                                     add their products up in one order */
   int32_t acc_chains_per_pass;   /* chains of a group (up to 64 hidden rows) */
-  int32_t acc_passes;            /* groups; two of them share one pass over lm_head */
+  int32_t acc_passes;            /* number of groups.  Both names are of a time when a group had a
+                                    pass to itself: now two groups share one, and lm_head is
+                                    read (acc_passes + 1) / 2 times */
 } lvspec_plan_info;
 
 int lvspec_describe_plan(const lvspec_attn_args* attn, const lvspec_rel_args* rel,

@@ -390,8 +390,8 @@ int enqueue_attn(const lvspec_attn_args* a, const AttnPlan& pl, void* workspace,
   k.scale_log2e = scale * 1.4426950408889634f;
   k.ws = static_cast<float*>(workspace);
   // several sequences share one line of tiles; a workspace that holds only the partials of equal
-  // splits is served by those.  The choice never looks at the lengths: results are the same
-  // bits whether the host knows them or not.
+  // splits is served by those.  The choice goes by the shapes, max_kv_len and the workspace, never
+  // by kv_len_host: results are the same bits whether the host knows the lengths or not.
   constexpr int64_t kMaxStride = (int64_t)8 << 32;     // travels as a 32-bit number of 8 elements
   k.flat_pos = have >= pl.ws_bytes && a->kv_sb < kMaxStride && a->kv_sh < kMaxStride &&
                        a->kv_sl < kMaxStride ? pl.flat_pos : 0;

@@ -1,5 +1,5 @@
 // Streamed skinny GEMM for gfx950: C[r][c] = sum_t A[r][t] X[c][t] with A a tall bf16 matrix read
-// exactly once from HBM and X at most 64 bf16 rows.  Two users:
+// exactly once from HBM and X at most 128 bf16 rows.  Two users:
 //   relevance (paper Eq. 8):  A = video hidden states H_V [l_v, d], X = draft hidden states
 //       H_D [gamma, d]; the kernel emits raw dot products and squared row norms per split of d;
 //       a finalize kernel turns them into cosines and the mean of the Top-N.
@@ -173,8 +173,8 @@ LVS_DEV void setup_task(const GemmKernelArgs& p, Cursor& c, IssuePtrs<MB, NBX, R
 // segments spread over all HBM channels (with a power-of-two row pitch, e.g. d = 8192, all
 // rows of a column chunk fall into the same few channels).  The order is a fixed function of
 // the task, so results stay reproducible.  lm_head: of the block of 64 (rot_shift = 0) or 128
-// vocabulary rows, whatever the rows of a stage: a logit's bits, and with them the order of
-// tokens that nearly tie, do not depend on the kernel that took the row.
+// vocabulary rows (lmh_order_rows), whatever the rows of a stage: a logit's bits, and with them the
+// order of tokens that nearly tie, do not depend on the stage size or on which rows share the call.
 template <int MB, int NBX, int RB>
 LVS_DEV void issue_stage(const IssuePtrs<MB, NBX, RB>& ip, int kc, int n_chunks, uint32_t slot,
                          int wave) {
@@ -223,7 +223,7 @@ LVS_DEV void wait_stages(int ahead) {
 // the maximum and the sums of the rows it has seen (no cross-lane work per task), lane r the r-th
 // best candidate of the whole wave.  Per task only the rows that beat the k-th best so far cost a
 // selection round (about k/t of task t's rows do), where every task used to run k rounds of its own
-// and write k candidates: five columns, V = 152064: 2376 records per column before, 475 now; the
+// and write k candidates: five columns, V = 152064: 2376 records per column before, 476 now; the
 // pass itself 228.5 -> 223.6 us at d = 5120, with 48 columns 333 -> 307, with k = 16 (d = 3584)
 // 177 -> 163.
 struct ColumnState {
@@ -512,13 +512,15 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(const GemmKernelArg
 }
 
 // ---- lm_head for 33 to 128 hidden rows ------------------------------------------------------------
-// A server's batch brings more hidden rows than the kernel above can hold next to its ring: with 33
-// to 64 columns it keeps one stage in flight (two slots), and more columns meant another pass over
-// lm_head.  Here one workgroup of eight waves has the CU to itself: 64 * MB vocabulary rows by two
+// A server's batch brings more hidden rows than the kernel above can hold next to its ring: with more
+// than 32 columns half of a CU's LDS would leave room for one stage in flight (two slots).  Here
+// one workgroup of eight waves has the CU to itself: 64 * MB vocabulary rows by two
 // column halves of 16 * NB2, waves 4 (row groups of 16 * MB) x 2 (halves), so that a wave feeds
 // MB * NB2 independent accumulators from MB + NB2 operands per step and every X byte in LDS is
-// read by four waves instead of eight.  What bounds it besides HBM is the LDS: per 32 KiB of
-// lm_head (3050 cycles at 6.6 TB/s) 128 columns write 64 and read 192 KiB (2000 cycles).
+// read by four waves instead of eight.  No unit is what bounds it: with 96 columns (4.8 TB/s) the
+// counters show the LDS active for 15 % of the cycles, without bank conflicts, and the matrix cores busy
+// for 18 %.  (Read from the code, not measured: a stage is 32 KiB of lm_head and 24 KiB of X per CU and
+// ends on a barrier that waits for the slowest of eight waves' copies, with two stages in flight.)
 //
 // Rings: three slots of A (two stages in flight) and two of X (it comes from L2).  Copies complete
 // in issue order, so X(i+1) is issued ahead of A(i+2) and the wait for X(i) leaves A(i+1) out.
@@ -808,8 +810,13 @@ int lmh_block_rows(int n_cols, int64_t row_pitch_bytes, int n_rows, int num_cu) 
   return row_pitch_bytes % 8192 == 0 ? Geo<2, 1, 256>::kRowsWg : Geo<1, 1, 256>::kRowsWg;
 }
 
-// A matter of results, not of speed: other rows here are other 32-bit sums.  20480 was once the
-// number of candidates that the merge held.
+// Part of the results: another block is another order of a logit's 32-bit sum (6e-6 apart, enough to
+// swap tokens that nearly tie).  These are the blocks that the logits have had since the first
+// release, when a block was also a task: 64 rows, but 128 for up to 32 hidden rows of a call where the
+// row pitch asked for larger tasks, or where 64-row tasks would have left more candidates than a
+// merge of that time could hold (20480).  So a row's logits are the same in every call of up to 32
+// hidden rows with the same k, and in every call of more; between the two they may differ at
+// d = 4096 and 8192 and, with V = 152064, at k above 8.
 int lmh_order_rows(int n_cols, int64_t row_pitch_bytes, int n_rows, int topk) {
   if (n_cols >= kWideCols) return 64;
   const int64_t blocks64 = ((int64_t)n_rows + 63) / 64;

@@ -161,3 +161,33 @@ def test_chains_of_a_tree_are_judged_as_chains(S, n_br, K, bonus, V):
         assert tree["best_branch"].cpu().tolist() == taus.argmax(1).tolist()
         seen |= set(chains["verdict"].unique().tolist())
     assert seen >= {0, 1, 2}
+
+
+@pytest.mark.parametrize("V,d,topk", [(5000, 4096, 4), (5000, 8192, 4), (152064, 128, 16), (152064, 128, 4)])
+def test_logits_in_calls_of_few_and_of_many_rows(V, d, topk):
+    # where the order of the sums is another one for up to 32 hidden rows (row pitches of 8 KiB, many
+    # candidates): the same bits in every call of up to 32 rows, and in every call of more
+    from paper_2604_05650_amd import binding as L
+    B, K = 20, 4
+    h = t_bf16(synth.normal_bf16((617, V, d, 0), (B, K, d), 1.0))
+    w = t_bf16(synth.normal_bf16((617, V, d, 1), (V, d), 0.1))
+
+    def logits(chains):
+        n = len(chains)
+        outs = L.loose_accept(h[chains].contiguous(), w, t_i32(np.zeros((n, K))), t_f32(np.zeros((n, K))),
+                              0, 0, topk=topk, return_logits=True)
+        return outs["logits"], outs["topk_ids"]
+
+    few, few_ids = logits([0])                                   # 4 rows
+    for chains in ([3, 0], [5, 1, 2, 6, 0], list(range(7, -1, -1))):     # 8, 20, 32
+        z, ids = logits(chains)
+        assert torch.equal(z[-1], few[0]) and torch.equal(ids[-1], few_ids[0])
+    many, many_ids = logits(list(range(8, -1, -1)))              # 36: both halves of one group
+    for chains in (list(range(15, -1, -1)), list(range(19, -1, -1))):    # 64; 80: two groups
+        z, ids = logits(chains)
+        assert torch.equal(z[-1], many[-1]) and torch.equal(ids[-1], many_ids[-1])
+    # two orders of the same 32-bit sum
+    scale = (h[0].float().abs() @ w.float().abs().T).max().item()
+    assert (few[0] - many[-1]).abs().max().item() <= 2 * d * 2.0 ** -24 * scale
+    if topk <= 4 and d < 4096:
+        assert torch.equal(few[0], many[-1])
