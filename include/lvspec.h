@@ -84,8 +84,7 @@ int lvspec_last_hip_error(void);
  * B * Hkv * attn_row_chunks * attn_splits * attn_rows_padded * 131 * 4 bytes (lvspec_describe_plan;
  * it may be less than lvspec_verify_attn_workspace asks for, and is accepted) is served by equal
  * splits instead: a sequence's bits then follow from its own data and length, the shapes and
- * max_kv_len alone, and a batch takes as long as its longest sequence.  One sequence, a batch of
- * equal lengths and a batch of short ones are cut into equal splits in any case.
+ * max_kv_len alone, and a batch takes as long as its longest sequence.
  * ------------------------------------------------------------------------------------------- */
 typedef struct {
   int32_t B, gamma, Hq, Hkv, D;     /* D must be 128; Hq % Hkv == 0; 1 <= gamma <= 32 */
@@ -327,8 +326,8 @@ typedef struct {
                                     add their products up in one order */
   int32_t acc_chains_per_pass;   /* chains of a group (up to 64 hidden rows) */
   int32_t acc_passes;            /* number of groups.  Both names are of a time when a group had a
-                                    pass to itself: now two groups share one, and lm_head is
-                                    read (acc_passes + 1) / 2 times */
+                                    pass to itself: now two groups share one where the
+                                    workspace is as large as asked for */
 } lvspec_plan_info;
 
 int lvspec_describe_plan(const lvspec_attn_args* attn, const lvspec_rel_args* rel,

@@ -264,3 +264,25 @@ def test_wide_top_n_slices(lv, d, N, kind):
         h_v[0] = h_v[0][np.argsort(-dots)]
     # the second sequence ends inside a slice, and there are slices past its end
     _check(h_d, h_v, [lv, 50 if kind == "short" else lv * 2 // 5], N, f"wide lv{lv} d{d} N{N} {kind}")
+
+
+@pytest.mark.parametrize("lv,d,N,splits", [
+    (4096, 1024, 100, 2),        # the one kernel
+    (4097, 128, 17, 1),          # slices of 1024 rows, the last of one row
+    (4097, 1024, 128, 2),
+    (4097, 2560, 100, 5),
+    (14336, 512, 100, 1),
+    (20481, 256, 100, 1),        # slices of 4096 rows
+])
+def test_prepared_wide_top_n(lv, d, N, splits):
+    # two sequences, so that the second one's norms lie lv_max behind the first one's; the second ends
+    # inside a slice, and slices lie past its end; a row of zeros among the candidates
+    from paper_2604_05650_amd import binding as L
+    a = L.RelArgs()
+    a.B, a.gamma, a.d, a.top_n, a.lv_max = 2, 3, d, N, lv
+    assert L.describe_plan(rel=a)["rel_splits"] == splits
+    h_d = synth.normal_bf16((213, lv, d, 0), (2, 3, d), 1.0)
+    h_v = synth.normal_bf16((213, lv, d, 1), (2, lv, d), 1.0)
+    h_v[1] = synth.f32_to_bf16_bits(4.0 * synth.bf16_bits_to_f32(h_v[1]))   # other norms
+    h_v[:, 7] = 0
+    _check_prepared(h_d, h_v, [lv, lv * 2 // 5], N, f"wide lv{lv} d{d} N{N}")
