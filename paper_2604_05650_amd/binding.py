@@ -177,10 +177,11 @@ def _check(status: int):
         raise LvspecError(status)
 
 
-# The functions below prepare a call in as few steps as the interpreter needs: new_empty of an input
-# takes 3.6 us where torch.empty takes 4.5, one stride() 0.4 us where one per dimension takes 1.5, and
-# an array assigned to a pointer field 0.7 us where ctypes.cast takes 6.4 (a smallest step of three
-# calls from Python: 70.6 -> 63.9 us).
+# What a call costs in the interpreter: new_empty of an input takes 3.6 us where torch.empty takes
+# 4.5 (outputs and workspaces of the three verify calls), one stride() 0.4 us where one per dimension
+# takes 1.5 (verify_attn_args), and an array assigned to a pointer field 0.7 us where ctypes.cast takes
+# 6.4.  A smallest step of three calls from Python: 72 -> 67 us.  The other argument functions read
+# a stride at a time, and kv_commit allocates with torch.empty.
 def _workspace(nbytes: int, like: torch.Tensor, workspace: Optional[torch.Tensor]) -> torch.Tensor:
     if workspace is not None:
         return workspace

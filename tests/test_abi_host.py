@@ -249,16 +249,16 @@ def test_launch_planning(L):
     assert L.describe_plan(rel=_rel(L, lv_max=1 << 21, hv_sb=(1 << 21) * 5120))["rel_slices"] == 0
     assert L.describe_plan(rel=_rel(L, top_n=100))["rel_slices"] == 0
     # lm_head: 64-row tasks at d = 5120, 128-row tasks at a row pitch that is a multiple of
-    # 8 KiB, or when the merge kernel could not keep the candidates in registers (top-k > 8)
+    # 8 KiB, or with many candidates (V = 152064: top-k > 8); these rows share an order of summation
     assert L.describe_plan(accept=_acc(L)) == dict(acc_rows_per_task=64, acc_chains_per_pass=1,
                                                    acc_passes=1)
     assert L.describe_plan(accept=_acc(L, d=8192, hd_sb=5 * 8192, hd_sg=8192))[
         "acc_rows_per_task"] == 128
     assert L.describe_plan(accept=_acc(L, topk=16))["acc_rows_per_task"] == 128
     assert L.describe_plan(accept=_acc(L, topk=8))["acc_rows_per_task"] == 64
-    # four chains of eight tokens: 32 rows in one pass; with bonus rows 36 -> the 48-column
-    # variant, still one pass; nine chains of five with bonus rows: 54 rows, one pass; twelve:
-    # two passes of six chains
+    # four chains of eight tokens: 32 rows in one group; with bonus rows 36, still one group; nine
+    # chains of five with bonus rows: 54 rows, one group; twelve: two groups of six chains (which
+    # share a pass over lm_head; acc_passes counts groups)
     c5a = dict(B=4, gamma=8, d=8192, hd_sb=8 * 8192, hd_sg=8192, n_loose=5, pst_window=8)
     assert L.describe_plan(accept=_acc(L, **c5a)) == dict(
         acc_rows_per_task=128, acc_chains_per_pass=4, acc_passes=1)

@@ -87,3 +87,65 @@ def test_captured_step_replays_bit_exact():
     g_out = out.float().cpu().numpy().astype(np.float64)
     err = np.abs(g_out - o_out).max(-1) / np.abs(o_out).max(-1)
     assert err.max() <= 1e-2
+
+
+def test_captured_batch_follows_the_lengths_on_the_device():
+    # a batch whose lengths change between replays: on the line over all sequences, in equal splits
+    # because they are short, and because they are equal; relevance with a wide Top-N; trees of 24
+    # hidden rows per sequence, 48 in the call
+    from paper_2604_05650_amd import binding as L
+    lib = L.raw()
+    B, gamma, Hq, Hkv, D, cap, d, V, lv = 6, 5, 16, 4, 128, 4000, 256, 9000, 5000
+    q = t_bf16(synth.normal_bf16((901, 0), (B, gamma, Hq, D), 1.0))
+    k = t_bf16(synth.normal_bf16((901, 1), (B, Hkv, cap, D), 1.0))
+    v = t_bf16(synth.normal_bf16((901, 2), (B, Hkv, cap, D), 1.0))
+    h_v = t_bf16(synth.normal_bf16((901, 3), (2, lv, d), 1.0))
+    h_d = t_bf16(synth.normal_bf16((901, 4), (2, 24, d), 1.0))
+    w = t_bf16(synth.normal_bf16((901, 5), (V, d), 0.1))
+    kv_len, l_v = t_i32([cap - gamma] * B), t_i32([lv, lv])
+    draft = t_i32(np.random.default_rng(901).integers(0, V, (6, 8)))
+    out = torch.empty_like(q)
+    rel = torch.empty((2, 24), dtype=torch.float32, device=dev())
+    outs = L.alloc_accept_outputs(6, 8, V, 4, dev(), n_branches=3)
+    aa = L.verify_attn_args(q, k, v, kv_len, out=out)
+    ra = L.visual_relevance_args(h_d, h_v, l_v, 40, relevance=rel)
+    ca = L.loose_accept_args(h_d.view(6, 8, d), w, draft, rel.view(6, 8), 3, 8, topk=4,
+                             loose_topk_gate=0, outs=outs, n_branches=3)
+    calls = ((aa, "verify_attn"), (ra, "visual_relevance"), (ca, "loose_accept"))
+    keep = []
+    for a, name in calls:
+        ws = torch.empty((getattr(lib, f"lvspec_{name}_workspace")(C.byref(a)),), dtype=torch.uint8,
+                         device=dev())
+        a.workspace, a.workspace_bytes = ws.data_ptr(), ws.numel()
+        keep.append(ws)
+
+    def enqueue(stream):
+        for a, name in calls:
+            assert getattr(lib, f"lvspec_{name}")(C.byref(a), stream.cuda_stream) == 0
+
+    def snapshot():
+        torch.cuda.synchronize()
+        return [t.clone() for t in (out, rel, *outs.values())]
+
+    enqueue(torch.cuda.current_stream())
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(g, stream=side):
+            enqueue(side)
+    for lens in ([3900, 10, 777, 0, 2000, 64], [200, 90, 0, 300, 31, 5], [3800] * B,
+                 [1, 3995, 3995, 2, 3, 3000]):
+        kv_len.copy_(t_i32(lens))
+        l_v.copy_(t_i32([lens[0], lv]))
+        enqueue(torch.cuda.current_stream())
+        want = snapshot()
+        for t in (out, rel, *outs.values()):
+            t.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        for a, b in zip(snapshot(), want):
+            assert torch.equal(a, b), lens
+    o_out, _, _ = oracle.verify_attn(*(synth.from_torch_bf16(t) for t in (q, k, v)), lens)
+    err = np.abs(out.float().cpu().numpy() - o_out).max(-1) / np.abs(o_out).max(-1)
+    assert err.max() <= 1e-2
