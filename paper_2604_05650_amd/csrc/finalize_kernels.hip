@@ -824,17 +824,18 @@ constexpr int kRelOneKernelRows = 4096;
 // Two-kernel Top-N for 16 < N <= 128 and 4097 to 65536 video rows.  One CU that reads a row's dot products
 // and norms alone is bound by its own requests in flight (rel_finalize_kernel: 230 KB at 14336 rows
 // in two splits), and the scores are needed once: so a workgroup per (slice, draft row) makes the
-// scores of 1024 (4096) video rows and leaves those that can be among the N largest, and one workgroup per
-// draft row selects among these.  At least N scores reach the N-th largest of the threads' maxima
-// (all scores, where there are fewer maxima than N).  The kept keys take the slice's places
-// of the cosine plane, their number the place of the slice's first dot product, which no one else
-// reads.  Scores rank like cosines and the N winners are the same, see rel_cand_kernel.
+// scores of 1024 (4096) video rows and leaves those that can be among the N largest, and one
+// workgroup per draft row selects among these.  At least N scores reach the N-th largest of the
+// threads' maxima (all scores, where there are fewer maxima than N).  The kept keys take the slice's
+// places of the cosine plane, their number the place of the slice's first dot product, which no one
+// else reads.  Scores rank like cosines and the N winners are the same, see rel_cand_kernel.
 // Both kernels are chains of latencies.  Per call against rel_finalize_kernel, N = 100: 14336 rows,
-// d = 5120, 5 draft rows (two splits) 42.6 -> 38.4 us; d = 1024: 8192 rows 20.5 -> 18.8, 63488 rows
-// 49.8 -> 34.4, 8 x 30000 rows with 8 draft rows each 100 -> 92.  Up to 4096 rows the kernels gain
-// about 1 us (4096 rows 18.7 -> 17.6) and a caller that is bound by its launches loses more on
-// the third (234 rows from Python 18.5 -> 20.2).  N > 128: a slice would keep most of its scores, and selecting among more than are
-// held in LDS costs more than the one kernel (N = 1000, 14336 rows: 26.7 us there, 34.3 here).
+// d = 5120, 5 draft rows (two splits) 42.6 -> 38.1 us; d = 1024: 8192 rows 20.5 -> 18.8, 63488 rows
+// 49.8 -> 34.4, 8 x 30000 rows with 8 draft rows each 100 -> 92; also where few of the rows are in use
+// (100 of 14336: 17.0 -> 12.7).  Up to 4096 rows the kernels gain about 1 us (4096 rows 18.7 -> 17.6)
+// and a caller that is bound by its launches loses more on the third (234 rows from Python 18.5 ->
+// 20.2).  N > 128: a slice would keep most of its scores, and selecting among more than are held in
+// LDS costs more than the one kernel (N = 1000, 14336 rows: 26.7 us there, 34.3 here).
 template <int NS, int M>
 __global__ __launch_bounds__(256) void rel_keep_kernel(const RelFinalizeArgs p) {
   __shared__ uint32_t tmax[256];
