@@ -611,6 +611,13 @@ LVS_DEV void attn_segment(const Args& p, uint8_t* smem, int lane, int wave, int 
   }
 }
 
+// Registers are limited to half of a SIMD's in every variant.  Left with all 512 for its one wave per
+// SIMD, the compiler puts the accumulators of the 16-row variant into the accumulation registers and
+// moves all of them through ordinary ones for every tile's rescaling: 16384 keys, 40 / 8 heads, 1 and
+// 3 draft rows 16.0 and 16.4 us with it, 15.7 and 16.0 without; 7296 keys, 64 / 8 heads, 2 rows 11.9 and 11.2.
+template <int RS>
+constexpr int kWavesPerSimd = RS == 1 ? 2 : 1;
+
 // Fast start.  All waves of all workgroups read the same few lines of the argument buffer when
 // the kernel starts, and that read is slow (in-kernel timestamps: the first wave has its
 // arguments 0.9 us after entry, the median wave after 2.5 us, the last after 4 us), so the
@@ -628,7 +635,7 @@ LVS_DEV void attn_segment(const Args& p, uint8_t* smem, int lane, int wave, int 
 // The structure behind them is then first needed for the query rows, behind the first copies.
 // In every other case (fast = 0) the kernel starts from the structure as before.
 template <int RS, int NBW>
-__global__ __launch_bounds__(256 * RS, 1) void attn_split_kernel(
+__global__ __launch_bounds__(256 * RS, kWavesPerSimd<RS>) void attn_split_kernel(
     const uint16_t* k0, const uint16_t* v0, int64_t kv_sh0, int kv_sl0, int n_split0,
     uint32_t split_mul0, int Hkv0, uint32_t hkv_mul0, uint32_t packed0, int len0,
     const AttnKernelArgs p) {
@@ -850,7 +857,7 @@ constexpr int kFlatArgsOffset = 56;
 // A workgroup per (stretch, row chunk); the row chunks of a stretch share an XCD's L2.  Strides in
 // units of eight elements; rc_mul_splits: ceil(32768 / n_rc), and `splits` from bit 16.
 template <int RS, int NBW>
-__global__ __launch_bounds__(256 * RS, 1) void attn_flat_kernel(
+__global__ __launch_bounds__(256 * RS, kWavesPerSimd<RS>) void attn_flat_kernel(
     const uint16_t* k0, const uint16_t* v0, uint32_t sb8, uint32_t sh8, uint32_t sl8,
     uint32_t packed, uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3, uint32_t x4,
     uint32_t rc_mul_splits, const AttnKernelArgs p) {
