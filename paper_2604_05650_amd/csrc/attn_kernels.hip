@@ -126,9 +126,7 @@ LVS_DEV void tile_softmax(WaveState<NB>& st, const f32x4 (&s)[2][NB], u32x4 (&po
   if (__any(grow)) {
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-      float x = fmaxf(st.m[nb], tmax[nb]);
-      x = fmaxf(x, xor_shuffle(x, 16));
-      x = fmaxf(x, xor_shuffle(x, 32));
+      const float x = max_halves(max_rows(fmaxf(st.m[nb], tmax[nb])));
       const float alpha = fast_exp2(st.m[nb] - x);
       st.m[nb] = x;
       st.l[nb] *= alpha;
