@@ -85,6 +85,10 @@ int lvspec_last_hip_error(void);
  * it may be less than lvspec_verify_attn_workspace asks for, and is accepted) is served by equal
  * splits instead: a sequence's bits then follow from its own data and length, the shapes and
  * max_kv_len alone, and a batch takes as long as its longest sequence.
+ * More than 64 query rows per kv head (G * gamma): with max_kv_len given, long enough sequences and the
+ * workspace asked for, up to 128 rows share a workgroup and one copy of the keys, with cuts of the keys
+ * of their own.  The plan that lvspec_describe_plan reports (row chunks of up to 64 rows) is then the one
+ * that serves a smaller workspace.
  * ------------------------------------------------------------------------------------------- */
 typedef struct {
   int32_t B, gamma, Hq, Hkv, D;     /* D must be 128; Hq % Hkv == 0; 1 <= gamma <= 32 */
@@ -314,7 +318,7 @@ int lvspec_kv_commit(const lvspec_commit_args* args, void* stream);
  * Returns the first planning error among the given arguments, else LVSPEC_OK.
  * ------------------------------------------------------------------------------------------- */
 typedef struct {
-  int32_t attn_rows_padded;      /* query rows per workgroup: 16, 32, 48 or 64 */
+  int32_t attn_rows_padded;      /* query rows per workgroup: 16, 32, 48 or 64 (see above for more) */
   int32_t attn_row_chunks;       /* workgroups that share one kv head's key range */
   int32_t attn_splits;           /* key-range splits per (sequence, kv head, row chunk) */
   int32_t rel_splits;            /* splits of the hidden dimension */

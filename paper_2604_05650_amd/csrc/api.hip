@@ -49,13 +49,88 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 bool stride_ok(int64_t s) { return s >= 0 && (s % 8) == 0; }
 
 // ------------------------------------------------------------------------------ attention
-struct AttnPlan {
-  int G, R, rpad, n_rc, n_split;
+// Rows of a kv head in chunks, and the two ways to divide the keys: equal splits per unit (sequence, kv
+// head, row chunk), and equal stretches of one line over all sequences.
+struct AttnCut {
+  int rpad, n_rc, n_split;
   size_t split_bytes;      // partials of n_split workgroups per unit
   int flat_pos;            // stretches of the line over all sequences, 0: none
   size_t flat_bytes;       // partials of those
+  size_t bytes() const { return flat_bytes > split_bytes ? flat_bytes : split_bytes; }
+};
+
+struct AttnPlan {
+  int G, R;
+  AttnCut cut;             // row chunks of up to 64 rows: what every workspace of cut.split_bytes serves
+  AttnCut wide;            // row chunks of 65 to 128 rows, n_rc = 0: not for this shape
   size_t ws_bytes;         // what the caller is asked for
 };
+
+// Equal splits and stretches for the row chunks that `c` holds; n_tiles of 32 keys at most.
+void divide_keys(const lvspec_attn_args* a, int64_t n_tiles, AttnCut* c) {
+  const int64_t units = (int64_t)a->B * a->Hkv * c->n_rc;
+  int64_t ns = num_compute_units() / units;
+  const int64_t cap_split = (n_tiles + 3) / 4;
+  if (ns > cap_split) ns = cap_split;
+  if (ns > 256) ns = 256;
+  if (ns < 1) ns = 1;
+  c->n_split = (int)ns;
+  const size_t rec_bytes = (size_t)c->rpad * 131 * sizeof(float);
+  c->split_bytes = (size_t)units * (size_t)ns * rec_bytes;
+  // A batch that the caller says is short keeps attn_split_kernel: its combine kernel does not wait
+  // for the lengths (2 x 2048 keys, 40 / 8 heads: 13.0 us against 14.1, 4 x 2048: 14.4 against 15.4;
+  // but 16 x 512, two workgroups per unit: 19.5 against 15.1).  By cap where there is no max_kv_len;
+  // the lengths themselves then ask for the same cut, see flat_equal_splits.
+  // Shapes that the static scratch serves with equal splits stay within it: fewer stretches leave a
+  // few CUs idle (one in sixteen for 256 units of 64 rows).
+  c->flat_pos = lvspec::attn_flat_positions(a->B, a->Hkv, c->rpad, c->n_rc, a->cap, num_compute_units());
+  if ((ns > 2 && n_tiles < lvspec::attn_short_tiles(a->B) * ns) || ns > 128) c->flat_pos = 0;
+  auto flat_bytes = [&] {
+    return ((size_t)c->flat_pos + (size_t)a->B * a->Hkv) * (size_t)c->n_rc * rec_bytes;
+  };
+  if (c->split_bytes <= (size_t)LVSPEC_STATIC_SCRATCH_BYTES) {
+    const int least = c->flat_pos * 7 / 8;
+    while (c->flat_pos > 0 && flat_bytes() > (size_t)LVSPEC_STATIC_SCRATCH_BYTES)
+      c->flat_pos = c->flat_pos - 8 >= least ? c->flat_pos - 8 : 0;
+  }
+  c->flat_bytes = c->flat_pos > 0 ? flat_bytes() : 0;
+}
+
+// More than 64 query rows per kv head in chunks of 65 to 128 (attn_segment32).
+void plan_wide(const lvspec_attn_args* a, int64_t n_tiles, AttnPlan* pl) {
+  AttnCut& w = pl->wide;
+  w = AttnCut{};
+  // Without max_kv_len the sequences may be a small part of the cache: short ones go faster in narrow chunks.
+  if (pl->R <= 64 || a->B > 64 || a->max_kv_len == 0) return;
+  AttnCut c{};
+  c.n_rc = (pl->R + 127) / 128;
+  c.rpad = ((pl->R + c.n_rc - 1) / c.n_rc + 3) / 4 * 4;
+  divide_keys(a, n_tiles, &c);
+  // Splits that fill the static scratch to the brim: one in sixteen fewer fits 128 rows on 256 CUs.
+  const size_t scratch = LVSPEC_STATIC_SCRATCH_BYTES;
+  if (a->B == 1 && c.split_bytes > scratch) {
+    const int most = (int)(scratch / (c.split_bytes / c.n_split));
+    if (most >= c.n_split - c.n_split / 16) {
+      c.split_bytes = c.split_bytes / c.n_split * most;
+      c.n_split = most;
+    }
+  }
+  if (a->B > 1 && c.flat_pos == 0) return;
+  // Twice the rows mean twice the partial records per workgroup, and a round is a longer chain: worth it
+  // from this many tiles of 32 keys per workgroup on.  Two chunks against one, us: one sequence, 40 / 8
+  // heads, 100 rows 12 tiles 21.4 and 21.5, 16 tiles 26.3 and 24.6; 64 / 8 heads, 80 rows 12 tiles 18.6 and
+  // 20.3, 16 tiles 22.7 and 22.6; 28 / 4 heads, 98 rows 10 tiles 22.3 and 25.0; four sequences, 40 / 8 heads,
+  // 80 rows 16 tiles 22.1 and 24.8; eight, 64 / 8 heads 16 tiles 23.0 and 24.2, 31 tiles 35.7 and 33.3.
+  // Three chunks against two: 40 / 8 heads, 150 rows 6 tiles 16.5 and 15.7; four against two: 64 / 8 heads,
+  // 240 rows 6 tiles 17.9 and 17.7.
+  const int64_t parts = a->B > 1 ? c.flat_pos : c.n_split;
+  const int64_t tiles = a->B > 1 ? n_tiles * a->B * a->Hkv : n_tiles;
+  const int64_t least = (pl->cut.n_rc > 2 ? 6 : 16) * (a->B > 1 ? 3 : 2) / 2;
+  if (tiles < least * parts) return;
+  // What the static scratch serves it goes on serving, with the same results.
+  if (pl->cut.bytes() <= scratch && c.bytes() > scratch) return;
+  w = c;
+}
 
 int plan_attn(const lvspec_attn_args* a, AttnPlan* pl) {
   if (a == nullptr) return LVSPEC_EINVAL;
@@ -71,40 +146,18 @@ int plan_attn(const lvspec_attn_args* a, AttnPlan* pl) {
   const int64_t lmax = a->max_kv_len > 0 ? a->max_kv_len : a->cap - a->gamma;
   pl->G = a->Hq / a->Hkv;
   pl->R = pl->G * a->gamma;
-  pl->n_rc = (pl->R + 63) / 64;
-  const int per_chunk = (pl->R + pl->n_rc - 1) / pl->n_rc;
-  pl->rpad = per_chunk <= 16 ? 16 : per_chunk <= 32 ? 32 : per_chunk <= 48 ? 48 : 64;
-  const int64_t units = (int64_t)a->B * a->Hkv * pl->n_rc;
+  AttnCut& c = pl->cut;
+  c.n_rc = (pl->R + 63) / 64;
+  const int per_chunk = (pl->R + c.n_rc - 1) / c.n_rc;
+  c.rpad = per_chunk <= 16 ? 16 : per_chunk <= 32 ? 32 : per_chunk <= 48 ? 48 : 64;
+  const int64_t units = (int64_t)a->B * a->Hkv * c.n_rc;
   // block ids and row indices stay below 2^27, the range of the kernels' multiply-shift division
   if (units * 64 > (int64_t)1 << 27 || a->Hq > 65536) return LVSPEC_EUNSUPPORTED;
   const int64_t n_tiles = (lmax + a->gamma + 31) / 32;
-  int64_t ns = num_compute_units() / units;
-  const int64_t cap_split = (n_tiles + 3) / 4;
-  if (ns > cap_split) ns = cap_split;
-  if (ns > 256) ns = 256;
-  if (ns < 1) ns = 1;
-  pl->n_split = (int)ns;
-  const size_t rec_bytes = (size_t)pl->rpad * 131 * sizeof(float);
-  pl->split_bytes = (size_t)units * (size_t)ns * rec_bytes;
-  // A batch that the caller says is short keeps attn_split_kernel: its combine kernel does not wait
-  // for the lengths (2 x 2048 keys, 40 / 8 heads: 13.0 us against 14.1, 4 x 2048: 14.4 against 15.4;
-  // but 16 x 512, two workgroups per unit: 19.5 against 15.1).  By cap where there is no max_kv_len;
-  // the lengths themselves then ask for the same cut, see flat_equal_splits.
-  // Shapes that the static scratch serves with equal splits stay within it: fewer stretches leave a
-  // few CUs idle (one in sixteen for 256 units of 64 rows).
-  pl->flat_pos = lvspec::attn_flat_positions(a->B, a->Hkv, pl->rpad, pl->n_rc, a->cap,
-                                             num_compute_units());
-  if ((ns > 2 && n_tiles < lvspec::attn_short_tiles(a->B) * ns) || ns > 128) pl->flat_pos = 0;
-  auto flat_bytes = [&] {
-    return ((size_t)pl->flat_pos + (size_t)a->B * a->Hkv) * (size_t)pl->n_rc * rec_bytes;
-  };
-  if (pl->split_bytes <= (size_t)LVSPEC_STATIC_SCRATCH_BYTES) {
-    const int least = pl->flat_pos * 7 / 8;
-    while (pl->flat_pos > 0 && flat_bytes() > (size_t)LVSPEC_STATIC_SCRATCH_BYTES)
-      pl->flat_pos = pl->flat_pos - 8 >= least ? pl->flat_pos - 8 : 0;
-  }
-  pl->flat_bytes = pl->flat_pos > 0 ? flat_bytes() : 0;
-  pl->ws_bytes = pl->flat_bytes > pl->split_bytes ? pl->flat_bytes : pl->split_bytes;
+  divide_keys(a, n_tiles, &c);
+  plan_wide(a, n_tiles, pl);
+  pl->ws_bytes = c.bytes();
+  if (pl->wide.n_rc > 0 && pl->wide.bytes() > pl->ws_bytes) pl->ws_bytes = pl->wide.bytes();
   return LVSPEC_OK;
 }
 
@@ -336,7 +389,7 @@ int lvspec_verify_attn(const lvspec_attn_args* a, void* stream) {
   if (rc != LVSPEC_OK) return rc;
   rc = check_attn_pointers(a);
   if (rc != LVSPEC_OK) return rc;
-  rc = check_ws(a->workspace, a->workspace_bytes, pl.split_bytes);
+  rc = check_ws(a->workspace, a->workspace_bytes, pl.cut.split_bytes);
   if (rc != LVSPEC_OK) return rc;
   return enqueue_attn(a, pl, a->workspace, a->workspace_bytes, stream);
 }
@@ -360,6 +413,9 @@ namespace {
 
 int enqueue_attn(const lvspec_attn_args* a, const AttnPlan& pl, void* workspace, size_t have,
                  void* stream) {
+  // Wide row chunks for a workspace as large as asked for; one that holds no more than equal splits of
+  // the narrow ones is served by those.
+  const AttnCut& cut = pl.wide.n_rc > 0 && have >= pl.ws_bytes ? pl.wide : pl.cut;
   lvspec::AttnKernelArgs k{};
   k.q = static_cast<const uint16_t*>(a->q);
   k.q_sb = a->q_sb; k.q_sg = a->q_sg; k.q_sh = a->q_sh;
@@ -379,22 +435,22 @@ int enqueue_attn(const lvspec_attn_args* a, const AttnPlan& pl, void* workspace,
   k.vis_begin = a->vis_begin;
   k.vis_end = a->vis_end;
   k.B = a->B; k.gamma = a->gamma; k.Hq = a->Hq; k.Hkv = a->Hkv;
-  k.G = pl.G; k.R = pl.R; k.rpad = pl.rpad; k.n_rc = pl.n_rc; k.n_split = pl.n_split;
-  k.div_split = lvspec::make_fast_div((uint32_t)pl.n_split);
-  k.div_rpad = lvspec::make_fast_div((uint32_t)pl.rpad);
+  k.G = pl.G; k.R = pl.R; k.rpad = cut.rpad; k.n_rc = cut.n_rc; k.n_split = cut.n_split;
+  k.div_split = lvspec::make_fast_div((uint32_t)cut.n_split);
+  k.div_rpad = lvspec::make_fast_div((uint32_t)cut.rpad);
   k.div_hkv = lvspec::make_fast_div((uint32_t)a->Hkv);
-  k.div_rc = lvspec::make_fast_div((uint32_t)pl.n_rc);
+  k.div_rc = lvspec::make_fast_div((uint32_t)cut.n_rc);
   k.div_g = lvspec::make_fast_div((uint32_t)pl.G);
   const float scale = a->scale > 0.f ? a->scale : 1.0f / __builtin_sqrtf((float)a->D);
-  k.xcd_map = ((int64_t)a->B * pl.n_rc * a->Hkv) % 8 == 0 ? 1 : 0;
+  k.xcd_map = ((int64_t)a->B * cut.n_rc * a->Hkv) % 8 == 0 ? 1 : 0;
   k.scale_log2e = scale * 1.4426950408889634f;
   k.ws = static_cast<float*>(workspace);
   // several sequences share one line of tiles; a workspace that holds only the partials of equal
   // splits is served by those.  The choice goes by the shapes, max_kv_len and the workspace, never
   // by kv_len_host: results are the same bits whether the host knows the lengths or not.
   constexpr int64_t kMaxStride = (int64_t)8 << 32;     // travels as a 32-bit number of 8 elements
-  k.flat_pos = have >= pl.ws_bytes && a->kv_sb < kMaxStride && a->kv_sh < kMaxStride &&
-                       a->kv_sl < kMaxStride ? pl.flat_pos : 0;
+  k.flat_pos = have >= cut.bytes() && a->kv_sb < kMaxStride && a->kv_sh < kMaxStride &&
+                       a->kv_sl < kMaxStride ? cut.flat_pos : 0;
   for (int i = 0; i < 32; ++i)
     k.draft_mask[i] = a->draft_mask ? (i < a->gamma ? a->draft_mask[i] : 0u)
                                     : (0xffffffffu >> (31 - i));
@@ -625,9 +681,9 @@ int lvspec_describe_plan(const lvspec_attn_args* attn, const lvspec_rel_args* re
     AttnPlan pl;
     const int rc = plan_attn(attn, &pl);
     if (rc == LVSPEC_OK) {
-      out->attn_rows_padded = pl.rpad;
-      out->attn_row_chunks = pl.n_rc;
-      out->attn_splits = pl.n_split;
+      out->attn_rows_padded = pl.cut.rpad;
+      out->attn_row_chunks = pl.cut.n_rc;
+      out->attn_splits = pl.cut.n_split;
     } else if (first == LVSPEC_OK) {
       first = rc;
     }

@@ -5,7 +5,8 @@
 // Kernel 1 (split):   one workgroup per (key-range split, kv head, sequence, row chunk), laid out
 //   on a 1-D grid so that all workgroups of a kv head land on one XCD; 4 * RS waves.
 //   All G*gamma query rows that share one kv head are processed together (G = Hq/Hkv), so every
-//   K/V byte is read from HBM exactly once (more than 64 rows take several row chunks).  The key
+//   K/V byte is read from HBM exactly once (more than 64 rows take several row chunks, or chunks of up
+//   to 128 rows on a core of their own, attn_rows32.h).  The key
 //   range of the workgroup is cut into tiles of 32 keys; stream s takes tiles s, s+4, ... and
 //   moves them through its own two-slot LDS ring with direct-to-LDS copies (one or two tiles
 //   beyond a multiple of four go through extra slots instead of a round of their own).
@@ -20,6 +21,7 @@
 // Kernel 2 (combine): log-sum-exp merge of the split partials in split order, bf16 output.
 // Batches take attn_flat_kernel and attn_flat_combine_kernel: the same work per tile and workgroup,
 // divided evenly over all sequences of the call.
+#include "attn_rows32.h"
 #include "lvspec_dev.h"
 #include "lvspec_kernels.h"
 
@@ -609,12 +611,52 @@ LVS_DEV void attn_segment(const Args& p, uint8_t* smem, int lane, int wave, int 
   }
 }
 
-// Registers are limited to half of a SIMD's in every variant.  Left with all 512 for its one wave per
-// SIMD, the compiler puts the accumulators of the 16-row variant into the accumulation registers and
-// moves all of them through ordinary ones for every tile's rescaling: 16384 keys, 40 / 8 heads, 1 and
-// 3 draft rows 16.0 and 16.4 us with it, 15.7 and 16.0 without; 7296 keys, 64 / 8 heads, 2 rows 11.9 and 11.2.
-template <int RS>
-constexpr int kWavesPerSimd = RS == 1 ? 2 : 1;
+// The work of a workgroup on a stretch of tiles, for the two kernels below: rows, threads, LDS.
+template <int RS, int NBW>
+struct Core16 {
+  static constexpr int kRows = 16 * NBW * RS;
+  static constexpr int kThreads = 256 * RS;
+  // Registers are limited to half of a SIMD's in every variant.  Left with all 512 for its one wave per
+  // SIMD, the compiler puts the accumulators of the 16-row variant into the accumulation registers and
+  // moves all of them through ordinary ones for every tile's rescaling: 16384 keys, 40 / 8 heads, 1 and
+  // 3 draft rows 16.0 and 16.4 us with it, 15.7 and 16.0 without; 7296 keys, 64 / 8 heads, 2 rows 11.9
+  // and 11.2.
+  static constexpr int kWavesPerSimd = RS == 1 ? 2 : 1;
+  // extra: whether some workgroup of the launch can hold more than 4q tiles with q >= 3 (only
+  // those use the extra-tile slots behind the rings)
+  static constexpr size_t lds_bytes(bool extra) {
+    const size_t ring = 4 * (size_t)kRingBytesPerWave + (extra ? kMaxExtraTiles * (size_t)kSlotBytes : 0);
+    const size_t merge = (3 * 4 * (size_t)kRows + 4 * (size_t)kRows * kORowStride) * sizeof(float);
+    return ring > merge ? ring : merge;
+  }
+  template <class Args, class Record>
+  LVS_DEV static void run(const Args& p, uint8_t* smem, int lane, int wave, int b, int kvh, int rc,
+                          int L, int gamma, int n_tiles, int t_begin, int t_end,
+                          const uint8_t* kbase, const uint8_t* vbase, int64_t rsb,
+                          Record&& record) {
+    attn_segment<RS, NBW>(p, smem, lane, wave, b, kvh, rc, L, gamma, n_tiles, t_begin, t_end, kbase,
+                          vbase, rsb, record);
+  }
+};
+
+// Ring slots: with four the first round lands later behind the longer first requests; 16384 keys,
+// 40 / 8 heads, 16 draft rows 23.0 and 24.9 us with three and four, tree of 20 24.6 and 24.5, 65536 keys
+// 62.4 and 60.7.
+template <int RG, int KS, int SL>
+struct Core32 {
+  static constexpr int kRows = 32 * RG;
+  static constexpr int kThreads = 64 * RG * KS;
+  static constexpr int kWavesPerSimd = 2;
+  static constexpr size_t lds_bytes(bool) { return Rows32<RG, KS, SL>::kLds; }
+  template <class Args, class Record>
+  LVS_DEV static void run(const Args& p, uint8_t* smem, int lane, int wave, int b, int kvh, int rc,
+                          int L, int gamma, int n_tiles, int t_begin, int t_end,
+                          const uint8_t* kbase, const uint8_t* vbase, int64_t rsb,
+                          Record&& record) {
+    attn_segment32<RG, KS, SL>(p, smem, lane, wave, b, kvh, rc, L, gamma, t_begin, t_end, kbase,
+                               vbase, rsb, record);
+  }
+};
 
 // Fast start.  All waves of all workgroups read the same few lines of the argument buffer when
 // the kernel starts, and that read is slow (in-kernel timestamps: the first wave has its
@@ -632,12 +674,12 @@ constexpr int kWavesPerSimd = RS == 1 ? 2 : 1;
 //   len0                     kv_len[0]
 // The structure behind them is then first needed for the query rows, behind the first copies.
 // In every other case (fast = 0) the kernel starts from the structure as before.
-template <int RS, int NBW>
-__global__ __launch_bounds__(256 * RS, kWavesPerSimd<RS>) void attn_split_kernel(
+template <class Core>
+__global__ __launch_bounds__(Core::kThreads, Core::kWavesPerSimd) void attn_split_kernel(
     const uint16_t* k0, const uint16_t* v0, int64_t kv_sh0, int kv_sl0, int n_split0,
     uint32_t split_mul0, int Hkv0, uint32_t hkv_mul0, uint32_t packed0, int len0,
     const AttnKernelArgs p) {
-  extern __shared__ __align__(16) uint8_t smem[];
+  extern __shared__ __align__(256) uint8_t smem[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   LVS_TRACE_BEGIN;
@@ -707,11 +749,10 @@ __global__ __launch_bounds__(256 * RS, kWavesPerSimd<RS>) void attn_split_kernel
   const int t_rem = n_tiles - t_base * n_split;
   const int t_begin = split * t_base + (split < t_rem ? split : t_rem);
   const int t_end = t_begin + t_base + (split < t_rem ? 1 : 0);
-  attn_segment<RS, NBW>(p, smem, lane, wave, b, kvh, rc, L, gamma, n_tiles, t_begin, t_end, kbase,
-                        vbase, rsb, [&](int bh) {
-                          return p.ws + (((size_t)bh * p.n_rc + rc) * n_split + split) *
-                                            (size_t)(16 * NBW * RS * 131);
-                        });
+  Core::run(p, smem, lane, wave, b, kvh, rc, L, gamma, n_tiles, t_begin, t_end, kbase, vbase, rsb,
+            [&](int bh) {
+              return p.ws + (((size_t)bh * p.n_rc + rc) * n_split + split) * ((size_t)p.rpad * 131);
+            });
   LVS_TRACE(8);
   LVS_TRACE_END;
 }
@@ -854,13 +895,13 @@ constexpr int kFlatArgsOffset = 56;
 
 // A workgroup per (stretch, row chunk); the row chunks of a stretch share an XCD's L2.  Strides in
 // units of eight elements; rc_mul_splits: ceil(32768 / n_rc), and `splits` from bit 16.
-template <int RS, int NBW>
-__global__ __launch_bounds__(256 * RS, kWavesPerSimd<RS>) void attn_flat_kernel(
+template <class Core>
+__global__ __launch_bounds__(Core::kThreads, Core::kWavesPerSimd) void attn_flat_kernel(
     const uint16_t* k0, const uint16_t* v0, uint32_t sb8, uint32_t sh8, uint32_t sl8,
     uint32_t packed, uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3, uint32_t x4,
     uint32_t rc_mul_splits, const AttnKernelArgs p) {
-  extern __shared__ __align__(16) uint8_t smem[];
-  constexpr uint32_t PAD = flat_pad(16 * NBW * RS);
+  extern __shared__ __align__(256) uint8_t smem[];
+  constexpr uint32_t PAD = flat_pad(Core::kRows);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const FlatShape sh = flat_shape(packed);
@@ -931,12 +972,12 @@ __global__ __launch_bounds__(256 * RS, kWavesPerSimd<RS>) void attn_flat_kernel(
       typedef const __attribute__((address_space(4))) uint8_t* BytesPtr;
       typedef const __attribute__((address_space(4))) AttnKernelArgs* ArgsPtr;
       const auto& args = *(ArgsPtr)((BytesPtr)at + kFlatArgsOffset);
-      attn_segment<RS, NBW>(
+      Core::run(
           args, smem, ln, wv, b, kvh, rc, L, sh.gamma, (int)n_tiles, (int)t0, (int)t1,
           reinterpret_cast<const uint8_t*>(k0) + base, reinterpret_cast<const uint8_t*>(v0) + base,
           rsb, [&](int) {
             const uint32_t rec = rec0 + (uint32_t)(b * sh.Hkv + kvh);
-            return args.ws + rec * (size_t)(16 * NBW * RS * 131);
+            return args.ws + rec * ((size_t)args.rpad * 131);
           });
     }
     v += n_tiles + PAD - t0;
@@ -950,7 +991,7 @@ __global__ __launch_bounds__(256 * RS, kWavesPerSimd<RS>) void attn_flat_kernel(
   }
 }
 
-static_assert(LastArgument<decltype(&attn_flat_kernel<1, 1>)>::offset() == kFlatArgsOffset,
+static_assert(LastArgument<decltype(&attn_flat_kernel<Core16<1, 1>>)>::offset() == kFlatArgsOffset,
               "the structure's place behind the leading arguments");
 
 // One group of 32 lanes per output row and share of its records, four channels a lane.  SG groups
@@ -1234,23 +1275,15 @@ __global__ __launch_bounds__(128 * kSG) void attn_combine_kernel(
 
 }  // namespace
 
-// extra: whether some workgroup of the launch can hold more than 4q tiles with q >= 3 (only
-// those use the extra-tile slots behind the rings)
-static size_t split_lds_bytes(int rpad, bool extra) {
-  const size_t ring = 4 * (size_t)kRingBytesPerWave + (extra ? kMaxExtraTiles * (size_t)kSlotBytes : 0);
-  const size_t merge = (3 * 4 * (size_t)rpad + 4 * (size_t)rpad * kORowStride) * sizeof(float);
-  return ring > merge ? ring : merge;
-}
-
-template <int RS, int NBW>
+template <class Core>
 static hipError_t launch_split(const AttnKernelArgs& a, hipStream_t stream) {
   // no sequence longer than lmax + gamma keys: the most tiles a workgroup can get
   const int64_t max_tiles = ((int64_t)a.lmax + a.gamma + kTileKeys - 1) / kTileKeys;
   const bool extra = (max_tiles + a.n_split - 1) / a.n_split > 3 * 4;
-  const size_t lds = split_lds_bytes(16 * NBW * RS, extra);
+  const size_t lds = Core::lds_bytes(extra);
   static LdsLimitOnce lds_limit;
-  hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(&attn_split_kernel<RS, NBW>),
-                                  split_lds_bytes(16 * NBW * RS, true));
+  hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(&attn_split_kernel<Core>),
+                                  Core::lds_bytes(true));
   if (e != hipSuccess) return e;
   dim3 grid(a.n_split * a.Hkv * a.B * a.n_rc);
   // fast start: one sequence with a host-known length (see the kernel)
@@ -1259,7 +1292,7 @@ static hipError_t launch_split(const AttnKernelArgs& a, hipStream_t stream) {
   const uint32_t packed = (a.div_split.shift & 255u) | ((a.xcd_map ? 1u : 0u) << 8) |
                           ((uint32_t)a.gamma << 16) | ((a.div_hkv.shift & 127u) << 24) |
                           ((fast ? 1u : 0u) << 31);
-  hipLaunchKernelGGL((attn_split_kernel<RS, NBW>), grid, dim3(256 * RS), lds, stream, a.k, a.v,
+  hipLaunchKernelGGL((attn_split_kernel<Core>), grid, dim3(Core::kThreads), lds, stream, a.k, a.v,
                      a.kv_sh, (int)a.kv_sl, a.n_split, a.div_split.mul, a.Hkv, a.div_hkv.mul,
                      packed, a.len_hot[0], a);
   return hipGetLastError();
@@ -1288,12 +1321,11 @@ FlatArgs flat_args(const AttnKernelArgs& a) {
 }
 }  // namespace
 
-template <int RS, int NBW>
+template <class Core>
 static hipError_t launch_flat(const AttnKernelArgs& a, hipStream_t stream) {
-  constexpr int rpad = 16 * NBW * RS;
-  const size_t lds = split_lds_bytes(rpad, true);
+  const size_t lds = Core::lds_bytes(true);
   static LdsLimitOnce lds_limit;
-  hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(&attn_flat_kernel<RS, NBW>), lds);
+  hipError_t e = lds_limit.ensure(reinterpret_cast<const void*>(&attn_flat_kernel<Core>), lds);
   if (e != hipSuccess) return e;
   const FlatArgs f = flat_args(a);
   const uint32_t units = (uint32_t)(a.B * a.Hkv);
@@ -1301,19 +1333,19 @@ static hipError_t launch_flat(const AttnKernelArgs& a, hipStream_t stream) {
   const bool fills = units * ns == (uint32_t)a.flat_pos || ns >= 4;
   const uint32_t splits = (ns - 1) | (fills ? 128u : 0u);
   const uint32_t line = (uint32_t)a.flat_pos * a.n_rc, equal = units * ns * a.n_rc;
-  hipLaunchKernelGGL((attn_flat_kernel<RS, NBW>), dim3(line > equal ? line : equal), dim3(256 * RS),
-                     lds, stream, a.k, a.v, (uint32_t)(a.kv_sb / 8), (uint32_t)(a.kv_sh / 8),
+  hipLaunchKernelGGL((attn_flat_kernel<Core>), dim3(line > equal ? line : equal),
+                     dim3(Core::kThreads), lds, stream, a.k, a.v, (uint32_t)(a.kv_sb / 8), (uint32_t)(a.kv_sh / 8),
                      (uint32_t)(a.kv_sl / 8), f.packed, f.x[0], f.x[1], f.x[2], f.x[3], f.x[4],
                      (uint32_t)((32768 + a.n_rc - 1) / a.n_rc) | splits << 16, a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   // eight groups per row where a unit has about eight records or more, two elsewhere
-  constexpr int PAD = flat_pad(rpad);
+  constexpr int PAD = flat_pad(Core::kRows);
   const uint32_t groups = (uint32_t)a.flat_pos >= 8 * units ? a.R : (a.R + 3) / 4;
   const auto kernel = (uint32_t)a.flat_pos >= 8 * units ? &attn_flat_combine_kernel<8, PAD>
                                                         : &attn_flat_combine_kernel<2, PAD>;
   hipLaunchKernelGGL(kernel, dim3(groups, a.Hkv, a.B), dim3(256), 0, stream, a.ws, f.packed, f.x[0],
-                     f.x[1], f.x[2], f.x[3], f.x[4], a.R, rpad, splits, groups, a);
+                     f.x[1], f.x[2], f.x[3], f.x[4], a.R, a.rpad, splits, groups, a);
   return hipGetLastError();
 }
 
@@ -1329,27 +1361,23 @@ int attn_flat_positions(int B, int Hkv, int rpad, int n_rc, int64_t cap, int num
   return places * B * Hkv < (most < exact ? most : exact) ? pos : 0;
 }
 
-// variant = 10 * RS + NBW; 0 picks the default for the row-chunk size
 hipError_t launch_attn(const AttnKernelArgs& a, hipStream_t stream) {
-  if (a.flat_pos > 0) {
-    if (a.rpad == 16) return launch_flat<1, 1>(a, stream);
-    if (a.rpad == 32) return launch_flat<2, 1>(a, stream);
-    if (a.rpad == 48) return launch_flat<3, 1>(a, stream);
-    return launch_flat<2, 2>(a, stream);
-  }
-  int variant = a.variant;
-  if (variant == 0) variant = a.rpad == 16 ? 11 : a.rpad == 32 ? 21 : a.rpad == 48 ? 31 : 22;
+  const bool flat = a.flat_pos > 0;
   hipError_t e;
-  switch (variant) {
-    case 11: if (a.rpad != 16) return hipErrorInvalidValue; e = launch_split<1, 1>(a, stream); break;
-    case 12: if (a.rpad != 32) return hipErrorInvalidValue; e = launch_split<1, 2>(a, stream); break;
-    case 21: if (a.rpad != 32) return hipErrorInvalidValue; e = launch_split<2, 1>(a, stream); break;
-    case 31: if (a.rpad != 48) return hipErrorInvalidValue; e = launch_split<3, 1>(a, stream); break;
-    case 14: if (a.rpad != 64) return hipErrorInvalidValue; e = launch_split<1, 4>(a, stream); break;
-    case 22: if (a.rpad != 64) return hipErrorInvalidValue; e = launch_split<2, 2>(a, stream); break;
-    case 41: if (a.rpad != 64) return hipErrorInvalidValue; e = launch_split<4, 1>(a, stream); break;
-    default: return hipErrorInvalidValue;
+  if (a.rpad <= 16) {
+    e = flat ? launch_flat<Core16<1, 1>>(a, stream) : launch_split<Core16<1, 1>>(a, stream);
+  } else if (a.rpad <= 32) {
+    e = flat ? launch_flat<Core16<2, 1>>(a, stream) : launch_split<Core16<2, 1>>(a, stream);
+  } else if (a.rpad <= 48) {
+    e = flat ? launch_flat<Core16<3, 1>>(a, stream) : launch_split<Core16<3, 1>>(a, stream);
+  } else if (a.rpad <= 64) {
+    e = flat ? launch_flat<Core16<2, 2>>(a, stream) : launch_split<Core16<2, 2>>(a, stream);
+  } else if (a.rpad <= 128) {
+    e = flat ? launch_flat<Core32<4, 2, 3>>(a, stream) : launch_split<Core32<4, 2, 3>>(a, stream);
+  } else {
+    return hipErrorInvalidValue;
   }
+  if (flat) return e;
   if (e != hipSuccess) return e;
   const dim3 cgrid(a.B * a.n_rc * a.Hkv * a.rpad);
 #define LVS_COMBINE_ARGS                                                                        \

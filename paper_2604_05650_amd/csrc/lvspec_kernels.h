@@ -58,7 +58,7 @@ struct AttnKernelArgs {
   int gamma, Hq, Hkv;
   int G;         // Hq / Hkv
   int R;         // query rows per kv head = G * gamma, ordered r = i * G + (h % G)
-  int rpad;      // rows per row chunk: 16, 32, 48 or 64
+  int rpad;      // rows per row chunk: 16, 32, 48, 64, or 65 to 128
   int xcd_map;   // 1: units (B * n_rc * Hkv) are a multiple of 8 and mapped one XCD each
   int n_rc;      // row chunks = ceil(R / rpad)
   int n_split;   // key-range splits
@@ -74,7 +74,6 @@ struct AttnKernelArgs {
   int flat_pos;  // > 0: equal stretches of one line over all sequences (a multiple of 8, B <= 64);
                  // then ws is [n_rc][flat_pos + B*Hkv][rpad * 131], or
                  // [n_rc][B*Hkv][n_split][rpad * 131] where the lengths ask for equal splits
-  int variant;   // kernel variant, 0 = default for rpad (development knob; host side only)
   const int32_t* vis_begin;   // nullptr = no span
   const int32_t* vis_end;
   uint16_t* out;
