@@ -39,18 +39,6 @@ LVS_DEV f32x16 mfma32(u32x4 a, u32x4 b, f32x16 c) {
                                                  __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// dma16 as one statement that the compiler does not know as an LDS write: LDS reads of these kernels
-// are then ordinary loads with waits of their own instead of a wait for every copy under way.  The
-// kernels wait for copies and keep reads behind the barrier themselves.
-LVS_DEV void dma16_asm(const void* gptr, uint32_t lds_base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt"
-               ::"s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(gptr));
-}
-
-LVS_DEV u32x4 lds_load16(uint32_t a) {
-  return *(const __attribute__((address_space(3))) u32x4*)(uintptr_t)a;
-}
-
 // Sixteen lanes read a block of 4 rows x 16 columns (lane i: row i / 4, columns 4*(i%4) .. +3) and get
 // it transposed: lane i column i, element j row j.
 LVS_DEV u32x2 lds_load_tr(uint32_t a) {
@@ -132,7 +120,7 @@ LVS_DEV void attn_segment32(const Args& p, uint8_t* smem, int lane, int wave, in
     if (round < n_full) {
       const int64_t off = round * step + (which ? v_minus_k : 0);
 #pragma unroll
-      for (int jj = 0; jj < W::kCopies; ++jj) dma16_asm(krow[jj] + off, dst + jj * 1024);
+      for (int jj = 0; jj < W::kCopies; ++jj) dma16_untracked(krow[jj] + off, dst + jj * 1024);
     } else {
       int cr = crow, nn = n16;
       asm volatile("" : "+v"(cr), "+v"(nn));      // (runs once: keep its arithmetic out of the loop)
@@ -141,7 +129,7 @@ LVS_DEV void attn_segment32(const Args& p, uint8_t* smem, int lane, int wave, in
       for (int jj = 0; jj < W::kCopies; ++jj) {
         int row = row0 + cr + 4 * jj;
         row = row < last_row ? row : last_row;
-        dma16_asm((which ? vbase : kbase) + (int64_t)row * rsb +
+        dma16_untracked((which ? vbase : kbase) + (int64_t)row * rsb +
                       ((nn ^ rows32_swz((cr + 4 * jj) & 15)) << 4), dst + jj * 1024);
       }
     }
@@ -228,8 +216,7 @@ LVS_DEV void attn_segment32(const Args& p, uint8_t* smem, int lane, int wave, in
   auto enter = [&](int t) {
     const int need = t + 1 < n_rounds ? 2 * t + 2 : 2 * t + 1;
     wait_copies_upto<W::kCopies, 2 * (SL - 2)>(issued - need);
-    __builtin_amdgcn_s_waitcnt(0xc07f);      // lgkmcnt(0) for the compiler's own count ...
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");    // ... and with the barrier
+    lds_barrier();
     request(t + SL - 1);
   };
   auto multiply = [&](int round) {

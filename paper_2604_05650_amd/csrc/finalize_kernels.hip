@@ -486,10 +486,10 @@ LVS_DEV void merge_row(const AcceptFinalizeArgs& p, int64_t col, int row, int la
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u) key[u] = k0 + 64 * u + lane < nk ? key[u] : 0ull;
-      if (k0 == 0)
-        top = topk_of<4>(key, p.topk, lane);
+      if (p.topk > kSortTopk)
+        topk_take<4, true>(top, key, p.topk, lane);
       else
-        topk_insert<4>(top, key, p.topk, lane);
+        topk_take<4, false>(top, key, p.topk, lane);
     }
   } else {
     // (many records share the k-th largest maximum) all candidates
@@ -501,10 +501,10 @@ LVS_DEV void merge_row(const AcceptFinalizeArgs& p, int64_t col, int row, int la
         const int i = k0 + 64 * u + lane;
         key[u] = i < nk ? ck[i] : 0ull;
       }
-      if (k0 == 0)
-        top = topk_of<4>(key, p.topk, lane);
+      if (p.topk > kSortTopk)
+        topk_take<4, true>(top, key, p.topk, lane);
       else
-        topk_insert<4>(top, key, p.topk, lane);
+        topk_take<4, false>(top, key, p.topk, lane);
     }
   }
   // ---- results of the row

@@ -19,7 +19,8 @@
 //
 // Instances <MODE, MB, NBX, RB>: 64*MB rows of A per task, 16*NBX columns of X.
 //   relevance: <1,1,512> (up to 16 draft rows, d % 256 == 0); otherwise <1|2, 1|2, 256>
-//   lm_head:   <1,1,256> or <2,1,256> up to 16 columns, <1,2,256> or <2,2,256> up to 32; more
+//   lm_head:   <1,1,256> or <2,1,256> up to 16 columns, <1,2,256> or <2,2,256> up to 32, each with and
+//              without the sorting networks of long candidate lists; more
 //              columns (up to 128) take lm_head_wide_kernel below
 #include "lvspec_dev.h"
 #include "lvspec_kernels.h"
@@ -31,7 +32,8 @@ namespace {
 constexpr int MODE_REL = 0;    // relevance, squared row norms of A taken in the same pass
 constexpr int MODE_LMH = 1;
 constexpr int MODE_RELP = 2;   // relevance with the rows' inverse norms prepared by the caller
-constexpr bool is_rel(int mode) { return mode != MODE_LMH; }
+constexpr int MODE_LMHS = 3;   // lm_head with more than kSortTopk candidates asked for
+constexpr bool is_rel(int mode) { return mode != MODE_LMH && mode != MODE_LMHS; }
 
 template <int MB, int NBX, int RB>
 struct Geo {
@@ -242,7 +244,7 @@ LVS_DEV void column_init(ColumnState& c) {
 // The set of the k best under the total order (value descending, id ascending) does not depend
 // on the order in which rows arrive, and the tasks of a workgroup are a fixed function of the
 // shape: results are reproducible.
-template <int NV>
+template <int NV, bool SORT>
 LVS_DEV void column_fold(ColumnState& c, const float (&vin)[NV], int id0, int n_rows, int topk,
                          bool want_z, int lane) {
   float v[NV];
@@ -271,12 +273,7 @@ LVS_DEV void column_fold(ColumnState& c, const float (&vin)[NV], int id0, int n_
   }
   c.m = mn;
   c.s = s;
-  // The first rows need no places found for them, a third of a round.  A small vocabulary has
-  // only first rows: k = 16, d = 1024, 32 hidden rows, V = 8192 34.3 -> 27.4 us, 32000 49.5 -> 38.6.
-  if (read_lane64(c.top, 0) == 0ull)
-    c.top = topk_of<NV>(key, topk, lane);
-  else
-    topk_insert<NV>(c.top, key, topk, lane);
+  topk_take<NV, SORT>(c.top, key, topk, lane);
 }
 
 // the workgroup's record of a column
@@ -357,9 +354,9 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(const GemmKernelArg
   }
 
   // lm_head: wave w serves columns w, w + 4, ...
-  constexpr int kCols = MODE == MODE_LMH ? 4 * NBX : 1;
+  constexpr int kCols = is_rel(MODE) ? 1 : 4 * NBX;
   ColumnState cst[kCols];
-  if constexpr (MODE == MODE_LMH) {
+  if constexpr (!is_rel(MODE)) {
 #pragma unroll
     for (int t = 0; t < kCols; ++t) column_init(cst[t]);
   }
@@ -487,7 +484,7 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(const GemmKernelArg
                     if (row0 + lane + 64 * j < n_rows)
                       p.logits[(int64_t)col * n_rows + row0 + lane + 64 * j] = v[t][j];
                 }
-                column_fold<MB>(cst[t4 + t], v[t], row0 + lane, n_rows, p.topk,
+                column_fold<MB, MODE == MODE_LMHS>(cst[t4 + t], v[t], row0 + lane, n_rows, p.topk,
                                 p.stats_z != nullptr, lane);
               }
             }
@@ -504,7 +501,7 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(const GemmKernelArg
     advance<MODE, G::kRowsWg>(p, cc);
     slot_c = slot_c + 1 == G::kStages ? 0 : slot_c + 1;
   }
-  if constexpr (MODE == MODE_LMH) {
+  if constexpr (!is_rel(MODE)) {
 #pragma unroll
     for (int t = 0; t < kCols; ++t)
       if (wave + 4 * t < p.n_cols) column_emit(cst[t], p, wave + 4 * t, lane);
@@ -549,7 +546,7 @@ struct Wide {
   static_assert(32 * kZtStride * 4 <= kASlot, "epilogue tile of 32 columns in one A slot");
 };
 
-template <int MB, int NB2>
+template <int MB, int NB2, bool SORT>
 __global__ __launch_bounds__(512, 2) void lm_head_wide_kernel(const GemmKernelArgs p) {
   using W = Wide<MB, NB2>;
   extern __shared__ __align__(16) uint8_t smem[];
@@ -724,7 +721,7 @@ __global__ __launch_bounds__(512, 2) void lm_head_wide_kernel(const GemmKernelAr
                 if (row0 + lane + 64 * j < p.n_rows)
                   p.logits[(int64_t)col * p.n_rows + row0 + lane + 64 * j] = v[t][j];
             }
-            column_fold<MB>(cst[4 * jj + t], v[t], row0 + lane, p.n_rows, p.topk,
+            column_fold<MB, SORT>(cst[4 * jj + t], v[t], row0 + lane, p.n_rows, p.topk,
                             p.stats_z != nullptr, lane);
           }
         }
@@ -770,20 +767,21 @@ hipError_t launch_gemm(const GemmKernelArgs& a, int num_cu, hipStream_t stream) 
       reinterpret_cast<const void*>(&gemm_stream_kernel<MODE, MB, NBX, RB>), lds);
   if (e != hipSuccess) return e;
   // (lm_head: one record per workgroup, the number the planner sized the records by)
-  const int grid = MODE == MODE_LMH ? a.n_rec : stream_grid(a.n_tasks, num_cu * G::kWgPerCu);
+  const int grid = !is_rel(MODE) ? a.n_rec : stream_grid(a.n_tasks, num_cu * G::kWgPerCu);
   hipLaunchKernelGGL((gemm_stream_kernel<MODE, MB, NBX, RB>), dim3(grid), dim3(256), lds, stream,
                      a);
   return hipGetLastError();
 }
 
-template <int MB, int NB2>
+template <int MB, int NB2, bool SORT>
 hipError_t launch_wide(const GemmKernelArgs& a, hipStream_t stream) {
   using W = Wide<MB, NB2>;
   static LdsLimitOnce lds_limit;
-  hipError_t e =
-      lds_limit.ensure(reinterpret_cast<const void*>(&lm_head_wide_kernel<MB, NB2>), W::kLds);
+  hipError_t e = lds_limit.ensure(
+      reinterpret_cast<const void*>(&lm_head_wide_kernel<MB, NB2, SORT>), W::kLds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((lm_head_wide_kernel<MB, NB2>), dim3(a.n_rec), dim3(512), W::kLds, stream, a);
+  hipLaunchKernelGGL((lm_head_wide_kernel<MB, NB2, SORT>), dim3(a.n_rec), dim3(512), W::kLds, stream,
+                     a);
   return hipGetLastError();
 }
 
@@ -840,23 +838,29 @@ hipError_t launch_rel_gemm(const GemmKernelArgs& a, int num_cu, hipStream_t stre
                           : launch_rel_mode<MODE_RELP>(a, num_cu, stream);
 }
 
-hipError_t launch_lmh_gemm(const GemmKernelArgs& a, int num_cu, hipStream_t stream) {
+template <bool SORT>
+static hipError_t launch_lmh(const GemmKernelArgs& a, int num_cu, hipStream_t stream) {
+  constexpr int MODE = SORT ? MODE_LMHS : MODE_LMH;
   const bool rows64 = a.rows_per_block == 64;
   if (!rows64 && a.rows_per_block != 128) return hipErrorInvalidValue;
   if (a.n_cols >= kWideCols) {
     const int widest = a.half_cols > a.n_cols - a.half_cols ? a.half_cols : a.n_cols - a.half_cols;
     if (a.half_cols > a.n_cols || widest > 64) return hipErrorInvalidValue;
     if (widest <= 32)
-      return rows64 ? launch_wide<1, 2>(a, stream) : launch_wide<2, 2>(a, stream);
+      return rows64 ? launch_wide<1, 2, SORT>(a, stream) : launch_wide<2, 2, SORT>(a, stream);
     if (widest <= 48)
-      return rows64 ? launch_wide<1, 3>(a, stream) : launch_wide<2, 3>(a, stream);
-    return rows64 ? launch_wide<1, 4>(a, stream) : launch_wide<2, 4>(a, stream);
+      return rows64 ? launch_wide<1, 3, SORT>(a, stream) : launch_wide<2, 3, SORT>(a, stream);
+    return rows64 ? launch_wide<1, 4, SORT>(a, stream) : launch_wide<2, 4, SORT>(a, stream);
   }
   if (a.n_cols <= 16)
-    return rows64 ? launch_gemm<MODE_LMH, 1, 1, 256>(a, num_cu, stream)
-                  : launch_gemm<MODE_LMH, 2, 1, 256>(a, num_cu, stream);
-  return rows64 ? launch_gemm<MODE_LMH, 1, 2, 256>(a, num_cu, stream)
-                : launch_gemm<MODE_LMH, 2, 2, 256>(a, num_cu, stream);
+    return rows64 ? launch_gemm<MODE, 1, 1, 256>(a, num_cu, stream)
+                  : launch_gemm<MODE, 2, 1, 256>(a, num_cu, stream);
+  return rows64 ? launch_gemm<MODE, 1, 2, 256>(a, num_cu, stream)
+                : launch_gemm<MODE, 2, 2, 256>(a, num_cu, stream);
+}
+
+hipError_t launch_lmh_gemm(const GemmKernelArgs& a, int num_cu, hipStream_t stream) {
+  return a.topk > kSortTopk ? launch_lmh<true>(a, num_cu, stream) : launch_lmh<false>(a, num_cu, stream);
 }
 
 }  // namespace lvspec

@@ -69,6 +69,31 @@ LVS_DEV void dma16(const void* gptr, uint32_t lds_base) {
       16, 0, POLICY);
 }
 
+// The same copy as a statement that the compiler does not know as an LDS write.  LDS reads are then
+// ordinary loads with waits of their own, spread among the instructions that use them, instead of a
+// wait for every copy under way; the kernel waits for copies (wait_copies) and separates reads and
+// copies of a slot by barriers itself (lds_barrier).  A kernel has either these copies or dma16
+// (the compiler does not see m0 change here).
+template <int POLICY = kCopyStream>
+LVS_DEV void dma16_untracked(const void* gptr, uint32_t lds_base) {
+  static_assert(POLICY == kCopyStream || POLICY == kCopyDefault, "policies in use");
+  const uint32_t at = __builtin_amdgcn_readfirstlane(lds_base);
+  if constexpr (POLICY == kCopyStream)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(at), "v"(gptr));
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(gptr));
+}
+
+LVS_DEV u32x4 lds_load16(uint32_t a) {
+  return *(const __attribute__((address_space(3))) u32x4*)(uintptr_t)a;
+}
+
+// Barrier behind this wave's LDS reads and writes; copies stay under way.
+LVS_DEV void lds_barrier() {
+  __builtin_amdgcn_s_waitcnt(0xc07f);      // lgkmcnt(0), for the compiler's own count ...
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");    // ... and with the barrier
+}
+
 // Wait until at most N copy instructions of this wave are outstanding, then read eight 16-byte
 // values from LDS: r[j] from a[j & 3] + (j >> 2) * OFF, and wait for them.
 template <int N, int OFF>
@@ -250,6 +275,80 @@ LVS_DEV uint64_t topk_of(uint64_t (&key)[NV], int k, int lane) {
   return top;
 }
 
+// Compare-exchange of 64-bit keys with the partner lane's: lanes without `bit` keep the larger.
+LVS_DEV uint64_t keep_ordered(uint64_t x, uint64_t partner, int bit, int lane) {
+  const bool other = (partner > x) != ((lane & bit) != 0);
+  return other ? partner : x;
+}
+template <int CTRL>
+LVS_DEV uint64_t dpp_move64(uint64_t x) {
+  const uint32_t lo = dpp_move<CTRL, 0xf>(0u, (uint32_t)x);
+  const uint32_t hi = dpp_move<CTRL, 0xf>(0u, (uint32_t)(x >> 32));
+  return ((uint64_t)hi << 32) | lo;
+}
+// partners within a row of 16 lanes
+LVS_DEV uint64_t lane_xor1(uint64_t x) { return dpp_move64<0xB1>(x); }
+LVS_DEV uint64_t lane_xor2(uint64_t x) { return dpp_move64<0x4E>(x); }
+LVS_DEV uint64_t lane_xor3(uint64_t x) { return dpp_move64<0x1B>(x); }
+LVS_DEV uint64_t lane_xor7(uint64_t x) { return dpp_move64<0x141>(x); }     // half mirror
+LVS_DEV uint64_t lane_xor8(uint64_t x) { return dpp_move64<0x128>(x); }     // rotation by 8
+LVS_DEV uint64_t lane_xor15(uint64_t x) { return dpp_move64<0x140>(x); }    // mirror
+LVS_DEV uint64_t lane_xor4(uint64_t x) { return lane_xor3(lane_xor7(x)); }
+
+// Every row of 16 lanes, a bitonic sequence, into descending order.
+LVS_DEV uint64_t sort_bitonic16(uint64_t x, int lane) {
+  x = keep_ordered(x, lane_xor8(x), 8, lane);
+  x = keep_ordered(x, lane_xor4(x), 4, lane);
+  x = keep_ordered(x, lane_xor2(x), 2, lane);
+  return keep_ordered(x, lane_xor1(x), 1, lane);
+}
+// Every row of 16 lanes into descending order.
+LVS_DEV uint64_t sort_row16(uint64_t x, int lane) {
+  x = keep_ordered(x, lane_xor1(x), 1, lane);
+  x = keep_ordered(x, lane_xor3(x), 2, lane);
+  x = keep_ordered(x, lane_xor1(x), 1, lane);
+  x = keep_ordered(x, lane_xor7(x), 4, lane);
+  x = keep_ordered(x, lane_xor2(x), 2, lane);
+  x = keep_ordered(x, lane_xor1(x), 1, lane);
+  x = keep_ordered(x, lane_xor15(x), 8, lane);
+  x = keep_ordered(x, lane_xor4(x), 4, lane);
+  x = keep_ordered(x, lane_xor2(x), 2, lane);
+  return keep_ordered(x, lane_xor1(x), 1, lane);
+}
+// The 16 largest of two descending rows, descending.
+LVS_DEV uint64_t merge_rows16(uint64_t a, uint64_t b, int lane) {
+  const uint64_t m = lane_xor15(b);
+  return sort_bitonic16(m > a ? m : a, lane);
+}
+// x becomes its even rows (lower half) in both rows of a pair (both halves), y the odd ones (the upper).
+// (Assembly for the reason given at max_halves.)
+LVS_DEV void split_rows(uint32_t& x, uint32_t& y) {
+  asm("v_mov_b32 %1, %0\n\ts_nop 1\n\tv_permlane16_swap_b32 %0, %1\n\ts_nop 1" : "+v"(x), "=&v"(y));
+}
+LVS_DEV void split_halves(uint32_t& x, uint32_t& y) {
+  asm("v_mov_b32 %1, %0\n\ts_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(x), "=&v"(y));
+}
+
+// Takes NV keys per lane into a wave's list of the 16 largest (lane r < 16 the r-th, 0 = none) by sorting
+// networks over the lanes: rows of 16, then rows against rows.  Keys are unique (0 aside).
+template <int NV>
+LVS_DEV void topk_merge(uint64_t& top, const uint64_t (&key)[NV], int lane) {
+  uint64_t x = sort_row16(key[0], lane);
+#pragma unroll
+  for (int j = 1; j < NV; ++j) x = merge_rows16(x, sort_row16(key[j], lane), lane);
+  uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32), lo2, hi2;
+  split_rows(lo, lo2);
+  split_rows(hi, hi2);
+  x = merge_rows16(((uint64_t)hi << 32) | lo, ((uint64_t)hi2 << 32) | lo2, lane);
+  lo = (uint32_t)x;
+  hi = (uint32_t)(x >> 32);
+  split_halves(lo, lo2);
+  split_halves(hi, hi2);
+  x = merge_rows16(((uint64_t)hi << 32) | lo, ((uint64_t)hi2 << 32) | lo2, lane);
+  x = merge_rows16(x, top, lane);
+  top = lane < 16 ? x : 0ull;
+}
+
 // A wave's running list of the k <= 16 largest 64-bit keys, lane r < 16 holding the r-th largest
 // (0 = none): take in NV keys per lane.  Only keys above the k-th so far cost a round, largest
 // first; every round retires one key, so the loop ends.  Equal keys are the same candidate.
@@ -273,6 +372,34 @@ LVS_DEV void topk_insert(uint64_t& top, uint64_t (&key)[NV], int k, int lane) {
     top = lane < pos ? top : lane == pos ? w : lane < 16 ? down : 0ull;
     kth = read_lane64(top, k - 1);
   }
+}
+
+// A wave's list of the k <= 16 largest takes in NV keys per lane, whichever way is the shortest.  The
+// first keys need no places found for them, a third of a round (a small vocabulary has only first rows:
+// k = 16, d = 1024, 32 hidden rows, V = 8192 34.3 -> 27.4 us).  With many candidates asked for, more than
+// a handful enter in the first tasks of a pass: sorted in at once they cost as much as about five rounds,
+// however many enter.  All rounds against this, hidden rows, V / d, k: 128, 152064 / 3584, 16 398 -> 335 us;
+// 100, 32000 / 2048, 16 87.7 -> 62.3 and 8 63.9 -> 59.4; 32, 8192 / 1024, 16 35.8 -> 23.4.  For k = 4 the
+// rounds stay the shorter way (128 rows, d = 8192 533 us, sorted 563); 3, 5 and 8 lanes as the bound
+// 336, 335 and 348 us on the first of these.  The networks are not in the code where nobody asks for
+// them: there they cost short passes 0.2 us (16 rows, k = 4, V = 8192 17.6 -> 17.8).
+constexpr int kSortTopk = 6;
+constexpr int kSortLanes = 5;
+template <int NV, bool SORT>
+LVS_DEV void topk_take(uint64_t& top, uint64_t (&key)[NV], int k, int lane) {
+  if constexpr (SORT) {      // k > kSortTopk
+    uint64_t best = key[0];
+#pragma unroll
+    for (int j = 1; j < NV; ++j) best = key[j] > best ? key[j] : best;
+    if (__popcll(__ballot(best > read_lane64(top, k - 1))) > kSortLanes) {
+      topk_merge<NV>(top, key, lane);
+      return;
+    }
+  }
+  if (read_lane64(top, 0) == 0ull)
+    top = topk_of<NV>(key, k, lane);
+  else
+    topk_insert<NV>(top, key, k, lane);
 }
 
 }  // namespace lvspec

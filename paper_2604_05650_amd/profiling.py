@@ -122,8 +122,8 @@ GROUPS = {   # kernels launched by one call of each entry point
     "visual_relevance": ("gemm_stream_kernel<0", "gemm_stream_kernel<2", "rel_finalize_kernel",
                          "rel_cand_kernel", "rel_merge_kernel", "rel_keep_kernel",
                          "rel_take_kernel"),
-    "lm_head_accept": ("gemm_stream_kernel<1", "lm_head_wide_kernel", "accept_finalize_kernel",
-                       "accept_merge_kernel", "accept_rule_kernel"),
+    "lm_head_accept": ("gemm_stream_kernel<1", "gemm_stream_kernel<3", "lm_head_wide_kernel",
+                       "accept_finalize_kernel", "accept_merge_kernel", "accept_rule_kernel"),
     "kv_commit": ("kv_commit_kernel",),
     "hv_prepare": ("hv_prepare_kernel",),
 }
@@ -131,7 +131,7 @@ GROUPS = {   # kernels launched by one call of each entry point
 STREAMS = {
     "verify_attn": ("attn_split_kernel", "attn_flat_kernel"),
     "visual_relevance": ("gemm_stream_kernel<0", "gemm_stream_kernel<2"),
-    "lm_head_accept": ("gemm_stream_kernel<1", "lm_head_wide_kernel"),
+    "lm_head_accept": ("gemm_stream_kernel<1", "gemm_stream_kernel<3", "lm_head_wide_kernel"),
 }
 CALIBRATION_KERNEL = "CUDAFunctorOnSelf_add<int>"
 GIB = float(1 << 30)

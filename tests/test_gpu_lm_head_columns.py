@@ -191,3 +191,27 @@ def test_logits_in_calls_of_few_and_of_many_rows(V, d, topk):
     assert (few[0] - many[-1]).abs().max().item() <= 2 * d * 2.0 ** -24 * scale
     if topk <= 4 and d < 4096:
         assert torch.equal(few[0], many[-1])
+
+
+@pytest.mark.parametrize("rows,V,d,topk", [
+    (1, 16, 128, 16), (5, 40, 128, 7), (5, 33000, 256, 16), (5, 70001, 128, 8), (32, 40001, 256, 12),
+    (16, 20001, 4096, 7), (36, 16384, 128, 16), (100, 40001, 128, 9), (128, 66000, 128, 16),
+])
+@pytest.mark.parametrize("ramp", [0.0, 4.0])
+def test_long_lists_are_those_of_the_logits(rows, V, d, topk, ramp):
+    # k = 7 to 16, single tasks and several per workgroup, in every stage size and column count; with
+    # the ramp later rows beat earlier ones, so that many enter every list to the last.  The lists
+    # against the logits that the same call returns, exactly: value descending, id ascending.
+    from paper_2604_05650_amd import binding as L
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(612 + rows + V)
+    w = torch.randn((V, d), generator=gen, device="cuda:0")
+    w += ramp * torch.arange(V, device="cuda:0")[:, None] / V
+    h = torch.rand((rows, 1, d), generator=gen, device="cuda:0") * 0.2
+    ids = torch.zeros((rows, 1), dtype=torch.int32, device="cuda:0")
+    outs = L.loose_accept(h.bfloat16(), w.bfloat16(), ids, torch.zeros((rows, 1), device="cuda:0"), 0, 0,
+                          topk=topk, return_logits=True)
+    torch.cuda.synchronize()
+    z = outs["logits"].view(rows, V).cpu().numpy()
+    want = np.argsort(-z, axis=1, kind="stable")[:, :topk]
+    np.testing.assert_array_equal(outs["topk_ids"].view(rows, topk).cpu().numpy(), want)
