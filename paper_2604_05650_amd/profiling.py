@@ -117,8 +117,8 @@ def mfma(db_path: str) -> str:
 
 
 GROUPS = {   # kernels launched by one call of each entry point
-    "verify_attn": ("attn_split_kernel", "attn_combine_kernel", "attn_flat_kernel",
-                    "attn_flat_combine_kernel"),
+    "verify_attn": ("attn_split_kernel", "attn_combine_kernel", "attn_combine32_kernel",
+                    "attn_flat_kernel", "attn_flat_combine_kernel"),
     "visual_relevance": ("gemm_stream_kernel<0", "gemm_stream_kernel<2", "rel_finalize_kernel",
                          "rel_cand_kernel", "rel_merge_kernel", "rel_keep_kernel",
                          "rel_take_kernel"),
