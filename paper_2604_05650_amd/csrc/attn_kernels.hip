@@ -1277,6 +1277,8 @@ __global__ __launch_bounds__(512) void attn_combine_kernel(
 // each, so that a thread has its whole share, four loads of 16 bytes, on the way at once (above: sixteen loads
 // of four bytes).  Per call at 32 splits, 8 kv heads, with one and the other: 100 rows 24.8 and 24.3 us, 64
 // rows (7296 keys) 14.8 and 14.5, 25 rows 16.45 and 16.39.
+// At 33 to 64 splits the same with sixteen groups gains nothing (4 kv heads, 16384 keys, 64 splits: 35 rows 15.05
+// above and 15.5 so, 63 rows 18.4 both, 98 rows 16.2 both), so the line lies at 32.
 __global__ __launch_bounds__(256) void attn_combine32_kernel(
     const float* ws, int rpad, int xcd_map, int Hkv, int n_rc, int R, int n_split,
     uint32_t rpad_mul, uint32_t rpad_shift, uint32_t hkv_mul, uint32_t hkv_shift, uint32_t rc_mul,
