@@ -35,8 +35,8 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0      # MI355X published HBM3E peak
 # kernels one call of each entry point launches; the durations in `rooflines` are per call
 KERNELS_OF = {
-    "verify_attn": ("lvspec_verify_attn = attn_split_kernel + attn_combine_kernel (batches: "
-                    "attn_flat_kernel + attn_flat_combine_kernel)"),
+    "verify_attn": ("lvspec_verify_attn = attn_split_kernel + attn_combine32_kernel (more than 32 splits: "
+                    "attn_combine_kernel; batches: attn_flat_kernel + attn_flat_combine_kernel)"),
     "visual_relevance": ("lvspec_visual_relevance = gemm_stream_kernel<REL> + rel_cand_kernel + "
                          "rel_merge_kernel (N above 16: rel_keep_kernel + rel_take_kernel, or "
                          "rel_finalize_kernel)"),
@@ -150,9 +150,12 @@ class Workload:
                          dtype=torch.uint8, device=dev)
         self.acc_args.workspace, self.acc_args.workspace_bytes = ws.data_ptr(), ws.numel()
         self.keep.append(ws)
-        # (acc_passes counts groups of chains; two groups share a pass over lm_head)
-        self.plan = L.describe_plan(attn=self.attn_args[0], rel=self.rel_args[0],
-                                    accept=self.acc_args)
+        # (acc_passes counts groups of chains; two groups share a pass over lm_head.)  attn_*: as for the
+        # smallest workspace, attn_run: as this run's workspace is served
+        least = L.AttnArgs.from_buffer_copy(self.attn_args[0])
+        least.workspace_bytes = 0
+        self.plan = dict(L.describe_plan(attn=least, rel=self.rel_args[0], accept=self.acc_args),
+                         attn_run=list(L.describe_plan(attn=self.attn_args[0]).values()))
         # algorithmic bytes: every K/V row once, Q and O once (per layer); H_V + H_D once;
         # lm_head + H_D once
         self.alg_bytes = {

@@ -81,14 +81,13 @@ int lvspec_last_hip_error(void);
  * sequence's keys are cut, and with that the rounding of its bf16 probabilities (a relative 2e-3 of
  * the result), follows from the lengths of all sequences, from the shapes and from max_kv_len; not
  * from where the lengths are given.  A workspace that holds no more than
- * B * Hkv * attn_row_chunks * attn_splits * attn_rows_padded * 131 * 4 bytes (lvspec_describe_plan;
- * it may be less than lvspec_verify_attn_workspace asks for, and is accepted) is served by equal
+ * B * Hkv * attn_row_chunks * attn_splits * attn_rows_padded * 131 * 4 bytes (lvspec_describe_plan
+ * with workspace_bytes = 0; it may be less than lvspec_verify_attn_workspace asks for, and is accepted) is served by equal
  * splits instead: a sequence's bits then follow from its own data and length, the shapes and
  * max_kv_len alone, and a batch takes as long as its longest sequence.
  * More than 64 query rows per kv head (G * gamma): with max_kv_len given, long enough sequences and the
  * workspace asked for, up to 128 rows share a workgroup and one copy of the keys, with cuts of the keys
- * of their own.  The plan that lvspec_describe_plan reports (row chunks of up to 64 rows) is then the one
- * that serves a smaller workspace.
+ * of their own.  A smaller workspace is served in row chunks of up to 64 rows.
  * ------------------------------------------------------------------------------------------- */
 typedef struct {
   int32_t B, gamma, Hq, Hkv, D;     /* D must be 128; Hq % Hkv == 0; 1 <= gamma <= 32 */
@@ -314,11 +313,14 @@ int lvspec_kv_commit(const lvspec_commit_args* args, void* stream);
  * Diagnostics: how the three verify calls would be launched for the given shapes (no paper
  * passage behind this one: it reports the library's own launch planning, for tuning and tests).
  * Any of the argument pointers may be NULL; its fields of *out are then left untouched.  Only
- * shape fields are read (no device pointer is dereferenced, nothing is launched).
+ * shape fields and, for the attention, workspace_bytes are read (no device pointer is dereferenced,
+ * nothing is launched): the attention fields say how a workspace of that many bytes is served, and
+ * with one smaller than asked for, 0 among them, how the smallest that is accepted is.
  * Returns the first planning error among the given arguments, else LVSPEC_OK.
  * ------------------------------------------------------------------------------------------- */
 typedef struct {
-  int32_t attn_rows_padded;      /* query rows per workgroup: 16, 32, 48 or 64 (see above for more) */
+  int32_t attn_rows_padded;      /* query rows per workgroup: 16, 32, 48 or 64; 65 to 128 where a
+                                    workspace as large as asked for is served by wide row chunks */
   int32_t attn_row_chunks;       /* workgroups that share one kv head's key range */
   int32_t attn_splits;           /* key-range splits per (sequence, kv head, row chunk) */
   int32_t rel_splits;            /* splits of the hidden dimension */

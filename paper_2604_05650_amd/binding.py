@@ -415,8 +415,8 @@ def kv_commit(k, v, kv_len, accept_len, chain_len, *, best_branch=None, n_branch
 
 def describe_plan(attn: Optional[AttnArgs] = None, rel: Optional[RelArgs] = None,
                   accept: Optional[AcceptArgs] = None) -> dict:
-    """lvspec_describe_plan: the launch planning for the given argument structures (shape fields
-    only are read).  Returns the fields of the structures that were given."""
+    """lvspec_describe_plan: the launch planning for the given argument structures (shape fields and
+    the attention's workspace_bytes are read).  Returns the fields of the structures that were given."""
     info = PlanInfo()
     _check(_lib.lvspec_describe_plan(C.byref(attn) if attn is not None else None,
                                      C.byref(rel) if rel is not None else None,

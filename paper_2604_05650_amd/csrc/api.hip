@@ -64,6 +64,9 @@ struct AttnPlan {
   AttnCut cut;             // row chunks of up to 64 rows: what every workspace of cut.split_bytes serves
   AttnCut wide;            // row chunks of 65 to 128 rows, n_rc = 0: not for this shape
   size_t ws_bytes;         // what the caller is asked for
+  // Wide row chunks for a workspace as large as asked for; one that holds no more than equal splits of
+  // the narrow ones is served by those.
+  const AttnCut& served_by(size_t have) const { return wide.n_rc > 0 && have >= ws_bytes ? wide : cut; }
 };
 
 // Equal splits and stretches for the row chunks that `c` holds; n_tiles of 32 keys at most.
@@ -413,9 +416,7 @@ namespace {
 
 int enqueue_attn(const lvspec_attn_args* a, const AttnPlan& pl, void* workspace, size_t have,
                  void* stream) {
-  // Wide row chunks for a workspace as large as asked for; one that holds no more than equal splits of
-  // the narrow ones is served by those.
-  const AttnCut& cut = pl.wide.n_rc > 0 && have >= pl.ws_bytes ? pl.wide : pl.cut;
+  const AttnCut& cut = pl.served_by(have);
   lvspec::AttnKernelArgs k{};
   k.q = static_cast<const uint16_t*>(a->q);
   k.q_sb = a->q_sb; k.q_sg = a->q_sg; k.q_sh = a->q_sh;
@@ -681,9 +682,10 @@ int lvspec_describe_plan(const lvspec_attn_args* attn, const lvspec_rel_args* re
     AttnPlan pl;
     const int rc = plan_attn(attn, &pl);
     if (rc == LVSPEC_OK) {
-      out->attn_rows_padded = pl.cut.rpad;
-      out->attn_row_chunks = pl.cut.n_rc;
-      out->attn_splits = pl.cut.n_split;
+      const AttnCut& cut = pl.served_by(attn->workspace_bytes);
+      out->attn_rows_padded = cut.rpad;
+      out->attn_row_chunks = cut.n_rc;
+      out->attn_splits = cut.n_split;
     } else if (first == LVSPEC_OK) {
       first = rc;
     }

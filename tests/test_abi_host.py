@@ -314,3 +314,19 @@ def test_wide_lm_head_stages(L):
         rec = workgroups * 96
         want = sum(-(-rec * n // 256) * 256 for n in (8, 8 * 4, 4))
         assert lib.lvspec_loose_accept_workspace(C.byref(a)) == want, V
+
+
+def test_plan_says_how_a_workspace_is_served(L):
+    # a tree of 2 x 10 rows at the 32B shape, 100 rows of a kv head: all in one workgroup with the workspace
+    # that is asked for, two chunks with less; three fields per plan
+    a = _attn(L, gamma=20, cap=16404, max_kv_len=16384)
+    asked = L.raw().lvspec_verify_attn_workspace(C.byref(a))
+    for have, plan in ((0, [64, 2, 16]), (asked - 1, [64, 2, 16]), (asked, [100, 1, 32]), (1 << 40, [100, 1, 32])):
+        a.workspace_bytes = have
+        assert list(L.describe_plan(attn=a).values()) == plan, have
+    # up to 64 rows there is one plan
+    a = _attn(L, gamma=8, cap=16392, max_kv_len=16384)
+    plans = set()
+    for a.workspace_bytes in (0, 1 << 40):
+        plans.add(tuple(L.describe_plan(attn=a).values()))
+    assert plans == {(48, 1, 32)}
