@@ -1414,11 +1414,14 @@ static hipError_t launch_flat(const AttnKernelArgs& a, hipStream_t stream) {
                      (uint32_t)((32768 + a.n_rc - 1) / a.n_rc) | splits << 16, a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // eight groups per row where a unit has about eight records or more, two elsewhere
+  // Eight groups per row where a unit has about eight records or more, two elsewhere.  With chunks of more
+  // than 64 rows a unit has twice the records and a merge the same rows: the line lies at twice as many
+  // (eight groups and two, 100 rows: 8 sequences of 4 tiles per workgroup, 28 / 4 heads 1.22 and 1.08 times the
+  // narrow chunks; 4 of 16384 keys, 40 / 8 heads 0.98 and 0.89).
   constexpr int PAD = flat_pad(Core::kRows);
-  const uint32_t groups = (uint32_t)a.flat_pos >= 8 * units ? a.R : (a.R + 3) / 4;
-  const auto kernel = (uint32_t)a.flat_pos >= 8 * units ? &attn_flat_combine_kernel<8, PAD>
-                                                        : &attn_flat_combine_kernel<2, PAD>;
+  const bool many = (uint32_t)a.flat_pos >= (Core::kRows > 64 ? 17 : 8) * units;
+  const uint32_t groups = many ? a.R : (a.R + 3) / 4;
+  const auto kernel = many ? &attn_flat_combine_kernel<8, PAD> : &attn_flat_combine_kernel<2, PAD>;
   hipLaunchKernelGGL(kernel, dim3(groups, a.Hkv, a.B), dim3(256), 0, stream, a.ws, f.packed, f.x[0],
                      f.x[1], f.x[2], f.x[3], f.x[4], a.R, a.rpad, splits, groups, a);
   return hipGetLastError();

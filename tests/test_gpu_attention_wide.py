@@ -106,3 +106,31 @@ def test_stale_lengths_stay_within_the_declared_rows():
     most = cap - gamma
     for stale, means in ((most + 999, most), (-5, 0)):
         assert torch.equal(_call(q, k, v, [stale], most)[0], _call(q, k, v, [means], most)[0])
+
+
+@pytest.mark.parametrize("Hq,Hkv,gamma,hint,kv_len", [
+    (28, 4, 14, 12000, [300] * 15 + [12000]),     # one long sequence among short ones
+    (40, 8, 20, 6200, [6200, 3000, 700, 90]),     # eight records of a head, two groups merge them
+    (40, 8, 20, 6200, [1900, 200, 60, 0]),        # far below the hint: equal splits
+    (40, 8, 20, 12400, [12400, 11000]),           # sixteen records
+    (28, 4, 16, 16400, [16400, 100, 9000]),       # more than sixteen: eight groups
+    (64, 8, 10, 3100, [3100, 2, 0, 155, 3000, 640, 31, 33]),
+])
+def test_wide_batches_of_uneven_lengths(Hq, Hkv, gamma, hint, kv_len):
+    from paper_2604_05650_amd import binding as L
+    B, D = len(kv_len), 128
+    key = (135, B, Hq, gamma, kv_len[0])
+    q, k, v = (synth.normal_bf16((*key, i), s, 1.0) for i, s in
+               enumerate([(B, gamma, Hq, D), (B, Hkv, hint + gamma, D), (B, Hkv, hint + gamma, D)]))
+    tq, tk, tv = t_bf16(q), t_bf16(k), t_bf16(v)
+    a = L.verify_attn_args(tq, tk, tv, t_i32(kv_len), out=torch.empty_like(tq), max_kv_len=hint)
+    a.workspace_bytes = 1 << 40
+    assert L.describe_plan(attn=a)["attn_rows_padded"] > 64
+    vis = [(min(n, 17), n * 3 // 4) for n in kv_len]
+    out, lse, vm = _call(tq, tk, tv, kv_len, hint, vis=vis)
+    o_out, o_lse, o_vm = oracle.verify_attn(q, k, v, kv_len, vis_begin=[x[0] for x in vis],
+                                            vis_end=[x[1] for x in vis])
+    assert_rows_close(bf16_out_to_f64(out), o_out, "wide out")
+    assert_scalars_close(lse.cpu().numpy().astype(np.float64), o_lse, "wide lse")
+    assert_scalars_close(vm.cpu().numpy().astype(np.float64), o_vm, "wide vis mass")
+    assert torch.equal(out, _call(tq, tk, tv, kv_len, hint, vis=vis, host=True)[0])
