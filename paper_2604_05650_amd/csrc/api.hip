@@ -119,16 +119,34 @@ void plan_wide(const lvspec_attn_args* a, int64_t n_tiles, AttnPlan* pl) {
     }
   }
   if (a->B > 1 && c.flat_pos == 0) return;
+  // More than 32 splits of one sequence: fewer than eight kv heads, whose records no longer lie in the L2
+  // of the XCD that merges them.  28 / 4 heads, 98 rows, in chunks of up to 64 rows and here: 2034 keys under
+  // a hint of 60000 12.4 and 19.1 us, 8178 keys 15.3 and 20.7; 8 / 2 heads, 80 rows, 57324 keys 21.2 and 26.2.
+  if (a->B == 1 && c.n_split > 32) return;
   // Twice the rows mean twice the partial records per workgroup, and a round is a longer chain: worth it
-  // from this many tiles of 32 keys per workgroup on.  Two chunks against one, us: one sequence, 40 / 8
-  // heads, 100 rows 12 tiles 21.4 and 21.5, 16 tiles 26.3 and 24.6; 64 / 8 heads, 80 rows 12 tiles 18.6 and
-  // 20.3, 16 tiles 22.7 and 22.6; 28 / 4 heads, 98 rows 10 tiles 22.3 and 25.0; four sequences, 40 / 8 heads,
-  // 80 rows 16 tiles 22.1 and 24.8; eight, 64 / 8 heads 16 tiles 23.0 and 24.2, 31 tiles 35.7 and 33.3.
-  // Three chunks against two: 40 / 8 heads, 150 rows 6 tiles 16.5 and 15.7; four against two: 64 / 8 heads,
-  // 240 rows 6 tiles 17.9 and 17.7.
+  // from this many tiles of 32 keys per workgroup on.  In narrow chunks and here, us:
+  //   one sequence, 8 kv heads, 100 rows 8 tiles 17.4 and 17.1, 16 tiles 24.3 and 22.2; 128 rows 12 tiles 21.3
+  //   and 21.5, 16 tiles 24.5 and 23.4; three chunks against two, 150 rows 6 tiles 16.5 and 15.7; four against
+  //   two, 240 rows 6 tiles 16.0 and 16.2, 12 tiles 21.2 and 20.0;
+  //   the 48-row variant (65 to 96, 129 to 144 rows) holds its own for longer: 80 rows 16 tiles 20.6 and 20.9,
+  //   28 tiles 29.2 and 28.1; batches of 4, 28 / 4 heads, 72 rows, equal lengths 16 tiles 0.98 times as long here,
+  //   24 tiles 0.95.
+  // max_kv_len is a bound of the lengths and no more, and which cut is used must not depend on where the
+  // lengths are given: the lines lie where a hint that is right gains, and lengths far below it lose little.
+  // Times as long as in the narrow chunks of the same shape: one sequence of 1000 to 3000 keys under a long
+  // hint, 8 kv heads, 100 rows 1.03 to 1.06, 80 and 128 rows 1.08 to 1.12; batches whose lengths spread over 5
+  // to 100 % of the hint, so that a stretch gets a third of the tiles that the hint promises, and that just pass
+  // the line 0.9 to 1.1; 3 to 7 tiles per workgroup, under a hint many times too long, 0.84 to 1.16 (2 to 8
+  // sequences, 2 to 8 kv heads, 80 to 100 rows).
   const int64_t parts = a->B > 1 ? c.flat_pos : c.n_split;
   const int64_t tiles = a->B > 1 ? n_tiles * a->B * a->Hkv : n_tiles;
-  const int64_t least = (pl->cut.n_rc > 2 ? 6 : 16) * (a->B > 1 ? 3 : 2) / 2;
+  const bool rows48 = pl->cut.rpad == 48;
+  int64_t least = pl->cut.n_rc > 2 ? 6 : 16;
+  if (a->B == 1) {
+    if (rows48 && pl->cut.n_rc == 2 && c.n_split > 16) least = 24;
+  } else {
+    least = rows48 && a->B * a->Hkv < 48 ? 32 : least * 3 / 2;
+  }
   if (tiles < least * parts) return;
   // What the static scratch serves it goes on serving, with the same results.
   if (pl->cut.bytes() <= scratch && c.bytes() > scratch) return;

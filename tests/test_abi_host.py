@@ -330,3 +330,25 @@ def test_plan_says_how_a_workspace_is_served(L):
     for a.workspace_bytes in (0, 1 << 40):
         plans.add(tuple(L.describe_plan(attn=a).values()))
     assert plans == {(48, 1, 32)}
+
+
+@pytest.mark.parametrize("shape,hint,plan", [
+    # one sequence: from 16 tiles of 32 keys per workgroup on (100 rows, 32 splits); 80 rows, which the 48-row
+    # variant takes in two chunks, from 24 on
+    (dict(Hq=40, gamma=20), 16384, [100, 1, 32]),
+    (dict(Hq=40, gamma=20), 16320, [64, 2, 16]),
+    (dict(Hq=64, gamma=10), 24560, [80, 1, 32]),
+    (dict(Hq=64, gamma=10), 24500, [48, 2, 16]),
+    # fewer than eight kv heads would take more than 32 splits, whatever the hint
+    (dict(Hq=28, Hkv=4, gamma=14), 60000, [64, 2, 32]),
+    (dict(Hq=28, Hkv=4, gamma=10), 60000, [48, 2, 32]),
+    (dict(Hq=8, Hkv=2, gamma=20), 100000, [48, 2, 64]),
+    # batches: a third more where the 48-row variant takes the chunks and few heads share the line
+    (dict(B=4, Hq=28, Hkv=4, gamma=10), 16200, [48, 2, 8]),
+    (dict(B=4, Hq=28, Hkv=4, gamma=10), 16384, [72, 1, 16]),
+    (dict(B=4, Hq=28, Hkv=4, gamma=14), 12288, [100, 1, 16]),
+    (dict(B=8, Hq=64, Hkv=8, gamma=10), 3072, [80, 1, 4]),
+])
+def test_wide_row_chunks_pay_for_long_sequences(L, shape, hint, plan):
+    a = _attn(L, cap=hint + 32, max_kv_len=hint, **shape)
+    assert list(L.describe_plan(attn=a).values()) == plan

@@ -142,3 +142,20 @@ def test_equal_splits_do_not_look_at_the_other_sequences(Hq, Hkv, gamma):
     other = a.run(split=True)
     assert torch.equal(out[0], other[0]) and not torch.equal(out[1], other[1])
     assert_rows_close(bf16_out_to_f64(a.run()[0]), bf16_out_to_f64(other[0]), "line, same sequence")
+
+
+@pytest.mark.parametrize("Hq,Hkv,gamma,kv_len,cap", [
+    (28, 4, 10, [1500] * 4, 20000),               # two row chunks of 35 rows, eight splits
+    (8, 2, 32, [2100, 2099, 2098, 2097], 20000),  # two of 64, as many tiles each
+    (64, 8, 9, [900, 900], 16384),                # two, eight kv heads
+    (40, 8, 32, [1000] * 3, 16384),               # three, and nine workgroups to a head
+    (16, 4, 20, [0, 0], 16384),                   # one tile, most splits empty
+    (28, 4, 10, [3000, 900, 40, 1], 60000),       # short ones of unequal lengths
+])
+def test_row_chunks_of_equal_splits(Hq, Hkv, gamma, kv_len, cap):
+    # all row chunks of a kv head on one XCD, whichever kernel divides the keys: the same records
+    b = Batch((Hq, gamma, len(kv_len)), kv_len, Hq, Hkv, gamma, cap)
+    assert b.stretches > 0 and b.n_rc > 1 and b.units % 8 == 0
+    out = b.run()
+    assert _other_bits(out, b.run(split=True)) < 2e-3
+    b.check(out, "row chunks")
