@@ -97,7 +97,7 @@ def test_wide_rows_of_a_token_major_cache():
 
 
 def test_stale_lengths_stay_within_the_declared_rows():
-    # device lengths outside [0, cap - gamma] are clamped; rows behind the declared ones are not read
+    # device lengths outside [0, cap - gamma] are clamped to its ends
     B, Hq, Hkv, gamma, D, cap = 1, 80, 16, 16, 128, 8300
     gen = torch.Generator(device=dev())
     gen.manual_seed(133)
@@ -134,3 +134,28 @@ def test_wide_batches_of_uneven_lengths(Hq, Hkv, gamma, hint, kv_len):
     assert_scalars_close(lse.cpu().numpy().astype(np.float64), o_lse, "wide lse")
     assert_scalars_close(vm.cpu().numpy().astype(np.float64), o_vm, "wide vis mass")
     assert torch.equal(out, _call(tq, tk, tv, kv_len, hint, vis=vis, host=True)[0])
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,gamma,hint,kv_len", [
+    (1, 80, 16, 20, 8300, [8170]),        # 100 rows; ends inside a tile, and an odd tile without a partner
+    (1, 128, 16, 16, 8200, [777]),        # workgroups without a tile
+    (1, 80, 16, 20, 8200, [0]),
+    (8, 40, 8, 20, 3100, [3100, 5, 0, 800, 1601, 2016, 64, 3000]),
+    (1, 40, 8, 5, 8200, [8170]),          # the cores of up to 64 rows: 32, 48 and 64
+    (1, 64, 8, 5, 8200, [777]),
+    (3, 64, 8, 8, 3100, [2900, 0, 95]),
+])
+def test_rows_behind_the_declared_ones_are_not_read(B, Hq, Hkv, gamma, hint, kv_len):
+    # NaN from the last draft row on, in every kv head and behind the cache's rows: a masked key's row that is
+    # read all the same gives 0 * NaN
+    D, cap = 128, hint + gamma
+    gen = torch.Generator(device=dev())
+    gen.manual_seed(136)
+    q = torch.randn((B, gamma, Hq, D), generator=gen, device=dev()).bfloat16()
+    kv = [torch.randn((B, Hkv, cap + 64, D), generator=gen, device=dev()).bfloat16() for _ in "kv"]
+    clean = _call(q, *(t[:, :, :cap] for t in kv), kv_len, hint)
+    for t in kv:
+        for b, n in enumerate(kv_len):
+            t[b, :, n + gamma:] = float("nan")
+    for got, want in zip(_call(q, *(t[:, :, :cap] for t in kv), kv_len, hint)[:2], clean[:2]):
+        assert torch.equal(got, want)
