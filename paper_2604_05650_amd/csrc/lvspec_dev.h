@@ -69,19 +69,17 @@ LVS_DEV void dma16(const void* gptr, uint32_t lds_base) {
       16, 0, POLICY);
 }
 
-// The same copy as a statement that the compiler does not know as an LDS write.  LDS reads are then
-// ordinary loads with waits of their own, spread among the instructions that use them, instead of a
+// The same copy (kCopyStream) as a statement that the compiler does not know as an LDS write.  LDS reads
+// are then ordinary loads with waits of their own, spread among the instructions that use them, instead of a
 // wait for every copy under way; the kernel waits for copies (wait_copies) and separates reads and
-// copies of a slot by barriers itself (lds_barrier).  A kernel has either these copies or dma16
-// (the compiler does not see m0 change here).
-template <int POLICY = kCopyStream>
+// copies of a slot by barriers itself (lds_barrier).  m0 is as before behind it (the compiler takes no
+// clobber of m0, and may keep a value there).
 LVS_DEV void dma16_untracked(const void* gptr, uint32_t lds_base) {
-  static_assert(POLICY == kCopyStream || POLICY == kCopyDefault, "policies in use");
   const uint32_t at = __builtin_amdgcn_readfirstlane(lds_base);
-  if constexpr (POLICY == kCopyStream)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(at), "v"(gptr));
-  else
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(gptr));
+  uint32_t keep;
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off nt\n\t"
+               "s_mov_b32 m0, %0"
+               : "=&s"(keep) : "s"(at), "v"(gptr));
 }
 
 LVS_DEV u32x4 lds_load16(uint32_t a) {
