@@ -618,9 +618,8 @@ struct Core16 {
   static constexpr int kThreads = 256 * RS;
   // Registers are limited to half of a SIMD's in every variant.  Left with all 512 for its one wave per
   // SIMD, the compiler puts the accumulators of the 16-row variant into the accumulation registers and
-  // moves all of them through ordinary ones for every tile's rescaling: 16384 keys, 40 / 8 heads, 1 and
-  // 3 draft rows 16.0 and 16.4 us with it, 15.7 and 16.0 without; 7296 keys, 64 / 8 heads, 2 rows 11.9
-  // and 11.2.
+  // moves all of them through ordinary ones for every tile's rescaling: 16384 keys, 40 / 8 heads, one draft
+  // row 16.8 us with it, 16.6 without; 7296 keys, 64 / 8 heads, 2 rows 13.1 and 12.6.
   static constexpr int kWavesPerSimd = RS == 1 ? 2 : 1;
   // extra: whether some workgroup of the launch can hold more than 4q tiles with q >= 3 (only
   // those use the extra-tile slots behind the rings)
@@ -1278,8 +1277,9 @@ __global__ __launch_bounds__(512) void attn_combine_kernel(
 
 // The same for up to 32 splits.  Eight groups of 32 lanes, four channels a lane, take every eighth split
 // each, so that a thread has its whole share, four loads of 16 bytes, on the way at once (above: sixteen loads
-// of four bytes).  Per call at 32 splits, 8 kv heads, with one and the other: 100 rows 24.8 and 24.3 us, 64
-// rows (7296 keys) 14.8 and 14.5, 25 rows 16.45 and 16.39.
+// of four bytes).  Per call at 32 splits, 8 kv heads, with the kernel above and this: 100 rows 24.7 and 23.7 us,
+// 128 rows 25.7 and 25.1, 64 rows (7296 keys) 15.65 and 15.44, 25 rows 16.9 both.  The splits add up in eight
+// partial sums (above: four): results a rounding apart, 2e-5 of a layer's.
 // At 33 to 64 splits the same with sixteen groups gains nothing (4 kv heads, 16384 keys, 64 splits: 35 rows 15.05
 // above and 15.5 so, 63 rows 18.4 both, 98 rows 16.2 both), so the line lies at 32.
 __global__ __launch_bounds__(256) void attn_combine32_kernel(

@@ -1,10 +1,10 @@
 // Attention of 65 to 128 query rows of a kv head by one workgroup (attn_segment32), on 32x32 MFMA tiles.
 //
-// What bounds these shapes is the arithmetic of a tile, not its copy: 64 keys by 128 rows are 1090
-// cycles of each SIMD's matrix core and about 1200 of its vector unit, where HBM delivers the 32 KiB of
-// such a round in 2600 cycles.  The 64-row variant of attn_segment takes such rows in two chunks, each a
-// workgroup with copies of its own, and spends 5700 cycles on 128 keys by 64 rows, waiting on one
-// instruction chain after the other.  Here all rows share one copy of each tile:
+// HBM is the floor: it delivers the 32 KiB of a round (64 keys) in 2600 cycles.  By 128 rows that are 1090 cycles
+// of each SIMD's matrix core and about 1200 of its vector unit, which fit under the copy only as far as they
+// overlap it and each other; a round takes about 3000.  The 64-row variant of attn_segment takes such rows in
+// two chunks, each a workgroup with copies of its own, and spends 5700 cycles on 128 keys by 64 rows, waiting
+// on one instruction chain after the other.  Here all rows share one copy of each tile:
 //   Eight waves, four groups of 32 rows by two streams of keys; the lane layout of a 32x32 result
 //   (one query row and sixteen keys per lane) is the operand layout of the second product up to an
 //   order of the keys that both of its operands share, so probabilities stay in their lane.
@@ -12,10 +12,10 @@
 //   The reads and the softmax of a round, and the products behind them (scores of the next round, then
 //   the output), are two halves; the second four waves, one on each SIMD next to one of the first four,
 //   run half a round late, so that one wave's products cover the other's vector work.
-// Per call, in two chunks and here: tree of 2 x 10 rows, 40 / 8 heads, 16384 keys 26.3 -> 24.6 us, 65536
-// keys 76.8 -> 59.9; 4 x 30000 keys, 64 / 8 heads, 10 rows 114 -> 95; 24 sequences of 3000 to 8750 keys,
-// 28 / 4 heads, 14 rows 89 -> 74.  Tried at these shapes: 64 rows per wave and four waves (113 us for the
-// third), both halves behind barriers of their own (116), waves without the half-round offset (100), a
+// Per call, in two chunks and here: tree of 2 x 10 rows, 40 / 8 heads, 16384 keys 27.5 -> 25.1 us (23.7 with
+// attn_combine32_kernel), 65536 keys 76.6 -> 59.8; 4 x 30000 keys, 64 / 8 heads, 10 rows 113.7 -> 95.0; 24
+// sequences of 3000 to 8750 keys, 28 / 4 heads, 14 rows 83.2 -> 65.6.  Tried on the 4 x 30000 keys: 64 rows per
+// wave and four waves (113), both halves behind barriers of their own (116), waves without the half-round offset (100), a
 // running maximum with slack 8 (the branch below is then rare: 92, but the probabilities lose the exact
 // one of their largest, error against 64 bits 2.15e-3 -> 2.32e-3), the same with probabilities split into
 // two bf16 (1.66e-3, 107 us); the rescaling of the output among the matrix instructions of the scores (96).

@@ -152,8 +152,8 @@ LVS_DEV float xor_shuffle(float x, int mask) { return __shfl_xor(x, mask, 64); }
 // its own value and its partner's, in either order): no trip through the LDS queue, behind whatever
 // reads wait there.  The running maximum of the attention kernels grows in most tiles of a short key
 // range (32 rows, t tiles seen: some row's with probability 32 / t), so its exchange is on the way of
-// every round: 16384 keys, 40 / 8 heads, 3 draft rows 16.5 -> 15.9 us per layer, 5 16.5 -> 16.4,
-// 12 20.1 -> 19.9, a tree of 20 27.2 -> 26.4.
+// every round: 16384 keys, 40 / 8 heads, 3 draft rows 16.9 -> 16.5 us per layer, 5 16.7 and 16.8,
+// 12 20.2 -> 20.0, 20 in chunks of 64 rows 28.3 -> 27.5.
 // (Assembly: this compiler takes the two results of the swap builtin for equal when its operands are.)
 LVS_DEV float max_halves(float x) {
   float y;
@@ -233,7 +233,7 @@ LVS_DEV uint32_t wave_max_u32(uint32_t x) {
 // maximum of a 64-bit unsigned key over the wave (identity 0): of the upper halves, then, among the
 // lanes that hold it, of the lower ones (mostly one lane: no second reduction).  The selection rounds of
 // the candidate lists are a chain of these: against one network of 64-bit steps 96 hidden rows, k = 4,
-// V = 152064, d = 5120 337 -> 327 us; 128 rows, V = 8192, d = 1024 36.2 -> 33.6.
+// V = 152064, d = 5120 328 -> 318 us; 128 rows, V = 8192, d = 1024 36.6 -> 33.9.
 LVS_DEV uint64_t wave_max_u64(uint64_t x) {
   const uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
   const uint32_t top = wave_max_u32(hi);
@@ -371,10 +371,10 @@ LVS_DEV void topk_insert(uint64_t& top, uint64_t (&key)[NV], int k, int lane) {
 // first keys need no places found for them, a third of a round (a small vocabulary has only first rows:
 // k = 16, d = 1024, 32 hidden rows, V = 8192 34.3 -> 27.4 us).  With many candidates asked for, more than
 // a handful enter in the first tasks of a pass: sorted in at once they cost as much as about five rounds,
-// however many enter.  All rounds against this, hidden rows, V / d, k: 128, 152064 / 3584, 16 398 -> 335 us;
-// 100, 32000 / 2048, 16 87.7 -> 62.3 and 8 63.9 -> 59.4; 32, 8192 / 1024, 16 35.8 -> 23.4.  For k = 4 the
-// rounds stay the shorter way (128 rows, d = 8192 533 us, sorted 563); 3, 5 and 8 lanes as the bound
-// 336, 335 and 348 us on the first of these.  The networks are not in the code where nobody asks for
+// however many enter.  All rounds against this, hidden rows, V / d, k: 128, 152064 / 3584, 16 393 -> 328 us;
+// 100, 32000 / 2048, 16 89.5 -> 61.7 and 8 65.2 -> 61.1; 32, 8192 / 1024, 16 37.6 -> 23.2.  For k = 4 the
+// rounds stay the shorter way (128 rows, d = 8192 533 us, sorted 563); 8 lanes as the bound are 4 % slower than
+// 5 on the first of these, 3 the same.  The networks are not in the code where nobody asks for
 // them: there they cost short passes 0.2 us (16 rows, k = 4, V = 8192 17.6 -> 17.8).
 constexpr int kSortTopk = 6;
 constexpr int kSortLanes = 5;
