@@ -137,3 +137,19 @@ def test_lds_summary_reads_conflict_share_per_kernel(tmp_path):
     lines = [ln for ln in text.splitlines() if "attn_split_kernel" in ln]
     assert len(lines) == 1 and "25.00%" in lines[0] and " 2 " in lines[0]
     assert "at::native" not in text
+
+
+def test_tracked_counters_are_of_the_cut_that_runs():
+    """attn_* in the stamp are the plan of the smallest workspace; bench.py runs with the one asked for, whose
+    plan is recorded beside them."""
+    import ctypes
+    import json
+    from paper_2604_05650_amd import binding as L
+    data = json.load(open(os.path.join(ROOT, "profiles", "traffic.json")))
+    for key in ("c2", "c3", "c4", "c4t", "c5"):
+        cfg = synth.CONFIGS[key]
+        a = L.AttnArgs()
+        a.B, a.gamma, a.Hq, a.Hkv, a.D, a.cap = cfg.B, cfg.gamma, cfg.Hq, cfg.Hkv, cfg.D, cfg.cap
+        a.max_kv_len = max(cfg.kv_len)
+        a.workspace_bytes = L.raw().lvspec_verify_attn_workspace(ctypes.byref(a))
+        assert data["stamp"]["plans"][cfg.name]["attn_run"] == list(L.describe_plan(attn=a).values()), key
