@@ -85,9 +85,9 @@ int lvspec_last_hip_error(void);
  * with workspace_bytes = 0; it may be less than lvspec_verify_attn_workspace asks for, and is accepted) is served by equal
  * splits instead: a sequence's bits then follow from its own data and length, the shapes and
  * max_kv_len alone, and a batch takes as long as its longest sequence.
- * More than 64 query rows per kv head (G * gamma): with max_kv_len given, long enough sequences and the
- * workspace asked for, up to 128 rows share a workgroup and one copy of the keys, with cuts of the keys
- * of their own.  A smaller workspace is served in row chunks of up to 64 rows.
+ * More than 64 query rows per kv head (G * gamma): where max_kv_len promises enough keys per workgroup,
+ * and with the workspace asked for, up to 128 rows share a workgroup and one copy of the keys, with cuts
+ * of the keys of their own.  A bound far above the lengths costs time there, so it should be a close one.  A smaller workspace is served in row chunks of up to 64 rows.
  * ------------------------------------------------------------------------------------------- */
 typedef struct {
   int32_t B, gamma, Hq, Hkv, D;     /* D must be 128; Hq % Hkv == 0; 1 <= gamma <= 32 */
